@@ -86,8 +86,8 @@ extern "C" {
 #define ME_JAMP_SCRATCH_BYTES (4ull << 30)
 /* device scratch of the split executor's colour-group sums and colour flows */
 #define ME_SPLIT_SCRATCH_BYTES (16ull << 30)
-/* Scratch of the fused helicity-recycling launches (me_set_bg variant 4): one slot
- * of dual amplitudes per workgroup of a launch. */
+/* Scratch of the fused recursion's launches (me_set_bg variant 4): one slot of dual
+ * amplitudes per workgroup of a launch. */
 #define ME_BG_FUSED_SCRATCH_BYTES (4ull << 30)
 
 typedef struct me_ctx* me_handle;
@@ -329,12 +329,14 @@ int me_set_split(me_handle h, int wpe, int fchunk, int rounds, int colour_grid);
  * threads per workgroup, 1 = half of both, 2 = twice both; 3 = helicity
  * recycling (four and five gluons: one workgroup per event(s), every current and
  * row spinor formed once per helicity assignment of its own particles, the full
- * orderings walked in rotation cycles); 4 = helicity recycling with the colour
- * form (FP64, or split FP16 / BF16, on the matrix cores) and the helicity sum of
- * each event formed by the same workgroup, no colour or reduction kernel, launches
- * of as many event blocks as ME_BG_FUSED_SCRATCH_BYTES of dual-amplitude slots
- * hold; 5 = the same as one persistent launch over the whole batch (scratch: one
- * slot per resident workgroup, about 126 MB for g g -> t tbar g g g).  See
+ * orderings walked in rotation cycles); 4 = the recursion from both ends of the
+ * quark line, one helicity of each mirror pair, canonical orderings of the long
+ * currents, with the colour form (FP64 in symmetry sectors, or split FP16 / BF16,
+ * on the matrix cores) and the helicity sum of each event formed by the same
+ * workgroup, no colour or reduction kernel, launches of as many event blocks as
+ * ME_BG_FUSED_SCRATCH_BYTES of dual-amplitude slots hold; 5 = the same as one
+ * persistent launch over the whole batch (scratch: one slot per resident workgroup,
+ * 63 MB for g g -> t tbar g g g).  See
  * me_autotune.  ME_EINVAL for other values, and for 3, 4 and 5 on other processes.
  * Results do not depend on it beyond rounding. */
 int me_set_bg(me_handle h, int variant);

@@ -27,7 +27,8 @@ PROCESSES = ['gg_ttx', 'gg_ttxg', 'gg_ttxgg', 'gg_ttxggg', 'gg_ttxgggg']
 # headers the generated process units include
 PROC_HEADERS = ['me_device.h', 'me_kernels.h', 'me_process.h', 'colour_mfma.h', 'me_team.h']
 SDE_HEADERS = ['me_sde.h', 'me_sde_desc.h']
-BG_HEADERS = ['me_device.h', 'me_bg.h', 'me_bgh.h', 'me_bg_desc.h', 'colour_mfma.h', 'me_colour_big.h']
+BG_HEADERS = ['me_device.h', 'me_bg.h', 'me_bgh.h', 'me_bgm.h', 'me_bgm_shape.h', 'me_bg_desc.h', 'colour_mfma.h',
+              'me_colour_big.h']
 
 
 def bg_unit(name, n):
@@ -48,13 +49,13 @@ def bg_unit(name, n):
                   'BIG_GRID)), dim3(256), 0, s, jt, nrow, cf64, out);\n')
     tri = 0 if ncol <= 128 else 1
     return (f'// Berends-Giele executor of process {name} (generated).\n'
-            '#include <algorithm>\n#include "me_bgh.h"\n#include "colour_mfma.h"\n#include "me_colour_big.h"\n'
+            '#include <algorithm>\n#include "me_bgm.h"\n#include "colour_mfma.h"\n#include "me_colour_big.h"\n'
             'namespace me {\n'
             f'static hipError_t colour64_{name}(const double* jt, int64_t nrow, const double* cf64, double* out, '
             'hipStream_t s) {\n' + colour + '  return hipGetLastError();\n}\n'
             f'const BgDesc* bg_{name}() {{\n  static const BgDesc d = {{"{name}", {n}, {ncol}, &launch_bg<{n}>, '
-            f'&colour64_{name}, {tri}, {int(n in (4, 5))}, &bgh_fused_per_cu<{n}>, &bgh_fused_slot_doubles<{n}>, '
-            f'&bgh_block_events<{n}>}};\n'
+            f'&colour64_{name}, {tri}, {int(n in (4, 5))}, &bgm_fused_per_cu<{n}>, '
+            f'&bgm_fused_slot_doubles<{n}>, &bgm_block_events<{n}>}};\n'
             '  return &d;\n}\n}\n')
 ARCH = 'gfx950'
 HIPCC = os.environ.get('HIPCC', '/opt/rocm/bin/hipcc')
@@ -158,7 +159,8 @@ def generate_sources(procs, build_dir):
     units.append((os.path.join(CSRC, 'me_api.hip'), os.path.join(build_dir, 'me_api.o'),
                   [regfile, os.path.join(INCLUDE, 'megpu.h'), os.path.join(CSRC, 'me_process.h'),
                    os.path.join(CSRC, 'me_error.h'), os.path.join(CSRC, 'me_sde_desc.h'),
-                   os.path.join(CSRC, 'me_bg_desc.h'), os.path.join(CSRC, 'me_bg_tables.h')]))
+                   os.path.join(CSRC, 'me_bg_desc.h'), os.path.join(CSRC, 'me_bg_tables.h'),
+                   os.path.join(CSRC, 'me_bgm_tables.h'), os.path.join(CSRC, 'me_bgm_shape.h')]))
     units.append((os.path.join(CSRC, 'surrogate.hip'), os.path.join(OBJ, 'surrogate.o'),
                   [os.path.join(INCLUDE, 'megpu.h'), os.path.join(CSRC, 'me_error.h')]))
     return units

@@ -23,6 +23,7 @@
 #include "me_sde_desc.h"
 #include "me_bg_desc.h"
 #include "me_bg_tables.h"
+#include "me_bgm_tables.h"
 
 namespace me {
 #include "registry.inc"   // const ProcessDesc* (*const kProcesses[])() and kNumProcesses
@@ -188,6 +189,9 @@ struct me_ctx {
   uint16_t* d_bg_cyc = nullptr;      // rotation-cycle tables of the helicity-recycling kernel
   int n_bg_cyc = 0;                  // [seg | cbase | rbase] sizes
   int n_bg_slot = 0;
+  uint32_t* d_bgm = nullptr;         // work-item tables of the two-sided recursion
+  uint16_t* d_bgm_orb = nullptr;     // orbits and sectors of its FP64 colour form
+  float* d_bgm_sec = nullptr;
   me_params params{};
   std::vector<int> good;      // host copy of the good helicities
   int* d_hels = nullptr;      // device, good helicities (capacity nhel)
@@ -225,7 +229,7 @@ struct me_ctx {
   int split_fchunk = 0;       // flows kernel: group sums per LDS chunk (8, 16, 32)
   int split_rounds = 0;       // events per chunk as whole rounds of group-sum waves (0: as many as fit)
   int colour_grid = 0;        // workgroups of the FP64 colour kernel
-  int bg_variant = 0;         // Berends-Giele kernel: launch shape 0, 1, 2; 3 = helicity recycling; 4 = the same, FP64 colour form fused
+  int bg_variant = 0;         // Berends-Giele kernel: launch shape 0, 1, 2; 3 = helicity recycling; 4, 5 = two-sided recursion, colour form fused
   int bg_grid = 0;            // workgroups (scratch slots) per launch of the fused kernel
   int bg_resident = 0;        // its resident workgroups on the device
   bool tuned = false;         // me_autotune has run (or found its configuration in the cache)
@@ -331,6 +335,14 @@ int enqueue_soa(me_ctx* c, const double* momenta, int64_t nevt, hipStream_t s) {
   return ME_OK;
 }
 
+// A new device array with the contents of v.
+template <class T>
+hipError_t upload(T** p, const std::vector<T>& v) {
+  hipError_t e = hipMalloc(p, v.size() * sizeof(T));
+  if (e == hipSuccess) e = hipMemcpy(*p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice);
+  return e;
+}
+
 // Sequence tables of the Berends-Giele executor, uploaded on first use.
 int ensure_bg_tables(me_ctx* c) {
   if (c->d_bg_sub) return ME_OK;
@@ -350,12 +362,23 @@ int ensure_bg_tables(me_ctx* c) {
     c->n_bg_slot = (int)cy.cbase.size();
     e = hipMalloc(&c->d_bg_cyc, all.size() * sizeof(uint16_t));
     if (e == hipSuccess) e = hipMemcpy(c->d_bg_cyc, all.data(), all.size() * sizeof(uint16_t), hipMemcpyHostToDevice);
+    const std::vector<uint32_t> m = c->bg->n == 4 ? me::BgmBuilder<4>().build() : me::BgmBuilder<5>().build();
+    if (e == hipSuccess) e = upload(&c->d_bgm, m);
+    const me::BgmSectors sc = me::bgm_sectors(c->bg->n, c->desc->cf_int);
+    if (e == hipSuccess) e = upload(&c->d_bgm_orb, sc.orb);
+    if (e == hipSuccess) e = upload(&c->d_bgm_sec, me::bgm_sector_operands(sc));
   }
   if (e != hipSuccess) {
     if (c->d_bg_sub) (void)hipFree(c->d_bg_sub);
     if (c->d_bg_mask) (void)hipFree(c->d_bg_mask);
     if (c->d_bg_last) (void)hipFree(c->d_bg_last);
     if (c->d_bg_cyc) (void)hipFree(c->d_bg_cyc);
+    if (c->d_bgm) (void)hipFree(c->d_bgm);
+    if (c->d_bgm_orb) (void)hipFree(c->d_bgm_orb);
+    if (c->d_bgm_sec) (void)hipFree(c->d_bgm_sec);
+    c->d_bgm = nullptr;
+    c->d_bgm_orb = nullptr;
+    c->d_bgm_sec = nullptr;
     c->d_bg_sub = nullptr;
     c->d_bg_mask = c->d_bg_last = nullptr;
     c->d_bg_cyc = nullptr;
@@ -366,9 +389,9 @@ int ensure_bg_tables(me_ctx* c) {
 
 // Events per chunk of the Berends-Giele executor: the dual amplitudes of a chunk
 // (2 NCOL doubles per row, nhel rows per event) fill at most ME_SPLIT_SCRATCH_BYTES.
-// The Berends-Giele executor runs its persistent kernel with the colour form (FP64,
+// The Berends-Giele executor runs the two-sided recursion with the colour form (FP64,
 // or split FP16 / BF16 on the matrix cores) and the helicity sum fused (launch
-// variant 4).
+// variants 4 and 5).
 bool bg_fused(const me_ctx* h) {
   return h->executor == ME_EXEC_BG && (h->bg_variant == 4 || h->bg_variant == 5) && h->bg->recycle &&
          h->bg->fused_slot_doubles;
@@ -377,9 +400,9 @@ bool bg_fused(const me_ctx* h) {
 // Event blocks per launch of the fused kernel: variant 5 = one persistent launch over
 // the resident workgroups; variant 4 = launches of as many blocks as
 // ME_BG_FUSED_SCRATCH_BYTES of slots hold, in whole rounds of the resident workgroups.
-int64_t bg_fused_blocks(const me_ctx* h, int nhel) {
+int64_t bg_fused_blocks(const me_ctx* h) {
   if (h->bg_variant == 5) return h->bg_resident;
-  const int64_t slot = (int64_t)h->bg->fused_slot_doubles(nhel) * (int64_t)sizeof(double);
+  const int64_t slot = h->bg->fused_slot_doubles() * (int64_t)sizeof(double);
   int64_t b = (int64_t)(ME_BG_FUSED_SCRATCH_BYTES / (uint64_t)slot);
   if (b >= h->bg_resident) b = (b / h->bg_resident) * h->bg_resident;
   return std::max<int64_t>(1, b);
@@ -735,6 +758,9 @@ int me_finalize(me_handle h) {
   if (h->d_bg_mask) (void)hipFree(h->d_bg_mask);
   if (h->d_bg_last) (void)hipFree(h->d_bg_last);
   if (h->d_bg_cyc) (void)hipFree(h->d_bg_cyc);
+  if (h->d_bgm) (void)hipFree(h->d_bgm);
+  if (h->d_bgm_orb) (void)hipFree(h->d_bgm_orb);
+  if (h->d_bgm_sec) (void)hipFree(h->d_bgm_sec);
   if (h->graph) (void)hipGraphExecDestroy(h->graph);
   if (h->capture_stream) (void)hipStreamDestroy(h->capture_stream);
   free_tables(h);
@@ -886,8 +912,8 @@ int prepare(me_ctx* h, int64_t nevt) {
       const int per_cu = h->bg->fused_per_cu ? h->bg->fused_per_cu() : 0;
       if (per_cu < 1) return fail(ME_EHIP, "fused Berends-Giele kernel: no resident workgroup fits");
       h->bg_resident = per_cu * std::max(1, h->simds / 4);
-      h->bg_grid = (int)bg_fused_blocks(h, nhel);
-      return ensure_sums(h, (size_t)h->bg_grid * (size_t)h->bg->fused_slot_doubles(nhel));
+      h->bg_grid = (int)bg_fused_blocks(h);
+      return ensure_sums(h, (size_t)h->bg_grid * (size_t)h->bg->fused_slot_doubles());
     }
     // dual amplitudes of an event chunk [2 NCOL][rows] in the split scratch, then
     // one colour sum per row
@@ -961,20 +987,19 @@ int enqueue(me_ctx* h, const double* momenta, int64_t nevt, double alpha_s, doub
     const bool fp64 = h->params.colorsum_mode == ME_CS_FP64;
     const double scale = fp64 ? 1.0 / ((double)h->desc->iden * (double)h->desc->cf_den) : 1.0 / h->desc->iden;
     if (bg_fused(h)) {
-      // recursion, colour form and helicity sum of each event block in one kernel
-      // (every colour form in units of the integer matrix), one scratch slot per
-      // workgroup: variant 5 one persistent launch, variant 4 launches of bg_grid
-      // blocks
-      const int ev = h->bg->fused_block_events();
-      const int64_t chunk = h->bg_variant == 5 ? nevt : (int64_t)h->bg_grid * ev;
+      // recursion, colour form and helicity sum of each event in one kernel (every
+      // colour form in units of the integer matrix), one scratch slot per workgroup:
+      // variant 5 one persistent launch, variant 4 launches of bg_grid event blocks
+      const int64_t chunk = h->bg_variant == 5 ? nevt : (int64_t)h->bg_grid * h->bg->fused_block_events();
       for (int64_t off = 0; off < nevt; off += chunk) {
         const int64_t n = std::min<int64_t>(chunk, nevt - off);
         me::BgArgs a{momenta + off * npar * 4, n, g, h->params.mt, h->d_hels, nhel, h->d_bg_sub, h->d_bg_mask,
                      h->d_bg_last, alphas ? alphas + off : nullptr, h->d_sums, s};
         a.variant = h->bg_variant;
-        a.cyc = me::BgCycles{h->d_bg_cyc, h->d_bg_cyc + h->n_bg_cyc, h->d_bg_cyc + h->n_bg_cyc + h->n_bg_slot};
+        a.bgm = h->d_bgm;
         a.fmt = fp64 ? -1 : (h->params.colorsum_mode == ME_CS_FP16X2 ? 0 : 1);   // CS_FMT_FP16, CS_FMT_BF16
-        a.cft = h->d_cf64_tri;
+        a.orb = h->d_bgm_orb;
+        a.sec = h->d_bgm_sec;
         a.cf_hi = h->d_cf_hi;
         a.cf_lo = h->d_cf_lo;
         a.out = out_me2 + off;

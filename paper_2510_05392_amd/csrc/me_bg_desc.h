@@ -22,7 +22,7 @@ struct BgCycles {
 };
 
 // One chunk of rows: row = k n + e (good helicity k, event e of the chunk) for
-// variants 0 .. 2, row = e nhel + k for variants 3 and 4 (helicity recycling).
+// variants 0 .. 2, row = e nhel + k for variant 3 (helicity recycling).
 struct BgArgs {
   const double* mom;     // device, [n][npar][4] (the chunk's events)
   int64_t n;
@@ -36,11 +36,13 @@ struct BgArgs {
   double* jt;            // device, dual amplitudes [2 NCOL][n nhel]
   hipStream_t stream;
   int variant = 0;       // 0, 1, 2: one row per item, launch shapes; 3: helicity recycling;
-                         // 4: helicity recycling with the FP64 colour form fused
-  BgCycles cyc{nullptr, nullptr, nullptr};   // variants 3 and 4 only
-  // variant 4 (persistent kernel): jt is grid slots of [2 NCOL][EV nhel]
+                         // 4, 5: two-sided recursion with the colour form fused
+  BgCycles cyc{nullptr, nullptr, nullptr};   // variant 3 only
+  // variants 4 and 5 (two-sided recursion, colour form fused): jt is grid slots
+  const uint32_t* bgm = nullptr; // its work-item tables (BgmBuilder)
+  const uint16_t* orb = nullptr; // orbits and sectors of the FP64 colour form (bgm_sectors)
+  const float* sec = nullptr;
   int fmt = -1;                  // colour form: -1 FP64, 0 split FP16, 1 split BF16 (CS_FMT_*)
-  const double* cft = nullptr;   // FP64: block-triangular colour matrix [16 MB][4 KS]
   const void* cf_hi = nullptr;   // split formats: colour-matrix tables [32 MB][16 KS] (lo may be null)
   const void* cf_lo = nullptr;
   double* out = nullptr;         // per-event |M|^2 [n] (nullptr: variant 4 runs as 3)
@@ -60,9 +62,9 @@ struct BgDesc {
   BgLauncher launch;
   Colour64Launcher colour64;
   int colour_tri;        // 1: colour64 takes the block-triangular matrix, 0: the full one
-  int recycle;           // 1: launch variants 3 and 4 (helicity recycling) are built
+  int recycle;           // 1: launch variants 3, 4 and 5 (helicity recycling) are built
   int (*fused_per_cu)();                 // resident workgroups per CU of the fused kernel (variants 4, 5)
-  int64_t (*fused_slot_doubles)(int nhel);   // its scratch per workgroup
+  int64_t (*fused_slot_doubles)();       // its scratch per workgroup
   int (*fused_block_events)();           // its events per workgroup block
 };
 

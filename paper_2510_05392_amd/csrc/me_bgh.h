@@ -18,12 +18,6 @@
 // current J(sigma), the row spinors R(sigma[:N-2]) and R(sigma[:N-1]) of each top
 // helicity, W = sum_{k>=1} R(sigma[:k]) (i g gamma.J(sigma[k:])), and the
 // amplitudes Q.J(sigma) + W v of the four quark helicity pairs.
-//
-// With the colour form fused (launch variant 4, FP64 mode) the workgroup then reads
-// its own rows' dual amplitudes back and forms Re(J^H CF J) of each row on the FP64
-// matrix cores, the block-triangular colour matrix staged in the LDS the frames
-// held; the separate colour kernel and its launch go away, and the matrix-core work
-// of one workgroup overlaps the vector work of the others on the same compute unit.
 #pragma once
 #include "me_bg.h"
 
@@ -462,245 +456,6 @@ __device__ __forceinline__ void bgh_krow(const int* hrow, int gh, int* krow) {
 }
 
 #ifdef __HIPCC__
-}  // namespace me
-#include "colour_mfma.h"
-namespace me {
-
-typedef double bgh_f64x4 __attribute__((ext_vector_type(4)));
-
-// Block-triangular colour matrix staged in LDS as FP32 (exact: integer entries
-// below 2^24): the 16 x 16 blocks (mb, kb) with kb >= mb, block-row major, rows
-// BGH_CS floats apart (16 + 2: the 16 rows x 2 K indices of a half-wave read
-// fall in distinct banks).
-constexpr int BGH_CS = 18;
-template <int NCOL>
-struct BghColour {
-  static constexpr int KS = (NCOL + 3) / 4;     // K steps of 4 flows
-  static constexpr int KP = 4 * KS;             // row length of the FP64 matrix
-  static constexpr int MB = (NCOL + 15) / 16;   // 16-flow blocks
-  static constexpr int NBLK = MB * (MB + 1) / 2;
-  static constexpr int FLOATS = NBLK * 16 * BGH_CS;
-  static constexpr int blk(int mb, int kb) { return mb * MB - mb * (mb - 1) / 2 + (kb - mb); }
-};
-
-// FP64 colour form of the rows r0 .. r0 + nr - 1 of jt [2 NCOL][rows] into
-// out[row] = sum_ik CF'[i][k] (A_i A_k + B_i B_k), J = A + iB, CF' the block-
-// triangular matrix (cft: [16 MB][KP] FP64, diagonal blocks CF, blocks above 2 CF,
-// zero below; same quadratic form as CF).  Every thread of the workgroup takes
-// part; cfs holds at least BghColour<NCOL>::FLOATS floats.  One wave per tile of 8
-// rows: v_mfma_f64_16x16x4f64 with the matrix block as A (lane l: row l % 16, K
-// index l / 16) and the real and imaginary parts of the 8 rows as the 16 columns
-// of B; D[i][j] sits in lane j + 16 (i % 4), element i / 4.  The column blocks kb
-// are taken from the last to the first: block row kb then has all its products,
-// and its row dots use the B operands just loaded for block kb (the flows of a
-// lane's B elements are those of its D elements), so each operand is read once.
-template <int NCOL, int THREADS>
-__device__ __forceinline__ void bgh_colour_rows(const double* __restrict__ jt, int64_t rows, int64_t r0, int nr,
-                                                const double* __restrict__ cft, float* cfs,
-                                                double* __restrict__ out) {
-  using C = BghColour<NCOL>;
-  constexpr int KS = C::KS, MB = C::MB;
-  for (int i = threadIdx.x; i < C::NBLK * 256; i += THREADS) {
-    const int b = i >> 8, e = i & 255, r = e >> 4, c = e & 15;
-    int mb = 0;
-    while (mb + 1 < MB && C::blk(mb + 1, mb + 1) <= b) ++mb;
-    const int kb = mb + (b - C::blk(mb, mb));
-    const int col = 16 * kb + c;
-    cfs[b * 16 * BGH_CS + r * BGH_CS + c] = col < C::KP ? (float)cft[(int64_t)(16 * mb + r) * C::KP + col] : 0.0f;
-  }
-  __syncthreads();
-  const int l = threadIdx.x & 63;
-  const int j = l & 15, part = j >> 3;
-  const int ntile = (nr + 7) >> 3;
-  for (int tile = threadIdx.x >> 6; tile < ntile; tile += THREADS / 64) {
-    // the matrix operands are read from LDS in each tile: kept out of registers
-    // across tiles (hoisted, the 128 of them would not fit)
-    asm volatile("" ::: "memory");
-    // the row stride is opaque in each tile: the flow offsets are formed as the loads
-    // need them instead of being hoisted out of the loops
-    int64_t rs = rows;
-    int kq = l >> 4;   // the lane's K index, likewise formed in each tile
-    asm volatile("" : "+s"(rs), "+v"(kq));
-    const int rr = 8 * tile + (j & 7);
-    const bool valid = rr < nr;
-    const double* x = jt + (int64_t)(part + 2 * kq) * rs + r0 + (valid ? rr : 0);
-    bgh_f64x4 acc[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb) acc[mb] = bgh_f64x4{0.0, 0.0, 0.0, 0.0};
-    double s = 0.0;
-#pragma unroll
-    for (int kb = MB - 1; kb >= 0; --kb) {
-      double b[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int ks = 4 * kb + q;
-        b[q] = (ks < KS && 4 * ks + kq < NCOL && valid) ? x[(int64_t)(8 * ks) * rs] : 0.0;
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (4 * kb + q >= KS) continue;
-#pragma unroll
-        for (int mb = 0; mb <= kb; ++mb) {
-          const double a = (double)cfs[C::blk(mb, kb) * 16 * BGH_CS + j * BGH_CS + 4 * q + kq];
-          acc[mb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[q], acc[mb], 0, 0, 0);
-        }
-      }
-      // row dots of block row kb: D[i][j], i = 16 kb + 4 v + kq, X[i][j] = b[v]
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (4 * kb + v < KS) s += b[v] * acc[kb][v];
-    }
-    s += __shfl_xor(s, 16);
-    s += __shfl_xor(s, 32);
-    s += __shfl_xor(s, 8);
-    if (l < 8 && valid) out[r0 + rr] = s;
-  }
-}
-
-// Records, for each row of an event, the largest |Re| and |Im| of its amplitudes
-// (bits of a non-negative double, which order as the unsigned integers) with LDS
-// atomics: the power-of-two scale of the FP16 colour form without a pass over the
-// row.
-struct BghRowMax {
-  unsigned long long* m;
-  __device__ __forceinline__ void operator()(int k, double re, double im) const {
-    atomicMax(m + k, (unsigned long long)__double_as_longlong(fmax(fabs(re), fabs(im))));
-  }
-};
-
-// Split-precision colour matrix staged in LDS for the fused kernel: flows in blocks
-// of 32, the block-triangular form (blocks (mb, kb), kb >= mb: CF on the diagonal,
-// 2 CF above; the same quadratic form as CF; the doubled entries stay exact), the
-// 32 rows of each block permuted so that a lane's accumulator rows are the flows
-// of its own B operand (M index i = 8 q + 4 h + s, q < 4, h < 2, s < 4 holds flow
-// 16 (q >> 1) + 8 h + 4 (q & 1) + s), rows of BGH_SV 16-byte vectors (4 + 1: the
-// pad puts the 16-byte reads of 8 consecutive rows on distinct banks).
-constexpr int BGH_SV = 5;
-template <int NCOL>
-struct BghSplit {
-  static constexpr int MB = (NCOL + 31) / 32;
-  static constexpr int NBLK = MB * (MB + 1) / 2;
-  static constexpr int VECS = NBLK * 32 * BGH_SV;   // 16-byte vectors per table
-  static constexpr int blk(int mb, int kb) { return mb * MB - mb * (mb - 1) / 2 + (kb - mb); }
-  static __device__ __forceinline__ int flow(int i) {
-    return 16 * (i >> 4) + 8 * ((i >> 2) & 1) + 4 * ((i >> 3) & 1) + (i & 3);
-  }
-};
-
-// Split-precision colour form (FMT = CS_FMT_FP16 or CS_FMT_BF16) of the rows
-// 0 .. nr - 1 of jt [2 NCOL][rows], by the whole workgroup: one wave per tile of 16
-// rows (32 B columns: real and imaginary parts), each row split into hi + lo in the
-// format (FP16 rows first scaled by the power of two that puts their largest
-// element, rmax[row], in [1, 2): exact), v_mfma_f32_32x32x16 against the staged
-// block-triangular matrix, FP64 row dots.  The column blocks kb are taken from the
-// last to the first, so that the rows of block kb are complete once kb is done and
-// their dots use the amplitudes just loaded for it: every amplitude is read once.
-// cf_hi / cf_lo: the format's [32 MB][16 KS] tables (cf_lo may be null); cfs holds
-// 2 BghSplit<NCOL>::VECS vectors.  out[row] = ME_row in units of the integer matrix.
-template <int NCOL, int FMT, int THREADS>
-__device__ __forceinline__ void bgh_colour_rows_split(const double* __restrict__ jt, int64_t rows, int nr,
-                                                      const void* __restrict__ cf_hi_raw,
-                                                      const void* __restrict__ cf_lo_raw, void* cfs_raw,
-                                                      const unsigned long long* rmax, double* __restrict__ out) {
-  typedef cs_types<FMT> T;
-  typedef typename T::vec vec;
-  typedef typename T::elem elem;
-  using B = BghSplit<NCOL>;
-  constexpr int MB = B::MB;
-  constexpr int KP = 16 * ((NCOL + 15) / 16);   // row length of the global tables
-  vec* cfs = reinterpret_cast<vec*>(cfs_raw);
-  const bool two = cf_lo_raw != nullptr;
-  for (int i = threadIdx.x; i < (two ? 2 : 1) * B::NBLK * 128; i += THREADS) {
-    const int tb = i / (B::NBLK * 128), rem = i % (B::NBLK * 128);
-    const int b = rem >> 7, row = (rem >> 2) & 31, w = rem & 3;
-    int mb = 0;
-    while (mb + 1 < MB && B::blk(mb + 1, mb + 1) <= b) ++mb;
-    const int kb = mb + (b - B::blk(mb, mb));
-    const int fa = 32 * mb + B::flow(row), col = 32 * kb + 8 * w;
-    vec v;
-    if (fa < NCOL && col < KP) {
-      v = reinterpret_cast<const vec*>(tb ? cf_lo_raw : cf_hi_raw)[(fa * KP + col) / 8];
-      if (kb > mb)
-#pragma unroll
-        for (int t = 0; t < 8; ++t) v[t] = (elem)(2.0f * (float)v[t]);
-    } else {
-#pragma unroll
-      for (int t = 0; t < 8; ++t) v[t] = (elem)0.0f;
-    }
-    cfs[tb * B::VECS + (b * 32 + row) * BGH_SV + w] = v;
-  }
-  __syncthreads();
-  const int l = threadIdx.x & 63;
-  const int j = l & 31, r = j & 15, part = j >> 4;
-  const int ntile = (nr + 15) >> 4;
-  for (int tile = threadIdx.x >> 6; tile < ntile; tile += THREADS / 64) {
-    // the row stride and the lane's K half are opaque in each tile, so that the flow
-    // offsets are formed as the loads need them, not hoisted out of the loops
-    int64_t rs = rows;
-    int half = l >> 5;
-    asm volatile("" : "+s"(rs), "+v"(half) : : "memory");
-    const int row = 16 * tile + r;
-    const bool valid = row < nr;
-    const double* x = jt + (int64_t)part * rs + (valid ? row : 0);
-    double scale = 1.0, unscale = 1.0;
-    if (FMT == CS_FMT_FP16) {
-      const double m = valid ? __longlong_as_double((long long)rmax[row]) : 0.0;
-      if (m > 0.0) {
-        const int e = ilogb(m);
-        scale = ldexp(1.0, -e);
-        unscale = ldexp(1.0, e);
-      }
-    }
-    const vec* ap = cfs + j * BGH_SV + half;
-    f32x16 acc[MB];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[mb][v] = 0.0f;
-    double sum = 0.0;
-#pragma unroll
-    for (int kb = MB - 1; kb >= 0; --kb) {
-      double xv[2][8];
-#pragma unroll
-      for (int ss = 0; ss < 2; ++ss)
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int c = 32 * kb + 16 * ss + 8 * half + t;
-          xv[ss][t] = (c < NCOL && valid) ? x[(int64_t)(2 * c) * rs] : 0.0;
-        }
-#pragma unroll
-      for (int ss = 0; ss < 2; ++ss) {
-        vec bh, bl;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const double v = xv[ss][t] * scale;
-          const elem hi = cs_round<elem>(v);
-          bh[t] = hi;
-          bl[t] = cs_round<elem>(v - (double)hi);
-        }
-#pragma unroll
-        for (int mb = 0; mb <= kb; ++mb) {
-          const vec a = ap[B::blk(mb, kb) * 32 * BGH_SV + 2 * ss];
-          acc[mb] = T::mfma(a, bh, acc[mb]);
-          acc[mb] = T::mfma(a, bl, acc[mb]);
-          if (two) {
-            const vec a2 = ap[B::VECS + B::blk(mb, kb) * 32 * BGH_SV + 2 * ss];
-            acc[mb] = T::mfma(a2, bh, acc[mb]);
-            acc[mb] = T::mfma(a2, bl, acc[mb]);
-          }
-        }
-      }
-      // rows of block kb: D element v is M row i = 8 (v >> 2) + 4 half + (v & 3),
-      // flow 32 kb + 16 (v >> 3) + 8 half + 4 ((v >> 2) & 1) + (v & 3)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) sum += xv[v >> 3][4 * ((v >> 2) & 1) + (v & 3)] * (double)acc[kb][v];
-    }
-    sum += __shfl_xor(sum, 32);   // the two K halves
-    sum += __shfl_xor(sum, 16);   // real + imaginary parts
-    if (l < 16 && valid) out[row] = sum * unscale;
-  }
-}
-
 // The work of one block of EV events e0 .. e0 + nev - 1, all good helicities, by
 // the whole workgroup: set-up, then for L = 2 .. N-2 the currents of length L with
 // the row spinors of length L - 1, then the cycle items, barriers between levels.
@@ -712,14 +467,10 @@ __device__ __forceinline__ void bgh_block(double* lds, const uint8_t* sm, uint16
                                           const double* __restrict__ mom, int64_t e0, int nev, double g0,
                                           double mt, int nhel, const BgTables& t, const BgCycles& cy,
                                           const double* __restrict__ alphas, double* __restrict__ jt, int64_t rows,
-                                          int64_t rbase, unsigned long long* rmax = nullptr) {
+                                          int64_t rbase) {
   using S = BgShape<N>;
   using H = BghShape<N>;
   constexpr int NPAR = N + 2;
-  // rmax (optional, LDS): largest |Re|, |Im| of the amplitudes of each row, at
-  // ev nhel + k
-  if (rmax)
-    for (int i = threadIdx.x; i < nev * nhel; i += THREADS) rmax[i] = 0ull;
   for (int i = threadIdx.x; i < nev * NPAR * 4; i += THREADS)
     lds[(i / (NPAR * 4)) * H::FRAME + H::MOFF + i % (NPAR * 4)] = mom[e0 * NPAR * 4 + i];
   for (int i = threadIdx.x; i < nev; i += THREADS)
@@ -753,11 +504,7 @@ __device__ __forceinline__ void bgh_block(double* lds, const uint8_t* sm, uint16
     if (krow[0] < 0 && krow[1] < 0 && krow[2] < 0 && krow[3] < 0) continue;
     bgh_fill_item<N>(tab, THREADS, t, cy, z, gh);
     const BghItem<N> item{tab, THREADS, sm + z * N * N};
-    if (rmax)
-      bgh_cycle_item<N>(lds + ev * H::FRAME, cy, item, z, krow, mt, jt, rows, rbase + (int64_t)ev * nhel,
-                        BghRowMax{rmax + ev * nhel});
-    else
-      bgh_cycle_item<N>(lds + ev * H::FRAME, cy, item, z, krow, mt, jt, rows, rbase + (int64_t)ev * nhel);
+    bgh_cycle_item<N>(lds + ev * H::FRAME, cy, item, z, krow, mt, jt, rows, rbase + (int64_t)ev * nhel);
   }
 }
 
@@ -798,71 +545,6 @@ bgh_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt, cons
   bgh_block<N, EV, THREADS>(lds, sm, tabs, hrow, mom, e0, nev, g0, mt, nhel, t, cy, alphas, jt, n * nhel, e0 * nhel);
 }
 
-// Launch variants 4 and 5: workgroup b takes the event blocks b, b + gridDim.x, ...
-// (one block each when the grid covers the launch's events, a persistent grid
-// otherwise).  For each block it writes the dual amplitudes to its own slot
-// of the scratch (jt + b [2 NCOL][EV nhel]), reads them back for the colour form of
-// its rows on the matrix cores (FMT < 0: FP64 with cft, the block-triangular colour
-// matrix staged in the LDS the frames held; else split FP16 / BF16 with the
-// format's tables cf_hi, cf_lo), sums each event's rows in helicity order and
-// writes out[e] = scale * sum.  No chunking: the scratch is the resident
-// workgroups' slots, and the whole batch is one launch.
-template <int N, int EV, int THREADS, int FMT, bool PERSIST>
-__global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2)))
-bgh_fused_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt, const int* __restrict__ hels,
-                 int nhel, BgTables t, BgCycles cy, const double* __restrict__ alphas, double* __restrict__ jt,
-                 const double* __restrict__ cft, const void* __restrict__ cf_hi, const void* __restrict__ cf_lo,
-                 double* __restrict__ out, double scale) {
-  using S = BgShape<N>;
-  using H = BghShape<N>;
-  using C = BghColour<S::NCOL>;
-  // row values after the staged matrix (float index, even): the FP64 form's
-  // block-triangular FP32 blocks, or the split forms' two block-triangular tables
-  constexpr int SPLIT_FLOATS = 2 * BghSplit<S::NCOL>::VECS * 4;
-  constexpr int RV = ((FMT < 0 ? C::FLOATS : SPLIT_FLOATS) + 1) & ~1;
-  static_assert(RV * sizeof(float) + (size_t)EV * (1 << (N + 2)) * sizeof(double) <=
-                    (size_t)EV * H::FRAME * sizeof(double),
-                "the staged colour matrix and the row values must fit in the frames");
-  extern __shared__ double lds[];
-  uint8_t* sm = reinterpret_cast<uint8_t*>(lds + EV * H::FRAME);
-  uint16_t* tabs = reinterpret_cast<uint16_t*>(sm + ((H::NCYC * N * N + 15) & ~15));
-  float* cfs = reinterpret_cast<float*>(lds);
-  double* rv = reinterpret_cast<double*>(cfs + RV);
-  __shared__ int hrow[1 << (N + 2)];
-  // the rows' largest amplitude components (FP16 scaling), written by the cycle items
-  __shared__ unsigned long long rmax[FMT == CS_FMT_FP16 ? EV << (N + 2) : 1];
-  bgh_tables<N, THREADS>(hrow, sm, hels, nhel, t, cy);
-  const int64_t srows = (int64_t)EV * nhel;
-  double* slot = jt + (int64_t)blockIdx.x * 2 * S::NCOL * srows;
-  // PERSIST: workgroup b takes the blocks b, b + gridDim.x, ...; else block b only
-  // (a loop over one block would keep its invariants live across iterations)
-  for (int64_t e0 = (int64_t)blockIdx.x * EV; e0 < n; e0 += PERSIST ? (int64_t)gridDim.x * EV : n) {
-    const int nev = (int)(n - e0 < EV ? n - e0 : EV);
-    bgh_block<N, EV, THREADS>(lds, sm, tabs, hrow, mom, e0, nev, g0, mt, nhel, t, cy, alphas, slot, srows, 0,
-                              FMT == CS_FMT_FP16 ? rmax : nullptr);
-    // every amplitude of the block is stored (workgroup-scope fence and barrier)
-    // and the frames are no longer read
-    __syncthreads();
-    // the colour phase (matrix cores, LDS) at a raised wave priority, so that its
-    // issue is not held behind the other workgroup's recursion (vector ALU)
-    __builtin_amdgcn_s_setprio(1);
-    if constexpr (FMT < 0)
-      bgh_colour_rows<S::NCOL, THREADS>(slot, srows, 0, nev * nhel, cft, cfs, rv);
-    else
-      bgh_colour_rows_split<S::NCOL, FMT, THREADS>(slot, srows, nev * nhel, cf_hi, cf_lo, cfs, rmax, rv);
-    __builtin_amdgcn_s_setprio(0);
-    __syncthreads();
-    // helicity sum of each event in row order (the order of reduce_rows_kernel)
-    for (int ev = threadIdx.x; ev < nev; ev += THREADS) {
-      double acc = 0.0;
-      for (int k = 0; k < nhel; ++k) acc += rv[ev * nhel + k];
-      out[e0 + ev] = scale * acc;
-    }
-    // the frames, the staged matrix and the slot are reused by the next block
-    if constexpr (PERSIST) __syncthreads();
-  }
-}
-
 // Events per workgroup and threads: the frames of EV events within about 56 KB.
 template <int N> struct BghLaunchShape;
 template <> struct BghLaunchShape<4> { static constexpr int EV = 8, THREADS = 256; };
@@ -881,104 +563,6 @@ hipError_t launch_bgh(const BgArgs& a) {
   hipLaunchKernelGGL((bgh_kernel<N, EV, THREADS>), dim3((unsigned)((a.n + EV - 1) / EV)), dim3(THREADS), lds,
                      a.stream, a.mom, a.n, a.g, a.mt, a.hels, a.nhel, t, a.cyc, a.alphas, a.jt);
   return hipGetLastError();
-}
-
-template <int N, int FMT, bool PERSIST>
-const void* bgh_fused_fn() {
-  constexpr int EV = BghLaunchShape<N>::EV, THREADS = BghLaunchShape<N>::THREADS;
-  return (const void*)bgh_fused_kernel<N, EV, THREADS, FMT, PERSIST>;
-}
-
-// Resident workgroups per compute unit of the fused persistent kernel (0 if not
-// built), the least over its colour-sum formats.
-template <int N>
-int bgh_fused_per_cu() {
-  if constexpr (N == 4 || N == 5) {
-    constexpr int EV = BghLaunchShape<N>::EV, THREADS = BghLaunchShape<N>::THREADS;
-    constexpr size_t lds = bgh_lds_bytes<N, EV, THREADS>();
-    int best = 1 << 20;
-    for (const void* fn : {bgh_fused_fn<N, -1, true>(), bgh_fused_fn<N, CS_FMT_FP16, true>(),
-                           bgh_fused_fn<N, CS_FMT_BF16, true>(), bgh_fused_fn<N, -1, false>(),
-                           bgh_fused_fn<N, CS_FMT_FP16, false>(), bgh_fused_fn<N, CS_FMT_BF16, false>()}) {
-      if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return 0;
-      int nb = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, THREADS, lds) != hipSuccess) return 0;
-      best = nb < best ? nb : best;
-    }
-    return best;
-  } else {
-    return 0;
-  }
-}
-
-// Events per workgroup block of the fused kernel (0 if not built).
-template <int N>
-int bgh_block_events() {
-  if constexpr (N == 4 || N == 5) {
-    return BghLaunchShape<N>::EV;
-  } else {
-    return 0;
-  }
-}
-
-// Doubles of scratch per workgroup of the fused kernel.
-template <int N>
-int64_t bgh_fused_slot_doubles(int nhel) {
-  if constexpr (N == 4 || N == 5) {
-    return (int64_t)2 * BgShape<N>::NCOL * BghLaunchShape<N>::EV * nhel;
-  } else {
-    return 0;
-  }
-}
-
-// Variant 4: one workgroup per event block (the launch's blocks must not exceed
-// a.grid slots); variant 5: a persistent grid of a.grid workgroups.
-template <int N, int FMT, bool PERSIST>
-hipError_t launch_bgh_fused_fmt(const BgArgs& a) {
-  constexpr int EV = BghLaunchShape<N>::EV, THREADS = BghLaunchShape<N>::THREADS;
-  constexpr size_t lds = bgh_lds_bytes<N, EV, THREADS>();
-  static const hipError_t attr = hipFuncSetAttribute(bgh_fused_fn<N, FMT, PERSIST>(),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (attr != hipSuccess) return attr;
-  if (!a.cyc.seg || !a.out || a.grid < 1 || (FMT < 0 ? !a.cft : !a.cf_hi)) return hipErrorInvalidValue;
-  if (a.n == 0 || a.nhel == 0) return hipSuccess;
-  const int64_t blocks = (a.n + EV - 1) / EV;
-  if (!PERSIST && blocks > a.grid) return hipErrorInvalidValue;   // one slot per block
-  const BgTables t{a.sub, a.mask, a.last};
-  const unsigned grid = (unsigned)(blocks < a.grid ? blocks : a.grid);
-  hipLaunchKernelGGL((bgh_fused_kernel<N, EV, THREADS, FMT, PERSIST>), dim3(grid), dim3(THREADS), lds, a.stream,
-                     a.mom, a.n, a.g, a.mt, a.hels, a.nhel, t, a.cyc, a.alphas, a.jt, a.cft, a.cf_hi, a.cf_lo, a.out,
-                     a.out_scale);
-  return hipGetLastError();
-}
-
-template <int N, bool PERSIST>
-hipError_t launch_bgh_fused_p(const BgArgs& a) {
-  if (a.fmt == CS_FMT_FP16) return launch_bgh_fused_fmt<N, CS_FMT_FP16, PERSIST>(a);
-  if (a.fmt == CS_FMT_BF16) return launch_bgh_fused_fmt<N, CS_FMT_BF16, PERSIST>(a);
-  return launch_bgh_fused_fmt<N, -1, PERSIST>(a);
-}
-
-template <int N>
-hipError_t launch_bgh_fused(const BgArgs& a) {
-  return a.variant == 5 ? launch_bgh_fused_p<N, true>(a) : launch_bgh_fused_p<N, false>(a);
-}
-
-// Launch of the executor's kernel in the chosen variant (3: helicity recycling,
-// 4 and 5: the kernel with the colour form and the helicity sum fused when a
-// per-event output is given, launched over a.grid workgroups; built for four and
-// five gluons).
-template <int N>
-hipError_t launch_bg(const BgArgs& a) {
-  if constexpr (N == 4 || N == 5) {
-    if ((a.variant == 4 || a.variant == 5) && a.out) return launch_bgh_fused<N>(a);
-    if (a.variant >= 3) return launch_bgh<N>(a);
-  } else {
-    if (a.variant >= 3) return hipErrorInvalidValue;
-  }
-  if (a.variant == 1) return launch_bg_v<N, 1>(a);
-  if (a.variant == 2) return launch_bg_v<N, 2>(a);
-  return launch_bg_v<N, 0>(a);
 }
 #endif
 

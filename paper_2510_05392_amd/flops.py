@@ -192,6 +192,28 @@ def bgh_event(n):
             'total': setup + currents + rows + items}
 
 
+# Two-sided recursion (csrc/me_bgm.h), one event: operations of its phases, counted by
+# compiling it for the host with the operation-counting scalar (tests/test_bgm.py)
+BGM = {4: {'setup': 1194, 'currents': 37944, 'spinors': 18796, 'qj': 56880, 'prefixes': 151488},
+       5: {'setup': 1970, 'currents': 406744, 'spinors': 59020, 'qj': 738432, 'prefixes': 2260992}}
+
+
+def bgm_event(n):
+    """FP64 flops of one event of the two-sided recursion (launch variants 4 and 5),
+    both quarks with pz >= 0: all 2^(n+1) pairs of mirrored helicities."""
+    return dict(BGM[n], total=sum(BGM[n].values()))
+
+
+def colour_sectors_flops(n):
+    """FP64 flops of one row's colour form in symmetry sectors (real and imaginary parts):
+    three stages of butterflies per orbit of eight, and per sector of m orbits the
+    product with its matrix and the dot product."""
+    orbits = {4: 4, 5: 16}[n]
+    fixed = 2 if n in (4, 5) else 0          # orbits of half length: absent from half of the sectors
+    dims = [orbits] * 4 + [orbits - fixed] * 4
+    return 2 * (24 * orbits + sum(2 * m * m + 2 * m for m in dims))
+
+
 def diagram_kernel(name, executor, bg_variant=0):
     """FP64 flops per (event, helicity) of the kernel that evaluates the diagrams:
     everything for the one-lane and team executors (flows and colour form are fused
@@ -208,14 +230,13 @@ def diagram_kernel(name, executor, bg_variant=0):
     if executor == 3:
         from .gen import codegen
         npar = codegen.PROCESS_NPAR[name]
-        if bg_variant in (3, 4, 5):
-            # per event over every helicity, shared out over the 2^npar rows
-            f = (bgh_event(npar - 2)['total'] + 6 * QUARK_BRANCH_MEAN) / 2 ** npar
-            if bg_variant in (4, 5):
-                from .gen.colour import colour_matrix
-                cf, _ = colour_matrix(npar - 2)
-                f += colour_sum_flops(cf)
-            return f
+        # per event over every helicity, shared out over the 2^npar rows
+        if bg_variant in (4, 5):
+            n = npar - 2
+            return (bgm_event(n)['total'] + 2 * QUARK_BRANCH_MEAN
+                    + 2 ** (n + 1) * colour_sectors_flops(n)) / 2 ** npar
+        if bg_variant == 3:
+            return (bgh_event(npar - 2)['total'] + 6 * QUARK_BRANCH_MEAN) / 2 ** npar
         return bg_row(npar - 2)['total'] + QUARK_BRANCH_MEAN
     return per_event_helicity(name) + QUARK_BRANCH_MEAN
 

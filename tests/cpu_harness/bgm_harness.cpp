@@ -1,0 +1,86 @@
+// Host build of the two-sided recursion (test-only): one event at a time, every phase's
+// items in turn, exactly the device functions the kernel runs per thread.
+#include <cstring>
+#include <vector>
+
+#include "me_bgm.h"
+#include "me_bgm_tables.h"
+
+template <int N>
+void bgm_eval(const double* mom, int nevt, double g, double mt, double* jamps) {
+  using namespace me;
+  using S = BgmShape<N>;
+  const std::vector<uint32_t> t = BgmBuilder<N>().build();
+  std::vector<cx16> frame((S::FRAME + 1) / 2), slot(S::SLOT / 2);
+  double* F = &frame[0].r;
+  double* jt = &slot[0].r;
+  for (int e = 0; e < nevt; ++e) {
+    for (int i = 0; i < (N + 2) * 4; ++i) F[S::MOFF + i] = mom[e * (N + 2) * 4 + i];
+    F[S::GOFF] = g;
+    for (int i = 0; i < (1 << N); ++i) bgm_setup_subset<N>(F, mt, i);
+    for (int i = 0; i < 2 * N - 1; ++i) bgm_setup_gluon<N>(F, i);
+    for (int i = 0; i < 4; ++i) bgm_setup_spinor<N>(F, mt, i);
+    for (int i = 0; i < 4; ++i) bgm_setup_q<N>(F, i);
+    cx j[4];
+    for (int i = 0; i < S::V(2); ++i) {
+      bgm_current<N, 2>(F, BgmRec<S::F2>(t.data() + S::T2, S::V(2), i), j);
+      bgm_store<N>(F, S::cslot(2) + i, j);
+    }
+    for (int i = 0; i < 2 * S::V(1); ++i) {
+      bgm_row1_item<N>(F, t.data(), mt, i >> 1, i & 1);
+      bgm_col1_item<N>(F, t.data(), mt, i >> 1, i & 1);
+    }
+    for (int i = 0; i < S::SV(3); ++i) {
+      bgm_current<N, 3>(F, BgmRec<S::F3>(t.data() + S::T3, S::SV(3), i), j);
+      bgm_store<N>(F, S::cslot(3) + i, j);
+    }
+    for (int i = 0; i < 2 * S::V(2); ++i) {
+      bgm_row2_item<N>(F, t.data(), mt, i >> 1, i & 1);
+      if (S::TWO) bgm_col2_item<N>(F, t.data(), mt, i >> 1, i & 1);
+    }
+    if (N == 5)
+      for (int i = 0; i < S::CV(4); ++i) {
+        bgm_current<N, 4>(F, BgmRec<S::F4>(t.data() + S::T4, S::CV(4), i), j);
+        bgm_store<N>(F, S::cslot(4) + i, j);
+      }
+    for (int i = 0; i < S::NCAN * S::NGH; ++i) bgm_qj_item<N>(F, t.data(), i);
+    BgmEnds ends;
+    bgm_ends<N>(F, ends);
+    for (int i = 0; i < S::VP2; ++i) {
+      BgmPrefix<N, 2> p;
+      p.read(t.data(), i);
+      bgm_prefix_item<N, S::NROW, 2>(F, p, ends, jt, BghNoNote());
+    }
+    for (int i = S::VP2; i < S::VP; ++i) {
+      BgmPrefix<N, 1> p;
+      p.read(t.data(), i);
+      bgm_prefix_item<N, S::NROW, 1>(F, p, ends, jt, BghNoNote());
+    }
+    for (int r = 0; r < S::NROW; ++r)
+      for (int c = 0; c < 2 * S::NCOL; ++c)
+        jamps[(((size_t)e * S::NROW + r) * S::NCOL + c / 2) * 2 + c % 2] = jt[(size_t)c * S::NROW + r];
+  }
+}
+
+extern "C" int harness_bgm_words(int n) {
+  return n == 4 ? (int)me::BgmBuilder<4>().build().size() - me::BgmShape<4>::TWORDS
+                : (int)me::BgmBuilder<5>().build().size() - me::BgmShape<5>::TWORDS;
+}
+
+// orbits (norb x 2^nsym columns) and sectors of the colour form; returns norb
+extern "C" int harness_bgm_sectors(int n, const int* cf, int* orb, double* sec) {
+  const me::BgmSectors s = me::bgm_sectors(n, cf);
+  std::copy(s.orb.begin(), s.orb.end(), orb);
+  std::copy(s.sec.begin(), s.sec.end(), sec);
+  return s.norb;
+}
+
+// jamps [nevt][NROW][n!][2]; hel[NROW] = helicity index of each row
+extern "C" int harness_bgm_eval(int n, const double* mom, int nevt, double g, double mt, double* jamps, int* hel) {
+  for (int r = 0; r < (2 << n); ++r) hel[r] = n == 4 ? me::bgm_helicity<4>(r) : me::bgm_helicity<5>(r);
+  switch (n) {
+    case 4: bgm_eval<4>(mom, nevt, g, mt, jamps); return 0;
+    case 5: bgm_eval<5>(mom, nevt, g, mt, jamps); return 0;
+    default: return -1;
+  }
+}

@@ -1,0 +1,62 @@
+"""The two-sided recursion (launch variants 4 and 5 of the Berends-Giele executor) on the
+host: its dual amplitudes against the one-sided recycling kernel's, flow by flow; the
+mirror relation it rests on; its colour form in symmetry sectors; its operation count."""
+import math
+
+import numpy as np
+import pytest
+
+from cpu_harness import bgm_build
+from cpu_harness import build as harness
+from paper_2510_05392_amd import flops, rambo
+from paper_2510_05392_amd.gen.colour import colour_matrix
+
+AS = 0.118
+
+
+@pytest.mark.parametrize('n,nevt', [(4, 40), (5, 6)])
+def test_amplitudes_flow_by_flow(n, nevt):
+    """Every row's dual amplitudes equal the one-sided recursion's (each rounds a few
+    hundred operations: 1e-12 of the event's largest amplitude), and the mirrored
+    helicity has their complex conjugates up to one sign for all flows."""
+    assert bgm_build.table_words_off(n) == 0
+    mom = rambo.generate(n + 2, nevt, 8)
+    g = math.sqrt(4 * math.pi * AS)
+    two, hel = bgm_build.jamps(n, mom, g, 173.0)
+    assert sorted(list(hel) + [2 ** (n + 2) - 1 - h for h in hel]) == list(range(2 ** (n + 2)))
+    one = harness.build_bg().jamps_recycled(n, mom, g, 173.0, list(range(2 ** (n + 2)))).transpose(1, 0, 2)
+    scale = np.abs(one).max(axis=(1, 2), keepdims=True)
+    assert np.max(np.abs(two - one[:, hel]) / scale) < 1e-12
+    mirror = one[:, 2 ** (n + 2) - 1 - hel].conj()
+    plus, minus = (np.abs(mirror - s * one[:, hel]).max(axis=2) / scale[..., 0] for s in (1, -1))
+    assert np.max(np.minimum(plus, minus)) < 1e-12
+
+
+@pytest.mark.parametrize('n', [4, 5, 6])
+def test_colour_sectors(n):
+    """The sum over sectors is the quadratic form of the colour matrix (sums of n!^2
+    products in two orders: 1e-12 of the form for amplitudes of random sign), and every
+    element is exact in FP32."""
+    cf = np.array(colour_matrix(n)[0])
+    orb, sec = bgm_build.sectors(n, cf)
+    assert sorted(set(orb.reshape(-1).tolist())) == list(range(len(cf)))
+    assert np.array_equal(sec.astype(np.float32), sec)
+    a = np.random.default_rng(n).normal(size=(5, len(cf)))
+    g = orb.shape[1]
+    sign = np.array([[(-1) ** bin(s & b).count('1') for b in range(g)] for s in range(g)])
+    x = a[:, orb] @ sign.T                                    # [5][orbit][sector]
+    form = np.einsum('eos,sop,eps->e', x, sec, x)
+    assert np.max(np.abs(form / np.einsum('ex,xy,ey->e', a, cf, a) - 1)) < 1e-12
+
+
+@pytest.mark.parametrize('n', [4, 5])
+def test_flops_equal_the_counted_operations(n):
+    """flops.bgm_event equals the operations of the device functions for one event,
+    counted with the operation-counting scalar, phase by phase (a quark with pz < 0
+    takes one operation more in each of its two spinors)."""
+    mom = rambo.generate(n + 2, 3, 1003)
+    f = flops.bgm_event(n)
+    for m in mom:
+        setup, currents, spinors, qj, prefixes = bgm_build.count_event(n, m)
+        assert setup == f['setup'] + 2 * int((m[2:4, 3] < 0).sum())
+        assert (currents, spinors, qj, prefixes) == (f['currents'], f['spinors'], f['qj'], f['prefixes'])
