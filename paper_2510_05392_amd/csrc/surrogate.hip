@@ -357,6 +357,342 @@ __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu
     if (h == 0 && e0 + 32 * c < n) y[e0 + 32 * c] = o[c][0] + b0;
 }
 
+// ---- training in three launches (hidden widths 32 MB, MB <= 8) -------------------
+// The weights as the matrix cores take them: operand (mb, kk) of a layer = 64 lanes x 8
+// consecutive BF16, lane l = 32 h + r holding W[32 mb + f(r)][16 kk + 8 h + t], t < 8,
+// f(r) the row order of mlp_infer_kernel (an accumulator's consecutive elements are
+// consecutive outputs).  One operand is 1 KB of consecutive memory.
+__host__ __device__ inline int mlp_row(int r) { return 16 * (r >> 4) + 8 * ((r >> 2) & 1) + 4 * ((r >> 3) & 1) + (r & 3); }
+// position of element [o][k] of a matrix with kk operands per row block
+__host__ __device__ inline int64_t mlp_packed(int o, int k, int kks) {
+  const int q = o & 31;   // the lane row r with mlp_row(r) = q: the order is its own inverse
+  const int r = mlp_row(q);
+  return (((int64_t)(o >> 5) * kks + (k >> 4)) * 64 + 32 * ((k >> 3) & 1) + r) * 8 + (k & 7);
+}
+
+struct MlpTrain {
+  const __bf16* wf[17];   // packed weights of the forward products
+  const __bf16* wb[17];   // packed transposes, layers 1 .. L - 2
+  const __bf16* wlast;    // the output layer's row
+  const float* b[17];
+  float* z[17];           // [nb][outp]
+  __bf16* h[17];          // inputs of each layer [nb][kin]
+  __bf16* ht[17];         // the same, [kin][nbs]
+  __bf16* dzt[17];        // output gradients [out][nbs]
+  float* part;            // [workgroup][D W + 2]: column sums of dZ, then the squared error
+  int layers, nfeat, kin0, outl;   // outl: row length of the output layer's z
+};
+
+// Forward pass, loss and the backward pass through every dZ, 32 rows a workgroup.  Each
+// layer is the transposed product Z^T = W H^T (dH^T = W^T dZ^T) with the rows as the 32
+// columns; the four waves share its 32-row output blocks (wave w: blocks w and w + 4)
+// and exchange the activations (gradients) through LDS.  The weights of a block are
+// read straight into the operand registers, all of a layer in flight, the next layer's
+// behind this one's epilogue: with 32 rows a workgroup nothing is used twice, and 4096
+// rows are only 128 workgroups, so the bound is the latency of one layer after the
+// other, not traffic or matrix rate.  Every product sums its K steps in the order of
+// the layer-by-layer kernels: activations and gradients are the same bits.  A step
+// (this, the weight gradients, Adam) on 4096 rows of a 21-256x4-1 network takes 124 us
+// on an MI355X, layer by layer 1620.
+template <int MB>
+__global__ void __launch_bounds__(256) mlp_train_kernel(const __bf16* __restrict__ feat, const float* __restrict__ target,
+                                                        int64_t nb, int64_t nbs, MlpTrain net) {
+  constexpr int W = 32 * MB, KS = 2 * MB, NB = (MB + 3) / 4, AS = W + 8, FS = W + 4;
+  __shared__ __attribute__((aligned(16))) __bf16 act[2][32 * AS];
+  __shared__ __attribute__((aligned(16))) float dzs[32 * FS];
+  __shared__ float dlast[32];
+  const int t = threadIdx.x, w = t >> 6, l = t & 63, h = l >> 5, j = l & 31;
+  const int64_t e = (int64_t)blockIdx.x * 32 + j;
+  const bool on = e < nb;
+  const int ks0 = net.kin0 >> 4, D = net.layers - 1;
+  float* part = net.part + (int64_t)blockIdx.x * (D * W + 2);
+  bf16x8 zero8;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) zero8[q] = to_bf16(0.0f);
+  bf16x8 a[NB][KS];
+  // a layer's operands of this wave's blocks
+  auto weights = [&](const __bf16* __restrict__ p) {
+    const bf16x8* q = reinterpret_cast<const bf16x8*>(p) + l;
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+      if (w + 4 * n < MB) {
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) a[n][kk] = q[(int64_t)((w + 4 * n) * KS + kk) * 64];
+      }
+  };
+  f32x16 acc[NB];
+  auto clear = [&]() {
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[n][v] = 0.0f;
+  };
+  // products of the operands in a with the rows in an activation buffer
+  auto products = [&](const __bf16* buf) {
+    clear();
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      const bf16x8 b = *reinterpret_cast<const bf16x8*>(buf + j * AS + 16 * kk + 8 * h);
+#pragma unroll
+      for (int n = 0; n < NB; ++n)
+        if (w + 4 * n < MB) acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[n][kk], b, acc[n], 0, 0, 0);
+    }
+  };
+  // bias, pre-activations, SiLU and the activations of hidden layer ly to LDS and memory
+  auto activate = [&](int ly, __bf16* buf) {
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      if (w + 4 * n >= MB) continue;
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int o = 32 * (w + 4 * n) + 16 * p + 8 * h;
+        float z[8];
+        bf16x8 hv;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float4 b4 = *reinterpret_cast<const float4*>(net.b[ly] + o + 4 * q);
+          const float bo[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            z[4 * q + s] = acc[n][8 * p + 4 * q + s] + bo[s];
+            hv[4 * q + s] = to_bf16(silu(z[4 * q + s]));
+          }
+        }
+        if (on) {
+          float4* zp = reinterpret_cast<float4*>(net.z[ly] + e * W + o);
+          zp[0] = float4{z[0], z[1], z[2], z[3]};
+          zp[1] = float4{z[4], z[5], z[6], z[7]};
+          *reinterpret_cast<bf16x8*>(net.h[ly + 1] + e * W + o) = hv;
+        } else {
+          hv = zero8;
+        }
+        *reinterpret_cast<bf16x8*>(buf + j * AS + o) = hv;
+        __bf16* ht = net.ht[ly + 1] + (int64_t)o * nbs + e;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) ht[(int64_t)s * nbs] = hv[s];
+      }
+    }
+  };
+  // layer 0: the feature rows from memory; its operands are at most 16 K steps
+  {
+    clear();
+    const bf16x8* q0 = reinterpret_cast<const bf16x8*>(net.wf[0]) + l;
+    for (int kk = 0; kk < ks0; ++kk) {
+      const bf16x8 b = on ? *reinterpret_cast<const bf16x8*>(feat + e * net.kin0 + 16 * kk + 8 * h) : zero8;
+#pragma unroll
+      for (int n = 0; n < NB; ++n)
+        if (w + 4 * n < MB)
+          acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q0[(int64_t)((w + 4 * n) * ks0 + kk) * 64], b, acc[n], 0, 0, 0);
+      if ((kk & 3) == w) {
+        if (on) *reinterpret_cast<bf16x8*>(net.h[0] + e * net.kin0 + 16 * kk + 8 * h) = b;
+        __bf16* ht = net.ht[0] + (int64_t)(16 * kk + 8 * h) * nbs + e;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) ht[(int64_t)s * nbs] = b[s];
+      }
+    }
+    if (D > 1) weights(net.wf[1]);
+    activate(0, act[0]);
+  }
+  __syncthreads();
+  for (int ly = 1; ly < D; ++ly) {
+    products(act[(ly - 1) & 1]);
+    if (ly + 1 < D) weights(net.wf[ly + 1]);
+    else if (D > 1) weights(net.wb[D - 1]);
+    activate(ly, act[ly & 1]);
+    __syncthreads();
+  }
+  // output layer: one row of weights (the others of its block zero), loss and its gradient
+  if (w == 0) {
+    const __bf16* buf = act[(D - 1) & 1];
+    f32x16 o;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[v] = 0.0f;
+    for (int kk = 0; kk < KS; ++kk) {
+      const bf16x8 wv = *reinterpret_cast<const bf16x8*>(net.wlast + 16 * kk + 8 * h);
+      const bf16x8 b = *reinterpret_cast<const bf16x8*>(buf + j * AS + 16 * kk + 8 * h);
+      o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(j == 0 ? wv : zero8, b, o, 0, 0, 0);
+    }
+    float r = 0.0f;
+    if (h == 0 && on) {
+      const float y = o[0] + net.b[D][0];
+      net.z[D][e * net.outl] = y;
+      r = y - target[e];
+    }
+    float sq = r * r, dz = 2.0f * r / (float)nb;
+    if (h == 0) {
+      const __bf16 d16 = to_bf16(dz);
+      dlast[j] = (float)d16;
+      net.dzt[D][e] = d16;
+    }
+#pragma unroll
+    for (int d = 16; d > 0; d >>= 1) {
+      sq += __shfl_xor(sq, d);
+      dz += __shfl_xor(dz, d);
+    }
+    if (l == 0) {
+      part[D * W] = dz;
+      part[D * W + 1] = sq;
+    }
+  }
+  __syncthreads();
+  // dZ of hidden layer ly from dH: memory (transposed), LDS for the next product, and the
+  // column sums of this workgroup's rows
+  auto gradient = [&](int ly, auto dh, __bf16* buf) {
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      if (w + 4 * n >= MB) continue;
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int o = 32 * (w + 4 * n) + 16 * p + 8 * h;
+        float g[8];
+        bf16x8 gv;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) g[s] = 0.0f;
+        if (on) {
+          const float4* zp = reinterpret_cast<const float4*>(net.z[ly] + e * W + o);
+          const float4 z0 = zp[0], z1 = zp[1];
+          const float z[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
+#pragma unroll
+          for (int s = 0; s < 8; ++s) g[s] = dh(n, 8 * p + s, o + s) * dsilu(z[s]);
+        }
+#pragma unroll
+        for (int s = 0; s < 8; ++s) gv[s] = to_bf16(g[s]);
+        *reinterpret_cast<bf16x8*>(buf + j * AS + o) = gv;
+        float4* dp = reinterpret_cast<float4*>(dzs + j * FS + o);
+        dp[0] = float4{g[0], g[1], g[2], g[3]};
+        dp[1] = float4{g[4], g[5], g[6], g[7]};
+        __bf16* gt = net.dzt[ly] + (int64_t)o * nbs + e;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) gt[(int64_t)s * nbs] = gv[s];
+      }
+    }
+    __syncthreads();
+    if (t < W) {
+      float s = 0.0f;
+#pragma unroll 8
+      for (int r = 0; r < 32; ++r) s += dzs[r * FS + t];
+      part[ly * W + t] = s;
+    }
+  };
+  const float dl = dlast[j];
+  gradient(D - 1, [&](int, int, int i) { return dl * (float)net.wlast[i]; }, act[D & 1]);
+  for (int ly = D - 1; ly > 0; --ly) {
+    // act[(ly + 1) & 1] holds dZ of layer ly
+    products(act[(ly + 1) & 1]);
+    if (ly > 1) weights(net.wb[ly - 1]);
+    __syncthreads();   // the column sums have been read
+    gradient(ly - 1, [&](int n, int v, int) { return acc[n][v]; }, act[ly & 1]);
+  }
+}
+
+// Weight and bias gradients of every layer from the transposed activations and output
+// gradients: block = one 32 x 32 tile of a layer's dW = dZ^T H (both operands have the
+// rows of the batch consecutive), its four waves on interleaved K steps, their sums
+// added in order; the last blocks add the workgroups' column sums (one layer each) and
+// squared errors.
+struct MlpGrad {
+  const __bf16* dzt[17];
+  const __bf16* ht[17];
+  float* gw[17];
+  float* gb[17];
+  int out[17], in[17], tile0[18];
+  const float* part;
+  int layers, width, groups;   // workgroups of the pass before
+  float* loss;
+};
+__global__ void __launch_bounds__(256) mlp_wgrad_kernel(int64_t nbs, MlpGrad net) {
+  __shared__ float red[3][64][17];
+  const int t = threadIdx.x, w = t >> 6, l = t & 63;
+  const int L = net.layers, ntile = net.tile0[L], rec = (L - 1) * net.width + 2;
+  if ((int)blockIdx.x >= ntile) {
+    // column sums of layer ly = blockIdx.x - ntile (the output layer: one column, and
+    // the loss)
+    const int ly = (int)blockIdx.x - ntile, n = ly < L - 1 ? net.width : 2;
+    if (t < n) {
+      const float* p = net.part + ly * net.width + t;
+      float s = 0.0f;
+#pragma unroll 8
+      for (int g = 0; g < net.groups; ++g) s += p[(int64_t)g * rec];
+      if (ly < L - 1 || t == 0) net.gb[ly][t] = s;
+      else if (net.loss) *net.loss += s;
+    }
+    return;
+  }
+  int ly = 0;
+  while (ly + 1 < L && (int)blockIdx.x >= net.tile0[ly + 1]) ++ly;
+  const int out = net.out[ly], in = net.in[ly], tj = (in + 31) / 32;
+  const int tile = (int)blockIdx.x - net.tile0[ly], o0 = 32 * (tile / tj), i0 = 32 * (tile % tj);
+  const int oa = o0 + (l & 31), ib = i0 + (l & 31);
+  const __bf16* A = net.dzt[ly] + (int64_t)(oa < out ? oa : 0) * nbs + 8 * (l >> 5);
+  const __bf16* B = net.ht[ly] + (int64_t)(ib < in ? ib : 0) * nbs + 8 * (l >> 5);
+  bf16x8 zero8;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) zero8[q] = to_bf16(0.0f);
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+  constexpr int U = 8;   // K steps in flight
+  for (int64_t k0 = 16 * w; k0 < nbs; k0 += 64 * U) {
+    bf16x8 a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t k = k0 + 64 * u;
+      a[u] = k < nbs && oa < out ? *reinterpret_cast<const bf16x8*>(A + k) : zero8;
+      b[u] = k < nbs ? *reinterpret_cast<const bf16x8*>(B + k) : zero8;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u], b[u], acc, 0, 0, 0);
+  }
+  if (w > 0)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) red[w - 1][l][v] = acc[v];
+  __syncthreads();
+  if (w > 0 || ib >= in) return;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int o = o0 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
+    if (o < out) net.gw[ly][(int64_t)o * in + ib] = ((acc[v] + red[0][l][v]) + red[1][l][v]) + red[2][l][v];
+  }
+}
+
+// Every parameter of the network, flat (all W then b, layer by layer): Adam on the FP32
+// masters when step is set, then the BF16 copies (row-major padded, and packed).
+struct MlpCopies {
+  __bf16* w16[17];
+  __bf16* wf[17];   // null: no packed copy
+  __bf16* wb[17];
+  int64_t off[18];
+  int out[17], in[17], kin[17];
+  int layers;
+};
+__global__ void __launch_bounds__(256) params_kernel(float* __restrict__ w, const float* __restrict__ g,
+                                                     float* __restrict__ m, float* __restrict__ v, int64_t n, int step,
+                                                     float lr, float b1, float b2, float eps, float c1, float c2,
+                                                     MlpCopies net) {
+  const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (k >= n) return;
+  float x = w[k];
+  if (step) {
+    const float gk = g[k];
+    const float mk = b1 * m[k] + (1.0f - b1) * gk;
+    const float vk = b2 * v[k] + (1.0f - b2) * gk * gk;
+    m[k] = mk;
+    v[k] = vk;
+    x -= lr * (mk / c1) / (sqrtf(vk / c2) + eps);
+    w[k] = x;
+  }
+  int ly = 0;
+  while (ly + 1 < net.layers && k >= net.off[ly + 1]) ++ly;
+  const int in = net.in[ly];
+  const int64_t r = k - net.off[ly];
+  if (r >= (int64_t)net.out[ly] * in) return;   // a bias
+  const int o = (int)(r / in), i = (int)(r % in);
+  const __bf16 y = to_bf16(x);
+  net.w16[ly][(int64_t)o * net.kin[ly] + i] = y;
+  if (net.wf[ly]) net.wf[ly][mlp_packed(o, i, net.kin[ly] >> 4)] = y;
+  if (net.wb[ly]) net.wb[ly][mlp_packed(i, o, net.out[ly] >> 4)] = y;
+}
+
 hipError_t gemm(const __bf16* A, int64_t sai, int64_t sak, const __bf16* B, int64_t sbk,
                 int64_t sbj, int64_t M, int64_t N, int64_t K, const float* bias, float* cf,
                 int64_t ldc, __bf16* ch, int64_t ldh, bool act, hipStream_t s) {
@@ -435,7 +771,6 @@ __global__ void silu_back_kernel(const float* __restrict__ dh, const float* __re
   dzh[k] = to_bf16(g);
 }
 
-// db[j] = sum_b dZ[b][j], fixed order
 // db[j] = sum_b dz[b][j]: a workgroup of 64 x 16 threads per 64 columns; thread
 // (x, y) sums rows y, y + 16, ... of column x (coalesced across x), then the 16
 // partial sums of a column are added in a fixed order (deterministic).
@@ -462,29 +797,6 @@ __global__ void sum_kernel(const float* __restrict__ x, int n, float* __restrict
     for (int i = 0; i < n; ++i) s += x[i];
     out[0] += s;
   }
-}
-
-// Adam on the FP32 masters, then refresh the BF16 copies W16 [out][kin] and W16T [kin][outp]
-__global__ void adam_kernel(float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
-                            float* __restrict__ v, int64_t n, float lr, float b1, float b2, float eps,
-                            float c1, float c2) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  const float gk = g[k];
-  const float mk = b1 * m[k] + (1.0f - b1) * gk;
-  const float vk = b2 * v[k] + (1.0f - b2) * gk * gk;
-  m[k] = mk;
-  v[k] = vk;
-  w[k] -= lr * (mk / c1) / (sqrtf(vk / c2) + eps);
-}
-
-__global__ void cast_weights_kernel(const float* __restrict__ w, int out, int in, int kin, int outp,
-                                    __bf16* __restrict__ w16) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= (int64_t)outp * kin) return;
-  const int o = (int)(k / kin), i = (int)(k % kin);
-  const float x = (o < out && i < in) ? w[(int64_t)o * in + i] : 0.0f;
-  w16[(int64_t)o * kin + i] = to_bf16(x);
 }
 
 // Clears n bytes (a multiple of 4) with vector stores: used instead of a memset in
@@ -842,8 +1154,13 @@ int quantile(const double* v, int64_t n, double q, hipStream_t st, double* out) 
 struct me_sur_ctx {
   int nfeat, width, depth, kin0;       // kin0: padded input width
   std::vector<int> in, out, kin, outp; // per linear layer: sizes and padded sizes
-  std::vector<float*> w, b, gw, gb, mw, vw, mb, vb;
+  // FP32 masters, gradients and Adam moments, each flat: all W then b, layer by layer
+  float *params = nullptr, *grads = nullptr, *mom1 = nullptr, *mom2 = nullptr;
+  std::vector<int64_t> off;         // first parameter of each layer, and their number
+  std::vector<float*> w, b, gw, gb; // the layers' parts of params and grads
   std::vector<__bf16*> w16;         // BF16 weights [outp][kin], zero padded
+  // packed copies for the three-launch training step (null: widths it does not take)
+  std::vector<__bf16*> wf, wb;
   float* mean = nullptr;
   float* inv_std = nullptr;
   int step = 0;
@@ -851,10 +1168,16 @@ struct me_sur_ctx {
   int64_t cap = 0;
   std::vector<float*> z;               // pre-activations per layer [cap][outp]
   std::vector<__bf16*> h;              // inputs of each layer, h[0] = features [cap][kin0]
-  float* dzf = nullptr;                // [cap][maxw]
+  // layer-by-layer backward pass, for a batch capacity of its own
+  int64_t bcap = 0;
+  float* dzf = nullptr;                // [bcap][maxw]
   __bf16* dzh = nullptr;
   float* dh = nullptr;
   float* partial = nullptr;            // per-block loss partial sums
+  // three-launch training step: transposed activations and gradients, column sums
+  int64_t tcap = 0;
+  std::vector<__bf16*> ht, dzt;
+  float* tpart = nullptr;
 };
 
 namespace {
@@ -878,9 +1201,9 @@ void sfree(me_sur_ctx* c) {
   auto f = [](void* p) {
     if (p) (void)hipFree(p);
   };
-  for (auto v : {&c->w, &c->b, &c->gw, &c->gb, &c->mw, &c->vw, &c->mb, &c->vb, &c->z})
-    for (float* p : *v) f(p);
-  for (auto v : {&c->w16, &c->h})
+  for (float* p : {c->params, c->grads, c->mom1, c->mom2, c->tpart}) f(p);
+  for (float* p : c->z) f(p);
+  for (auto v : {&c->w16, &c->wf, &c->wb, &c->h, &c->ht, &c->dzt})
     for (__bf16* p : *v) f(p);
   f(c->mean);
   f(c->inv_std);
@@ -898,34 +1221,34 @@ uint64_t splitmix(uint64_t& x) {
   return z ^ (z >> 31);
 }
 
+// Whether the network runs in the whole-network kernels (hidden layers of 32 MB units).
+bool whole_net(const me_sur_ctx* c) { return c->width % 32 == 0 && c->width <= 256; }
+
+template <class T>
+void drop(std::vector<T*>& v, size_t n) {
+  for (T* p : v)
+    if (p) (void)hipFree(p);
+  v.assign(n, nullptr);
+}
+template <class T>
+void drop(T*& p) {
+  if (p) (void)hipFree(p);
+  p = nullptr;
+}
+
+// Activations of nb rows.
 int ensure_batch(me_sur_ctx* c, int64_t nb) {
   if (nb <= c->cap) return ME_OK;
-  for (float* p : c->z) if (p) (void)hipFree(p);
-  for (size_t i = 1; i < c->h.size(); ++i) if (c->h[i]) (void)hipFree(c->h[i]);
-  if (c->h[0]) (void)hipFree(c->h[0]);
-  if (c->dzf) (void)hipFree(c->dzf);
-  if (c->dzh) (void)hipFree(c->dzh);
-  if (c->dh) (void)hipFree(c->dh);
-  if (c->partial) (void)hipFree(c->partial);
   const int L = (int)c->in.size();
-  int maxw = c->kin0;
-  for (int l = 0; l < L; ++l) maxw = std::max(maxw, std::max(c->outp[l], c->kin[l]));
-  hipError_t e = hipSuccess;
-  c->h.assign(L + 1, nullptr);
-  c->z.assign(L, nullptr);
-  e = dalloc(&c->h[0], (size_t)nb * c->kin0);
+  c->cap = 0;
+  drop(c->z, L);
+  drop(c->h, L + 1);
+  hipError_t e = dalloc(&c->h[0], (size_t)nb * c->kin0);
   for (int l = 0; l < L && e == hipSuccess; ++l) {
     e = dalloc(&c->z[l], (size_t)nb * c->outp[l]);
     if (e == hipSuccess && l + 1 < L) e = dalloc(&c->h[l + 1], (size_t)nb * c->kin[l + 1]);
   }
-  if (e == hipSuccess) e = dalloc(&c->dzf, (size_t)nb * maxw);
-  if (e == hipSuccess) e = dalloc(&c->dzh, (size_t)nb * maxw);
-  if (e == hipSuccess) e = dalloc(&c->dh, (size_t)nb * maxw);
-  if (e == hipSuccess) e = dalloc(&c->partial, (size_t)(nb + 255) / 256 + 1);
-  if (e != hipSuccess) {
-    c->cap = 0;
-    return sfail(ME_ENOMEM, std::string("surrogate activations: ") + hipGetErrorString(e));
-  }
+  if (e != hipSuccess) return sfail(ME_ENOMEM, std::string("surrogate activations: ") + hipGetErrorString(e));
   // zero the padded columns once: GEMMs write only the valid ones
   for (int l = 0; l + 1 < L; ++l)
     (void)hipMemset(c->h[l + 1], 0, (size_t)nb * c->kin[l + 1] * sizeof(__bf16));
@@ -933,15 +1256,68 @@ int ensure_batch(me_sur_ctx* c, int64_t nb) {
   return ME_OK;
 }
 
-int refresh_bf16(me_sur_ctx* c, hipStream_t s) {
-  for (size_t l = 0; l < c->in.size(); ++l) {
-    const int64_t n = (int64_t)c->outp[l] * c->kin[l];
-    hipLaunchKernelGGL(cast_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, c->w[l],
-                       c->out[l], c->in[l], c->kin[l], c->outp[l], c->w16[l]);
-  }
-  hipError_t e = hipGetLastError();
-  return e == hipSuccess ? ME_OK : shipfail(e, "weight cast");
+// Buffers of the layer-by-layer backward pass.
+int ensure_backward(me_sur_ctx* c, int64_t nb) {
+  if (nb <= c->bcap) return ME_OK;
+  c->bcap = 0;
+  drop(c->dzf);
+  drop(c->dzh);
+  drop(c->dh);
+  drop(c->partial);
+  int maxw = c->kin0;
+  for (size_t l = 0; l < c->in.size(); ++l) maxw = std::max(maxw, std::max(c->outp[l], c->kin[l]));
+  hipError_t e = dalloc(&c->dzf, (size_t)nb * maxw);
+  if (e == hipSuccess) e = dalloc(&c->dzh, (size_t)nb * maxw);
+  if (e == hipSuccess) e = dalloc(&c->dh, (size_t)nb * maxw);
+  if (e == hipSuccess) e = dalloc(&c->partial, (size_t)(nb + 255) / 256 + 1);
+  if (e != hipSuccess) return sfail(ME_ENOMEM, std::string("surrogate gradients: ") + hipGetErrorString(e));
+  c->bcap = nb;
+  return ME_OK;
 }
+
+// Buffers of the three-launch training step: rows of nbs elements (nb up to whole
+// workgroups of 32 rows), so that 16-byte reads of 8 rows are aligned.
+int64_t train_stride(int64_t nb) { return (nb + 31) / 32 * 32; }
+int ensure_train(me_sur_ctx* c, int64_t nb) {
+  if (nb <= c->tcap) return ME_OK;
+  const int L = (int)c->in.size();
+  c->tcap = 0;
+  drop(c->ht, L);
+  drop(c->dzt, L);
+  drop(c->tpart);
+  const int64_t s = train_stride(nb);
+  hipError_t e = dalloc(&c->tpart, (size_t)(s / 32) * ((size_t)(L - 1) * c->width + 2));
+  for (int l = 0; l < L && e == hipSuccess; ++l) {
+    e = dalloc(&c->ht[l], (size_t)c->kin[l] * s);
+    if (e == hipSuccess) e = dalloc(&c->dzt[l], (size_t)c->out[l] * s);
+  }
+  if (e != hipSuccess) return sfail(ME_ENOMEM, std::string("surrogate training: ") + hipGetErrorString(e));
+  c->tcap = nb;
+  return ME_OK;
+}
+
+// One pass over the parameters: Adam when lr is given, and the BF16 copies.
+int update_params(me_sur_ctx* c, hipStream_t s, const float* lr) {
+  MlpCopies net{};
+  net.layers = (int)c->in.size();
+  for (int l = 0; l < net.layers; ++l) {
+    net.w16[l] = c->w16[l];
+    net.wf[l] = c->wf[l];
+    net.wb[l] = c->wb[l];
+    net.off[l] = c->off[l];
+    net.out[l] = c->out[l];
+    net.in[l] = c->in[l];
+    net.kin[l] = c->kin[l];
+  }
+  const int64_t n = c->off.back();
+  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+  const float c1 = 1.0f - std::pow(b1, (float)c->step), c2 = 1.0f - std::pow(b2, (float)c->step);
+  hipLaunchKernelGGL(params_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, c->params, c->grads, c->mom1,
+                     c->mom2, n, lr ? 1 : 0, lr ? *lr : 0.0f, b1, b2, eps, c1, c2, net);
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? ME_OK : shipfail(e, lr ? "adam" : "weight cast");
+}
+int refresh_bf16(me_sur_ctx* c, hipStream_t s) { return update_params(c, s, nullptr); }
 
 // forward pass over nb rows of h[0]; the output (normalised log ME) is column 0 of z[L-1];
 // the hidden layers' FP32 pre-activations z[l] are kept only for training (keep_z)
@@ -955,6 +1331,56 @@ int forward(me_sur_ctx* c, int64_t nb, hipStream_t s, bool keep_z = true) {
     if (e != hipSuccess) return shipfail(e, "forward gemm");
   }
   return ME_OK;
+}
+
+// Gradients of a batch in two launches (feat 16-byte aligned, activations ensured).
+int train_grads(me_sur_ctx* c, const uint16_t* feat, const float* target, int64_t nb, float* loss, hipStream_t st) {
+  int rc = ensure_train(c, nb);
+  if (rc) return rc;
+  const int L = (int)c->in.size(), mb = c->width / 32;
+  const int64_t nbs = train_stride(nb), groups = nbs / 32;
+  MlpTrain a{};
+  MlpGrad g{};
+  for (int l = 0; l < L; ++l) {
+    a.wf[l] = c->wf[l];
+    a.wb[l] = c->wb[l];
+    a.b[l] = c->b[l];
+    a.z[l] = c->z[l];
+    a.h[l] = c->h[l];
+    a.ht[l] = c->ht[l];
+    a.dzt[l] = c->dzt[l];
+    g.dzt[l] = c->dzt[l];
+    g.ht[l] = c->ht[l];
+    g.gw[l] = c->gw[l];
+    g.gb[l] = c->gb[l];
+    g.out[l] = c->out[l];
+    g.in[l] = c->in[l];
+    g.tile0[l + 1] = g.tile0[l] + (c->out[l] + 31) / 32 * ((c->in[l] + 31) / 32);
+  }
+  a.wlast = c->w16[L - 1];
+  a.part = c->tpart;
+  a.layers = L;
+  a.nfeat = c->nfeat;
+  a.kin0 = c->kin0;
+  a.outl = c->outp[L - 1];
+  g.part = c->tpart;
+  g.layers = L;
+  g.width = c->width;
+  g.groups = (int)groups;
+  g.loss = loss;
+  const void* fns[8] = {(const void*)mlp_train_kernel<1>, (const void*)mlp_train_kernel<2>,
+                        (const void*)mlp_train_kernel<3>, (const void*)mlp_train_kernel<4>,
+                        (const void*)mlp_train_kernel<5>, (const void*)mlp_train_kernel<6>,
+                        (const void*)mlp_train_kernel<7>, (const void*)mlp_train_kernel<8>};
+  const __bf16* f = reinterpret_cast<const __bf16*>(feat);
+  int64_t n = nb, stride = nbs;
+  void* args[] = {&f, &target, &n, &stride, &a};
+  hipError_t e = hipLaunchKernel(fns[mb - 1], dim3((unsigned)groups), dim3(256), args, 0, st);
+  if (e == hipSuccess) e = hipGetLastError();
+  if (e != hipSuccess) return shipfail(e, "training pass");
+  hipLaunchKernelGGL(mlp_wgrad_kernel, dim3((unsigned)(g.tile0[L] + L)), dim3(256), 0, st, nbs, g);
+  e = hipGetLastError();
+  return e == hipSuccess ? ME_OK : shipfail(e, "weight gradients");
 }
 
 }  // namespace
@@ -983,45 +1409,43 @@ int me_sur_init(const me_sur_params* p, me_surrogate* out) {
     c->kin.push_back(pad16(in));
     c->outp.push_back(pad32(o));
   }
-  hipError_t e = hipSuccess;
+  c->off.push_back(0);
+  for (int l = 0; l < L; ++l) c->off.push_back(c->off[l] + (int64_t)c->out[l] * c->in[l] + c->out[l]);
+  const size_t np = (size_t)c->off.back();
+  hipError_t e = dalloc(&c->params, np);
+  if (e == hipSuccess) e = dalloc(&c->grads, np);
+  if (e == hipSuccess) e = dalloc(&c->mom1, np);
+  if (e == hipSuccess) e = dalloc(&c->mom2, np);
+  // Kaiming-uniform style initialisation, bound sqrt(6 / fan_in) / 2 for SiLU
+  std::vector<float> hp(np, 0.0f);
   uint64_t st = p->seed;
   for (int l = 0; l < L && e == hipSuccess; ++l) {
     const size_t nw = (size_t)c->out[l] * c->in[l];
-    // Kaiming-uniform style initialisation, bound sqrt(6 / fan_in) / 2 for SiLU
-    std::vector<float> hw(nw), hb(c->out[l], 0.0f);
     const double bound = std::sqrt(3.0 / c->in[l]);
     for (size_t k = 0; k < nw; ++k) {
       const double u = (splitmix(st) >> 11) * (1.0 / 9007199254740992.0);
-      hw[k] = (float)((2.0 * u - 1.0) * bound);
+      hp[c->off[l] + k] = (float)((2.0 * u - 1.0) * bound);
     }
-    float *w, *b, *gw, *gb, *mw, *vw, *mb, *vb;
-    __bf16* w16;
-    e = dalloc(&w, nw);
-    if (e == hipSuccess) e = dalloc(&b, c->out[l]);
-    if (e == hipSuccess) e = dalloc(&gw, nw);
-    if (e == hipSuccess) e = dalloc(&gb, c->out[l]);
-    if (e == hipSuccess) e = dalloc(&mw, nw);
-    if (e == hipSuccess) e = dalloc(&vw, nw);
-    if (e == hipSuccess) e = dalloc(&mb, c->out[l]);
-    if (e == hipSuccess) e = dalloc(&vb, c->out[l]);
-    if (e == hipSuccess) e = dalloc(&w16, (size_t)c->outp[l] * c->kin[l]);
-    if (e != hipSuccess) break;
-    c->w.push_back(w);
-    c->b.push_back(b);
-    c->gw.push_back(gw);
-    c->gb.push_back(gb);
-    c->mw.push_back(mw);
-    c->vw.push_back(vw);
-    c->mb.push_back(mb);
-    c->vb.push_back(vb);
-    c->w16.push_back(w16);
-    e = hipMemcpy(w, hw.data(), nw * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(b, hb.data(), hb.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(mw, 0, nw * 4);
-    if (e == hipSuccess) e = hipMemset(vw, 0, nw * 4);
-    if (e == hipSuccess) e = hipMemset(mb, 0, c->out[l] * 4);
-    if (e == hipSuccess) e = hipMemset(vb, 0, c->out[l] * 4);
+    c->w.push_back(c->params + c->off[l]);
+    c->b.push_back(c->w[l] + nw);
+    c->gw.push_back(c->grads + c->off[l]);
+    c->gb.push_back(c->gw[l] + nw);
+    // BF16 copies: what is padding stays zero
+    c->w16.push_back(nullptr);
+    c->wf.push_back(nullptr);
+    c->wb.push_back(nullptr);
+    const size_t n16 = (size_t)c->outp[l] * c->kin[l];
+    e = dalloc(&c->w16[l], n16);
+    if (e == hipSuccess) e = hipMemset(c->w16[l], 0, n16 * sizeof(__bf16));
+    if (whole_net(c) && l + 1 < L) {
+      if (e == hipSuccess) e = dalloc(&c->wf[l], n16);
+      if (e == hipSuccess) e = hipMemset(c->wf[l], 0, n16 * sizeof(__bf16));
+      if (e == hipSuccess && l > 0) e = dalloc(&c->wb[l], n16);
+    }
   }
+  if (e == hipSuccess) e = hipMemcpy(c->params, hp.data(), np * 4, hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemset(c->mom1, 0, np * 4);
+  if (e == hipSuccess) e = hipMemset(c->mom2, 0, np * 4);
   if (e == hipSuccess) e = dalloc(&c->mean, c->nfeat);
   if (e == hipSuccess) e = dalloc(&c->inv_std, c->nfeat);
   if (e == hipSuccess) {
@@ -1063,32 +1487,18 @@ int me_sur_num_params(me_surrogate s, int64_t* n) {
   int rc = scheck(s);
   if (rc) return rc;
   if (!n) return sfail(ME_EINVAL, "null argument");
-  int64_t t = 0;
-  for (size_t l = 0; l < s->in.size(); ++l) t += (int64_t)s->out[l] * s->in[l] + s->out[l];
-  *n = t;
+  *n = s->off.back();
   return ME_OK;
 }
 
 static int copy_params(me_surrogate s, float* host, int64_t cap, bool to_host, bool grads) {
   int rc = scheck(s);
   if (rc) return rc;
-  int64_t n = 0;
-  me_sur_num_params(s, &n);
+  const int64_t n = s->off.back();
   if (!host || cap < n) return sfail(ME_EINVAL, "parameter buffer too small");
-  int64_t off = 0;
-  for (size_t l = 0; l < s->in.size(); ++l) {
-    const size_t nw = (size_t)s->out[l] * s->in[l];
-    float* dw = grads ? s->gw[l] : s->w[l];
-    float* db = grads ? s->gb[l] : s->b[l];
-    hipError_t e = to_host ? hipMemcpy(host + off, dw, nw * 4, hipMemcpyDeviceToHost)
-                           : hipMemcpy(dw, host + off, nw * 4, hipMemcpyHostToDevice);
-    off += nw;
-    if (e == hipSuccess)
-      e = to_host ? hipMemcpy(host + off, db, s->out[l] * 4, hipMemcpyDeviceToHost)
-                  : hipMemcpy(db, host + off, s->out[l] * 4, hipMemcpyHostToDevice);
-    off += s->out[l];
-    if (e != hipSuccess) return shipfail(e, "parameter copy");
-  }
+  hipError_t e = to_host ? hipMemcpy(host, grads ? s->grads : s->params, n * 4, hipMemcpyDeviceToHost)
+                         : hipMemcpy(s->params, host, n * 4, hipMemcpyHostToDevice);
+  if (e != hipSuccess) return shipfail(e, "parameter copy");
   if (!to_host) return refresh_bf16(s, nullptr);
   return ME_OK;
 }
@@ -1190,6 +1600,11 @@ int me_sur_grads(me_surrogate s, const uint16_t* feat, const float* target, int6
   rc = ensure_batch(s, nb);
   if (rc) return rc;
   const int L = (int)s->in.size();
+  // the whole-network kernels read the feature rows 16 bytes at a time
+  if (whole_net(s) && ((uintptr_t)feat & 15) == 0 && (nb + 31) / 32 < (1ll << 31))
+    return train_grads(s, feat, target, nb, loss, st);
+  rc = ensure_backward(s, nb);
+  if (rc) return rc;
   hipError_t e = hipMemcpyAsync(s->h[0], feat, (size_t)nb * s->kin0 * 2, hipMemcpyDeviceToDevice, st);
   if (e != hipSuccess) return shipfail(e, "feature copy");
   rc = forward(s, nb, st);
@@ -1232,18 +1647,7 @@ int me_sur_adam(me_surrogate s, float lr, void* stream) {
   if (rc) return rc;
   hipStream_t st = (hipStream_t)stream;
   s->step += 1;
-  const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  const float c1 = 1.0f - std::pow(b1, (float)s->step), c2 = 1.0f - std::pow(b2, (float)s->step);
-  for (size_t l = 0; l < s->in.size(); ++l) {
-    const int64_t nw = (int64_t)s->out[l] * s->in[l];
-    hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, st, s->w[l], s->gw[l],
-                       s->mw[l], s->vw[l], nw, lr, b1, b2, eps, c1, c2);
-    hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((s->out[l] + 255) / 256)), dim3(256), 0, st, s->b[l],
-                       s->gb[l], s->mb[l], s->vb[l], (int64_t)s->out[l], lr, b1, b2, eps, c1, c2);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return shipfail(e, "adam");
-  return refresh_bf16(s, st);
+  return update_params(s, st, &lr);
 }
 
 int me_sur_train_step(me_surrogate s, const uint16_t* feat, const float* target, int64_t nb, float lr,

@@ -1,0 +1,61 @@
+"""The training step's whole-network kernels against the layer-by-layer ones, which the
+same call runs when the feature rows are not 16-byte aligned: batches around a
+workgroup's 32 rows, the smallest and the largest hidden widths, one and several layers."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip('torch')
+pytestmark = pytest.mark.gpu
+
+
+def _say(msg):
+    print(msg, flush=True)
+
+
+@pytest.fixture(scope='module')
+def binding():
+    if not torch.cuda.is_available():
+        pytest.fail('GPU tests need a GPU')
+    from paper_2510_05392_amd import binding as b
+    b.load()
+    return b
+
+
+@pytest.mark.parametrize('width,depth,nfeat', [(32, 1, 15), (64, 3, 21), (96, 2, 10), (160, 1, 28), (256, 4, 15)])
+@pytest.mark.parametrize('nb', [1, 31, 32, 33, 100, 1000])
+def test_whole_network_step_against_layers(binding, width, depth, nfeat, nb):
+    """Both take every product's K steps in the same order, so pre-activations and
+    activations are the same bits; the gradients' sums over the rows differ in order
+    (FP32: nb 2^-24 of the sum of the terms' magnitudes, bounded by sqrt(nb) times the
+    layer's largest entry), and the loss likewise."""
+    _say(f'case training step {nfeat}-{width}x{depth} nb={nb}')
+    rng = np.random.default_rng(nb)
+    kpad = binding.Surrogate(nfeat, width, depth, seed=3).kpad
+    x = np.zeros((nb, kpad), np.float32)
+    x[:, :nfeat] = rng.normal(size=(nb, nfeat))
+    rows = torch.from_numpy(x).bfloat16().view(torch.int16).reshape(-1)
+    target = torch.from_numpy(rng.normal(size=nb).astype(np.float32)).cuda()
+    got = []
+    for shift in (0, 1):
+        store = torch.zeros(nb * kpad + 8, dtype=torch.int16, device='cuda')
+        feat = store[shift:shift + nb * kpad]
+        feat.copy_(rows)
+        sur = binding.Surrogate(nfeat, width, depth, seed=3)
+        loss = torch.zeros(1, dtype=torch.float32, device='cuda')
+        sur.me_sur_grads(feat, target, nb, loss)
+        torch.cuda.synchronize()
+        acts = [sur.me_sur_activations(k, kind, nb) for k in range(depth + 1) for kind in (0, 1)]
+        g1 = sur.me_sur_get_grads()
+        for _ in range(3):
+            sur.me_sur_train_step(feat, target, nb, 1e-3, loss)
+        torch.cuda.synchronize()
+        got.append((acts, g1, float(loss.item()), sur.me_sur_get_params()))
+    (fa, fg, fl, fp), (la, lg, ll, lp) = got
+    assert all(np.array_equal(a, b) for a, b in zip(fa, la))
+    tol = max(nb, 16) * 2.0 ** -24
+    assert np.linalg.norm(fg - lg) <= tol * np.linalg.norm(lg) * 4
+    assert abs(fl - ll) <= 1e-4 * abs(ll)
+    # three Adam steps move a parameter by at most 3 lr each; where a gradient is no more
+    # than its rounding the step's direction is not determined
+    assert np.abs(fp - lp).max() <= 6.1e-3
+    assert np.linalg.norm(fp - lp) <= 2e-2 * np.linalg.norm(lp)
