@@ -339,6 +339,8 @@ def main():
     executor = (tuned or {}).get('executor', 0)
     bg_variant = (tuned or {}).get('bg_variant', 0)
     bgk = {0: 'bg_kernel', 1: 'bg_kernel', 2: 'bg_kernel', 3: 'bgh_kernel'}.get(bg_variant, 'bgm_fused_kernel')
+    if process == 'gg_ttxgggg':   # six gluons: one FP64 kernel whatever the launch shape
+        bgk = 'bgm_fused_kernel'
     kname = {1: f'team_kernel<{process}_team>', 2: f'sums_kernel<{process}>',
              3: f'{bgk}<{NPAR[process] - 2}>'}.get(executor, f'me_kernel<{process}>')
     ncol = {'gg_ttx': 2, 'gg_ttxg': 6, 'gg_ttxgg': 24, 'gg_ttxggg': 120, 'gg_ttxgggg': 720}[process]

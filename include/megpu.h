@@ -326,7 +326,9 @@ int me_set_split(me_handle h, int wpe, int fchunk, int rounds, int colour_grid);
 
 /* Kernel of the Berends-Giele executor (paper, Discussion: the recursion for many
  * gluons): 0 = one (event, helicity) row per item with the default rows and
- * threads per workgroup, 1 = half of both, 2 = twice both; 3 = helicity
+ * threads per workgroup, 1 = half of both, 2 = twice both (six gluons in FP64: the
+ * kernel of 4 whichever is set, launches of no more events than the batch has); 3 =
+ * helicity
  * recycling (four and five gluons: one workgroup per event(s), every current and
  * row spinor formed once per helicity assignment of its own particles, the full
  * orderings walked in rotation cycles); 4 = the recursion from both ends of the

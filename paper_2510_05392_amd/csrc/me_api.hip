@@ -189,9 +189,9 @@ struct me_ctx {
   uint16_t* d_bg_cyc = nullptr;      // rotation-cycle tables of the helicity-recycling kernel
   int n_bg_cyc = 0;                  // [seg | cbase | rbase] sizes
   int n_bg_slot = 0;
-  uint32_t* d_bgm = nullptr;         // work-item tables of the two-sided recursion
-  uint16_t* d_bgm_orb = nullptr;     // orbits and sectors of its FP64 colour form
-  float* d_bgm_sec = nullptr;
+  uint32_t* d_bgm = nullptr;         // work-item tables of the two-sided recursion, and in
+  float* d_bgm_sec = nullptr;        // the same allocation the sectors and orbits of its
+  uint16_t* d_bgm_orb = nullptr;     // FP64 colour form
   me_params params{};
   std::vector<int> good;      // host copy of the good helicities
   int* d_hels = nullptr;      // device, good helicities (capacity nhel)
@@ -335,11 +335,22 @@ int enqueue_soa(me_ctx* c, const double* momenta, int64_t nevt, hipStream_t s) {
   return ME_OK;
 }
 
-// A new device array with the contents of v.
-template <class T>
-hipError_t upload(T** p, const std::vector<T>& v) {
-  hipError_t e = hipMalloc(p, v.size() * sizeof(T));
-  if (e == hipSuccess) e = hipMemcpy(*p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice);
+// Tables of the two-sided recursion of n gluons: one allocation, one copy.  Those that
+// do not depend on the handle are built once.
+hipError_t upload_bgm(me_ctx* c) {
+  const std::vector<uint32_t>& items = c->bg->n == 4 ? me::bgm_items<4>()
+                                       : c->bg->n == 5 ? me::bgm_items<5>()
+                                                       : me::bgm_items<6>();
+  const me::BgmSectors sc = me::bgm_sectors(c->bg->n, c->desc->cf_int);
+  const std::vector<float> sec = me::bgm_sector_operands(sc);
+  std::vector<uint32_t> all(items.size() + sec.size() + (sc.orb.size() + 1) / 2);
+  std::memcpy(all.data(), items.data(), items.size() * 4);
+  std::memcpy(all.data() + items.size(), sec.data(), sec.size() * 4);
+  std::memcpy(all.data() + items.size() + sec.size(), sc.orb.data(), sc.orb.size() * 2);
+  hipError_t e = hipMalloc(&c->d_bgm, all.size() * 4);
+  if (e == hipSuccess) e = hipMemcpy(c->d_bgm, all.data(), all.size() * 4, hipMemcpyHostToDevice);
+  c->d_bgm_sec = reinterpret_cast<float*>(c->d_bgm + items.size());
+  c->d_bgm_orb = reinterpret_cast<uint16_t*>(c->d_bgm + items.size() + sec.size());
   return e;
 }
 
@@ -362,23 +373,15 @@ int ensure_bg_tables(me_ctx* c) {
     c->n_bg_slot = (int)cy.cbase.size();
     e = hipMalloc(&c->d_bg_cyc, all.size() * sizeof(uint16_t));
     if (e == hipSuccess) e = hipMemcpy(c->d_bg_cyc, all.data(), all.size() * sizeof(uint16_t), hipMemcpyHostToDevice);
-    const std::vector<uint32_t> m = c->bg->n == 4 ? me::BgmBuilder<4>().build() : me::BgmBuilder<5>().build();
-    if (e == hipSuccess) e = upload(&c->d_bgm, m);
-    const me::BgmSectors sc = me::bgm_sectors(c->bg->n, c->desc->cf_int);
-    if (e == hipSuccess) e = upload(&c->d_bgm_orb, sc.orb);
-    if (e == hipSuccess) e = upload(&c->d_bgm_sec, me::bgm_sector_operands(sc));
   }
+  if (e == hipSuccess && c->bg->fused_slot_doubles() > 0) e = upload_bgm(c);
   if (e != hipSuccess) {
     if (c->d_bg_sub) (void)hipFree(c->d_bg_sub);
     if (c->d_bg_mask) (void)hipFree(c->d_bg_mask);
     if (c->d_bg_last) (void)hipFree(c->d_bg_last);
     if (c->d_bg_cyc) (void)hipFree(c->d_bg_cyc);
     if (c->d_bgm) (void)hipFree(c->d_bgm);
-    if (c->d_bgm_orb) (void)hipFree(c->d_bgm_orb);
-    if (c->d_bgm_sec) (void)hipFree(c->d_bgm_sec);
     c->d_bgm = nullptr;
-    c->d_bgm_orb = nullptr;
-    c->d_bgm_sec = nullptr;
     c->d_bg_sub = nullptr;
     c->d_bg_mask = c->d_bg_last = nullptr;
     c->d_bg_cyc = nullptr;
@@ -389,12 +392,13 @@ int ensure_bg_tables(me_ctx* c) {
 
 // Events per chunk of the Berends-Giele executor: the dual amplitudes of a chunk
 // (2 NCOL doubles per row, nhel rows per event) fill at most ME_SPLIT_SCRATCH_BYTES.
-// The Berends-Giele executor runs the two-sided recursion with the colour form (FP64,
-// or split FP16 / BF16 on the matrix cores) and the helicity sum fused (launch
-// variants 4 and 5).
+// The Berends-Giele executor runs the two-sided recursion with the colour form and the
+// helicity sum fused: four and five gluons in launch variants 4 and 5 (FP64, or split
+// FP16 / BF16 on the matrix cores); six gluons in FP64 whatever the launch shape (4096
+// events 12.6 ms, 284 ms with the fastest shape of the one-row kernel).
 bool bg_fused(const me_ctx* h) {
-  return h->executor == ME_EXEC_BG && (h->bg_variant == 4 || h->bg_variant == 5) && h->bg->recycle &&
-         h->bg->fused_slot_doubles;
+  if (h->executor != ME_EXEC_BG || h->bg->fused_slot_doubles() == 0) return false;
+  return h->bg->recycle ? h->bg_variant >= 4 : h->params.colorsum_mode == ME_CS_FP64;
 }
 
 // Event blocks per launch of the fused kernel: variant 5 = one persistent launch over
@@ -759,8 +763,6 @@ int me_finalize(me_handle h) {
   if (h->d_bg_last) (void)hipFree(h->d_bg_last);
   if (h->d_bg_cyc) (void)hipFree(h->d_bg_cyc);
   if (h->d_bgm) (void)hipFree(h->d_bgm);
-  if (h->d_bgm_orb) (void)hipFree(h->d_bgm_orb);
-  if (h->d_bgm_sec) (void)hipFree(h->d_bgm_sec);
   if (h->graph) (void)hipGraphExecDestroy(h->graph);
   if (h->capture_stream) (void)hipStreamDestroy(h->capture_stream);
   free_tables(h);
@@ -913,6 +915,8 @@ int prepare(me_ctx* h, int64_t nevt) {
       if (per_cu < 1) return fail(ME_EHIP, "fused Berends-Giele kernel: no resident workgroup fits");
       h->bg_resident = per_cu * std::max(1, h->simds / 4);
       h->bg_grid = (int)bg_fused_blocks(h);
+      // a slot of six gluons is 1.9 MB: no more of them than events
+      if (!h->bg->recycle) h->bg_grid = (int)std::min<int64_t>(h->bg_grid, std::max<int64_t>(nevt, 1));
       return ensure_sums(h, (size_t)h->bg_grid * (size_t)h->bg->fused_slot_doubles());
     }
     // dual amplitudes of an event chunk [2 NCOL][rows] in the split scratch, then

@@ -1,5 +1,5 @@
 // Two-sided colour-ordered recursion with helicity recycling: the dual amplitudes of
-// one event, four or five gluons, by one workgroup (launch variants 4 and 5).  The
+// one event, four to six gluons, by one workgroup (launch variants 4 and 5).  The
 // recursion, vertices and conventions are those of me_bg.h and me_bgh.h; what is
 // different is how much of it is formed, and where.
 //
@@ -12,29 +12,30 @@
 //    J(alpha, x, beta) = (-1)^|alpha| sum J(x, rho) over the shuffles rho of reversed
 //    alpha with beta (Kleiss-Kuijf for currents).  Currents of length 4 and more are
 //    formed only for the (L-1)! orderings with their lowest gluon first and expanded
-//    where they are used (1 .. 3 terms for length 4).
-//  * The quark line is cut at the block that holds position M = 2:
-//      A(sigma) = Q.J(sigma) + i g sum_{i <= 2 < j, (i,j) != (0,N)}
+//    where they are used (1 .. 3 terms for length 4, up to 6 for length 5).
+//  * The quark line is cut at the block that holds position M = 2 (six gluons: 3):
+//      A(sigma) = Q.J(sigma) + i g sum_{i <= M < j, (i,j) != (0,N)}
 //                 R(sigma[:i]) gamma.J(sigma[i:j]) C(sigma[j:]),
 //    R(p) the row spinor of the top end (me_bg.h), C(s) the column spinor of the
 //    antitop end, C(()) = v, C(s) = S(p3 - P(rest)) sum_j i g gamma.J(s[:j]) C(s[j:]).
-//    Only R and C of at most two gluons exist; the sums over i belong to prefixes of
+//    Only R and C of at most two gluons are stored; the sums over i belong to prefixes of
 //    sigma, so a work item = (prefix of length N-1, its helicities) forms
 //    X_j = sum_i R gamma.J(sigma[i:j]) for j < N once for both helicities of the last
 //    gluon.
 //  * Q.J(sigma) needs the currents of length N only contracted: they are formed for
 //    the orderings that start with gluon 0, and their contractions with the four
-//    Q = i g ubar gamma v expanded (1 .. 6 terms).
+//    Q = i g ubar gamma v expanded (1 .. 10 terms).
 //
 // FP64 operations per event with all helicities (flops.bgm_event; counted by running
 // this code on a counting double): 3.47e6 for g g -> t t~ g g g against 19.1e6 of the
-// one-sided kernel of me_bgh.h, 0.27e6 against 1.24e6 for g g -> t t~ g g.  Bound by the
-// issue of FP64 vector instructions: 42e3 a wave and event on each of a compute unit's
-// SIMDs, 18 ms of the 28.5 for 262144 five-gluon events; the rest is latency of LDS and
-// of the work-item records between barriers.  On an MI355X, FP64 colour, against the
-// one-sided kernel: 262144 g g -> t t~ g g g 28.5 ms (149.7), 524288 g g -> t t~ g g
-// 5.7 ms (18.8); split FP16 colour, 100003 g g -> t t~ g g g 11.6 ms (51.1); 1000
-// events 0.12 ms (0.63).
+// one-sided kernel of me_bgh.h, 0.27e6 against 1.24e6 for g g -> t t~ g g, 59.5e6 for
+// g g -> t t~ g g g g.  Bound by the issue of FP64 vector instructions: 42e3 a wave and
+// event on each of a compute unit's SIMDs, 18 ms of the 28.5 for 262144 five-gluon
+// events; the rest is latency of LDS and of the work-item records between barriers.  On
+// an MI355X, FP64 colour, against the one-sided kernel: 262144 g g -> t t~ g g g 28.5 ms
+// (149.7), 524288 g g -> t t~ g g 5.7 ms (18.8), 1000 g g -> t t~ g g g 0.12 ms (0.63);
+// split FP16 colour, 100003 g g -> t t~ g g g 11.6 ms (51.1); six gluons against the
+// one-row kernel of me_bg.h, 4096 events 12.6 ms (284).
 //
 // Frame of an event in LDS: slots of four complex numbers, component-major (component
 // c of slot s is the 16-byte element c NS + s), so that the 16-byte reads of lanes on
@@ -124,8 +125,8 @@ __device__ __forceinline__ void bgm_mom(const double* F, int mask, double* p) {
   for (int u = 0; u < 4; ++u) p[u] = F[BgmShape<N>::PSOFF + 4 * mask + u];
 }
 
-// Sum of cnt stored currents with a common sign (an expansion of me_bgm_tables.h):
-// off(t) the address of term t, info = cnt, bit 15 = negative.
+// Sum of stored currents with a common sign (an expansion of me_bgm_tables.h): off(t) the
+// address of term t, info = their number (1 or 3 for length 4), bit 15 = negative.
 template <int N, typename Off>
 __device__ __forceinline__ void bgm_expand(const double* F, int info, Off off, cx* v) {
   const int cnt = info & 0x7fff;
@@ -133,10 +134,35 @@ __device__ __forceinline__ void bgm_expand(const double* F, int info, Off off, c
   if (cnt > 1) {
     cx a[4], b[4];
     bgm_load<N>(F, off(1), a);
-    bgm_load<N>(F, off(2), b);   // expansions of length 4 have 1 or 3 terms
+    bgm_load<N>(F, off(2), b);
 #pragma unroll
     for (int c = 0; c < 4; ++c) v[c] = (v[c] + a[c]) + b[c];
   }
+  const double s = (info & 0x8000) ? -1.0 : 1.0;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) v[c] = s * v[c];
+}
+
+// The same for currents of length 5, which six gluons keep in memory (1, 4 or 6 terms).
+__device__ __forceinline__ void bgm_load5(const cx16* j5, int k, cx* v) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const cx16 x = j5[c * BgmShape<6>::CV(5) + k];
+    v[c] = cx{x.r, x.i};
+  }
+}
+template <typename Var>
+__device__ __forceinline__ void bgm_expand5(const cx16* j5, int info, Var var, cx* v) {
+  const int cnt = info & 0x7fff;
+  bgm_load5(j5, var(0), v);
+#pragma unroll
+  for (int t = 1; t < 6; ++t)
+    if (t < cnt) {
+      cx a[4];
+      bgm_load5(j5, var(t), a);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[c] = v[c] + a[c];
+    }
   const double s = (info & 0x8000) ? -1.0 : 1.0;
 #pragma unroll
   for (int c = 0; c < 4; ++c) v[c] = s * v[c];
@@ -283,9 +309,9 @@ __device__ __forceinline__ constexpr int bgm_field(int start, int len) {
   return f + start;
 }
 
-// Current of length L = 2 .. 5 over the subset pm[L] (pm[j]: its first j gluons).
-// head(j) = address of the sub-current of the first j gluons, mid(j, l) of gluons
-// j .. l - 1, tail(v) reads that of the last L - 1.  The tails that several splits share
+// Current of length L = 2 .. 6 over the subset pm[L] (pm[j]: its first j gluons):
+// head(j, v) reads the sub-current of the first j gluons, mid(j, l, v) that of gluons
+// j .. l - 1, tail(v) that of the last L - 1.  The tails that several splits share
 // stay in registers, and each vector is asked for one vertex ahead of its use (two
 // waves per SIMD do not hide the latency of LDS behind each other).
 template <int N, int L, typename Head, typename Mid, typename Tail>
@@ -295,23 +321,23 @@ __device__ __forceinline__ void bgm_splits(const double* F, const int* pm, Head 
   double P[4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) a3[c] = a4[c] = cx{0.0, 0.0};
-  bgm_load<N>(F, head(1), A);
+  head(1, A);
   tail(B);
   bgm_mom<N>(F, pm[L], P);
 #pragma unroll
-  for (int l = 2; l < L; ++l) bgm_load<N>(F, mid(l, L), T[l]);
+  for (int l = 2; l < L; ++l) mid(l, L, T[l]);
 #pragma unroll
   for (int j = 1; j < L; ++j) {
     cx M[4], X[4];
     double pa[4];
     bgm_mom<N>(F, pm[j], pa);
-    if (j + 1 < L) bgm_load<N>(F, mid(j, j + 1), M);
+    if (j + 1 < L) mid(j, j + 1, M);
     bgm_v3(A, pa, j == 1 ? B : T[j], P, a3);
     bgm_pin(a3);
 #pragma unroll
     for (int l = j + 1; l < L; ++l) {
-      if (l + 1 < L) bgm_load<N>(F, mid(j, l + 1), X);
-      else bgm_load<N>(F, head(j + 1), X);
+      if (l + 1 < L) mid(j, l + 1, X);
+      else head(j + 1, X);
       bg_v4(A, M, T[l], a4);
       bgm_pin(a4);
       bgh_copy(X, l + 1 < L ? M : A);
@@ -335,21 +361,44 @@ __device__ __forceinline__ void bgm_current(const double* F, const Rec& rec, cx*
     pm[j] = ((j - 1) & 1) ? w >> 8 : w & 0xff;
   }
   bgm_splits<N, L>(
-      F, pm, [&](int j) { return rec(bgm_field<L>(0, j)); }, [&](int j, int l) { return rec(bgm_field<L>(j, l - j)); },
+      F, pm, [&](int j, cx* v) { bgm_load<N>(F, rec(bgm_field<L>(0, j)), v); },
+      [&](int j, int l, cx* v) { bgm_load<N>(F, rec(bgm_field<L>(j, l - j)), v); },
       [&](cx* v) { bgm_load<N>(F, rec(bgm_field<L>(1, L - 1)), v); }, out);
 }
 
-// Current of length 5 (ordering that starts with gluon 0) from its record: as above
-// for lengths 1 .. 3, then the prefix of length 4, the expansion of the last four
-// gluons (three addresses, info), and the prefix masks.
-__device__ __forceinline__ void bgm_current5(const double* F, const BgmRec<BgmShape<5>::F5>& rec, cx* out) {
-  constexpr int N = 5, L = 5, K = bgm_field<L>(0, 4);
+// Canonical current of length 5 from its record: as above for lengths 1 .. 3, then the
+// prefix of length 4, the expansion of the last four gluons (three addresses, info), and
+// the masks.
+template <int N>
+__device__ __forceinline__ void bgm_current5(const double* F, const BgmRec<BgmShape<N>::F5>& rec, cx* out) {
+  constexpr int L = 5, K = bgm_field<L>(0, 4);
   const int w0 = rec(K + 5), w1 = rec(K + 6);
-  const int pm[6] = {0, w0 & 0xff, w0 >> 8, w1 & 0xff, w1 >> 8, (1 << N) - 1};
+  const int pm[6] = {0, w0 & 0xff, w0 >> 8, w1 & 0xff, w1 >> 8, rec(K + 7)};
   bgm_splits<N, L>(
-      F, pm, [&](int j) { return rec(j < 4 ? bgm_field<L>(0, j) : K); },
-      [&](int j, int l) { return rec(bgm_field<L>(j, l - j)); },
+      F, pm, [&](int j, cx* v) { bgm_load<N>(F, rec(j < 4 ? bgm_field<L>(0, j) : K), v); },
+      [&](int j, int l, cx* v) { bgm_load<N>(F, rec(bgm_field<L>(j, l - j)), v); },
       [&](cx* v) { bgm_expand<N>(F, rec(K + 4), [&](int t) { return rec(K + 1 + t); }, v); }, out);
+}
+
+// Current of six gluons, ordering that starts with gluon 0: lengths 1 .. 3, the prefix of
+// length 4, the expansions of gluons 1 .. 4 and 2 .. 5, the prefix of length 5 and the
+// expansion of the last five (variant numbers), the masks.
+__device__ __forceinline__ void bgm_current6(const double* F, const cx16* j5, const BgmRec<BgmShape<6>::F6>& rec,
+                                             cx* out) {
+  constexpr int N = 6, L = 6, K = bgm_field<L>(0, 4);
+  const int w0 = rec(K + 17), w1 = rec(K + 18);
+  const int pm[7] = {0, w0 & 0xff, w0 >> 8, w1 & 0xff, w1 >> 8, rec(K + 19), (1 << N) - 1};
+  bgm_splits<N, L>(
+      F, pm,
+      [&](int j, cx* v) {
+        if (j < 5) bgm_load<N>(F, rec(j < 4 ? bgm_field<L>(0, j) : K), v);
+        else bgm_load5(j5, rec(K + 9), v);
+      },
+      [&](int j, int l, cx* v) {
+        if (l - j < 4) bgm_load<N>(F, rec(bgm_field<L>(j, l - j)), v);
+        else bgm_expand<N>(F, rec(K + 4 * j), [&](int t) { return rec(K + 4 * j - 3 + t); }, v);
+      },
+      [&](cx* v) { bgm_expand5(j5, rec(K + 16), [&](int t) { return rec(K + 10 + t); }, v); }, out);
 }
 
 // Row spinors of one gluon (variant it, both top helicities) and column spinors of one
@@ -421,16 +470,19 @@ __device__ __forceinline__ void bgm_col2_item(double* F, const uint32_t* tabs, d
 }
 
 // Q.J of canonical ordering it >> (N-1), gluon helicities it & (NGH - 1), for the four
-// quark helicity pairs.
+// quark helicity pairs, to qj [ordering][2 u + v][gh] (j5: the currents of length 5 of
+// six gluons).
 template <int N>
-__device__ __forceinline__ void bgm_qj_item(double* F, const uint32_t* tabs, int it) {
+__device__ __forceinline__ void bgm_qj_item(const double* F, const uint32_t* tabs, const cx16* j5, cx16* qj, int it) {
   using S = BgmShape<N>;
   cx j[4];
   if constexpr (N == 5)
-    bgm_current5(F, BgmRec<S::F5>(tabs + S::T5, S::CV(5), it), j);
+    bgm_current5<N>(F, BgmRec<S::F5>(tabs + S::T5, S::CV(5), it), j);
+  else if constexpr (N == 6)
+    bgm_current6(F, j5, BgmRec<S::F6>(tabs + S::T6, S::CV(6), it), j);
   else
     bgm_current<N, 4>(F, BgmRec<S::F4>(tabs + S::T4, S::CV(4), it), j);
-  cx16* dst = reinterpret_cast<cx16*>(F + S::QJOFF) + (it >> (N - 1)) * S::NROW + (it & (S::NGH - 1));
+  cx16* dst = qj + (it >> (N - 1)) * S::NROW + (it & (S::NGH - 1));
 #pragma unroll
   for (int uv = 0; uv < 4; ++uv) {
     cx q[4];
@@ -558,7 +610,7 @@ __device__ __forceinline__ void bgm_prefix_item(const double* F, const BgmPrefix
 #pragma unroll
       for (int t = 0; t < S::QKK; ++t) {
         if (t < qn) {
-          const char* qt = q + rec(FC + 1 + t);
+          const char* qt = q + rec(FC + 1 + t) * (16 * S::NROW);
 #pragma unroll
           for (int uv = 0; uv < 4; ++uv) {
             const cx16 x = *reinterpret_cast<const cx16*>(qt + 16 * uv * S::NGH);
@@ -587,6 +639,111 @@ __device__ __forceinline__ void bgm_prefix_item(const double* F, const BgmPrefix
         jt[(int64_t)(2 * col) * RS + row] = y.r;
         jt[(int64_t)(2 * col + 1) * RS + row] = y.i;
         note(row, y.r, y.i);
+      }
+    }
+  }
+}
+
+// The same for six gluons, cut at position 3: the row spinor of three gluons is formed
+// here, R(sigma[:3]) = S . i g X_3, currents of length 5 and Q.J come from memory, and
+// each leaf is formed after the other (register space).
+template <int RS>
+__device__ __forceinline__ void bgm_prefix6_item(const double* F, const uint32_t* tabs, const BgmEnds& ends, double mt,
+                                                 const cx16* j5, const cx16* qj, double* __restrict__ jt, int it) {
+  constexpr int N = 6;
+  using S = BgmShape<N>;
+  const BgmRec<S::FP> rec(tabs + S::TP, S::VP, it);
+  constexpr int FC = 26;
+  const double g = F[S::GOFF];
+  cx r3[2][4], x4[2][4], x5[2][4];
+  auto add = [&](cx(*x)[4], const cx* j, const cx(*r)[4], bool first) {
+    const BgmSlash s = bgm_slash(j);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (first) bgm_rg(r[u], s, x[u]);
+      else bgm_rg_acc(r[u], s, x[u]);
+      bgm_pin(x[u]);
+    }
+  };
+  cx j[4], r[2][4];
+  bgm_load<N>(F, rec(4), j);
+  add(r3, j, ends.ub, true);
+  bgm_expand<N>(F, rec(8), [&](int t) { return rec(5 + t); }, j);
+  add(x4, j, ends.ub, true);
+  bgm_expand5(j5, rec(18), [&](int t) { return rec(12 + t); }, j);
+  add(x5, j, ends.ub, true);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) bgm_load<N>(F, rec(k) + 16 * u * S::V(k + 1), r[u]);
+    bgm_load<N>(F, rec(3 - k), j);
+    add(r3, j, r, false);
+    bgm_load<N>(F, rec(9 + k), j);
+    add(x4, j, r, false);
+    if (k == 0) bgm_expand<N>(F, rec(22), [&](int t) { return rec(19 + t); }, j);
+    else bgm_load<N>(F, rec(23), j);
+    add(x5, j, r, false);
+  }
+  {
+    const int m = rec(25);
+    double q[4];
+    bgm_topmom<N>(F, m, q);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      cx y[4];
+      bgh_prop(r3[u], q, F[S::TFOFF + m], mt, g, y);
+      bgh_copy(y, r3[u]);
+      bgm_pin(r3[u]);
+    }
+  }
+  bgm_load<N>(F, rec(11), j);
+  add(x4, j, r3, false);
+  bgm_load<N>(F, rec(24), j);
+  add(x5, j, r3, false);
+  const int qinfo = rec(FC + 1 + S::QKK), qn = qinfo & 0x7fff;
+  const double qs = (qinfo & 0x8000) ? -1.0 : 1.0;
+  const int nleaf = it < S::VP2 ? 2 : 1;
+#pragma unroll 1
+  for (int h = 0; h < nleaf; ++h) {
+    const BgmRec<S::FL> leaf(tabs + (h ? S::TL1 : S::TL0), h ? S::VP2 : S::VP, it);
+    const int gh = leaf(14);
+    cx xn[2][4];
+    bgm_expand5(j5, leaf(6), [&](int t) { return leaf(t); }, j);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) bgm_load<N>(F, rec(0) + 16 * u * S::V(1), r[u]);
+    add(xn, j, r, true);
+    bgm_expand<N>(F, leaf(10), [&](int t) { return leaf(7 + t); }, j);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) bgm_load<N>(F, rec(1) + 16 * u * S::V(2), r[u]);
+    add(xn, j, r, false);
+    bgm_load<N>(F, leaf(11), j);
+    add(xn, j, r3, false);
+    cx a[4];
+#pragma unroll
+    for (int uv = 0; uv < 4; ++uv) a[uv] = cx{0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < S::QKK; ++t)
+      if (t < qn) {
+        const cx16* q = qj + rec(FC + 1 + t) * S::NROW + gh;
+#pragma unroll
+        for (int uv = 0; uv < 4; ++uv) {
+          const cx16 x = q[uv * S::NGH];
+          a[uv] = a[uv] + cx{x.r, x.i};
+        }
+      }
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      cx c[4], w[2];
+      bgm_load<N>(F, leaf(13) + 16 * v * S::V(1), c);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) w[u] = sdot(xn[u], ends.v[v]) + sdot(x5[u], c);
+      bgm_load<N>(F, leaf(12) + 16 * v * S::V(2), c);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const cx x = w[u] + sdot(x4[u], c), q = a[2 * u + v];
+        const int row = (2 * u + v) * S::NGH + gh, col = rec(FC);
+        jt[(int64_t)(2 * col) * RS + row] = qs * q.r - g * x.i;
+        jt[(int64_t)(2 * col + 1) * RS + row] = qs * q.i + g * x.r;
       }
     }
   }
@@ -621,10 +778,12 @@ __device__ __forceinline__ int bgm_row(int h) {
 // evenly, but three waves a SIMD leave room for 168 registers each, and workgroups of
 // six waves were seen to run one at a time on a compute unit (65 ms for 262144 events
 // where four waves took 40, before later changes).  A four-gluon event (19 KB) is one wave's work; four share a
-// workgroup so that the set-up, which differs from lane to lane, is shared by kind.
+// workgroup so that the set-up, which differs from lane to lane, is shared by kind.  A
+// six-gluon event (124 KB) has a compute unit to itself: eight waves, two a SIMD.
 template <int N> struct BgmLaunchShape;
 template <> struct BgmLaunchShape<4> { static constexpr int EV = 4, WPE = 1, W = 2; };
 template <> struct BgmLaunchShape<5> { static constexpr int EV = 1, WPE = 4, W = 2; };
+template <> struct BgmLaunchShape<6> { static constexpr int EV = 1, WPE = 8, W = 2; };
 
 // The items of a level to the threads, whole waves: the items of the next kind start
 // on a wave of their own.
@@ -719,7 +878,7 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* __restri
   double* F = lds + ev * S::FRAME;
   double* je = jt + ev * S::NROW;
   const bool on = ev < nev;
-  if constexpr (N == 5) {
+  if constexpr (N >= 5) {
     if (on)
       for (int i = t; i < S::CV(4); i += TE) {
         cx j[4];
@@ -728,12 +887,31 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* __restri
       }
     __syncthreads();
   }
+  // currents of length 5 and Q.J of six gluons are in the event's scratch
+  cx16* j5 = reinterpret_cast<cx16*>(je + S::XJOFF);
+  cx16* qj = S::BIG ? reinterpret_cast<cx16*>(je + S::XQOFF) : reinterpret_cast<cx16*>(F + S::QJOFF);
+  if constexpr (S::BIG) {
+    for (int i = t; i < S::CV(5); i += TE) {
+      cx j[4];
+      bgm_current5<N>(F, BgmRec<S::F5>(tabs + S::T5, S::CV(5), i), j);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) j5[c * S::CV(5) + i] = cx16{j[c].r, j[c].i};
+    }
+    pairs(t, TE);
+    __syncthreads();
+  }
   if (on) {
     constexpr int NQ = S::NCAN * S::NGH;
-    for (int i = t; i < NQ; i += TE) bgm_qj_item<N>(F, tabs, i);
+    for (int i = t; i < NQ; i += TE) bgm_qj_item<N>(F, tabs, j5, qj, i);
     if (N == 5 && t >= NQ % TE) pairs(t - NQ % TE, TE - NQ % TE);   // the waves without a second current
   }
   __syncthreads();
+  if constexpr (S::BIG) {
+    BgmEnds ends;
+    bgm_ends<N>(F, ends);
+    for (int i = t; i < S::VP; i += TE) bgm_prefix6_item<S::NROW>(F, tabs, ends, mt, j5, qj, je, i);
+    return;
+  }
   if (on) {
     BgmEnds ends;
     bgm_ends<N>(F, ends);
@@ -768,20 +946,16 @@ typedef double bgm_f64x4 __attribute__((ext_vector_type(4)));
 // FP64 colour form in symmetry sectors.  Relabelling gluons (0 1) and (2 3), and
 // reversing the ordering, each map orderings to orderings and leave the colour matrix
 // unchanged, and they commute: in the sums and differences over their orbits the
-// matrix falls into eight blocks (bgm_sector_tables), of at most NO rows, NO the
-// number of orbits (4, 16).  An orbit's members are read once and combined by three
+// matrix falls into eight blocks (bgm_sectors), one row per orbit (4, 16).  Six gluons
+// have the exchange of (4 5) too: sixteen blocks of 48.  An orbit's members are read once and combined by
 // stages of butterflies in registers:
 //   a_s[o] = sum_b (-1)^popcount(s & b) A(member b of orbit o).
-template <int N>
-struct BgmOrbits {
-  static constexpr int NO = N == 4 ? 4 : 16;
-};
-
+template <int G>
 __device__ __forceinline__ void bgm_butterfly(double* x) {
 #pragma unroll
-  for (int d = 1; d < 8; d <<= 1)
+  for (int d = 1; d < G; d <<= 1)
 #pragma unroll
-    for (int b = 0; b < 8; ++b)
+    for (int b = 0; b < G; ++b)
       if (!(b & d)) {
         const double p = x[b], q = x[b | d];
         x[b] = p + q;
@@ -817,7 +991,7 @@ __device__ __forceinline__ double bgm_colour5(const double* __restrict__ jt, con
 #pragma unroll
     for (int p = 0; p < 2; ++p)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) bgm_butterfly(a[p][q]);
+      for (int q = 0; q < 4; ++q) bgm_butterfly<8>(a[p][q]);
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       bgm_f64x4 acc[2] = {bgm_f64x4{0.0, 0.0, 0.0, 0.0}, bgm_f64x4{0.0, 0.0, 0.0, 0.0}};
@@ -851,7 +1025,7 @@ __device__ __forceinline__ double bgm_colour4(const double* __restrict__ je, con
   for (int o = 0; o < 4; ++o) {
 #pragma unroll
     for (int b = 0; b < 8; ++b) a[o][b] = x[(int)orb[o * 8 + b] * 2 * RS];
-    bgm_butterfly(a[o]);
+    bgm_butterfly<8>(a[o]);
   }
   double f = 0.0;
 #pragma unroll
@@ -876,6 +1050,60 @@ struct BgmRowMax {
     atomicMax(m + k, (unsigned long long)__double_as_longlong(fmax(fabs(re), fabs(im))));
   }
 };
+
+// Six gluons: 16 rows' real or imaginary parts at a time.  The workgroup transforms the
+// 48 orbits of the 16 columns into LDS ([sector][orbit][column]); each wave then takes
+// two sectors, three 16-row blocks each, on the matrix cores as above (blocks below the
+// diagonal skipped, those above doubled).  192 x 2 products per column group of 16
+// against 2 x 4140 of the block-triangular form of 720 flows.
+template <int WAVES>
+__device__ __forceinline__ double bgm_colour6(double* lds, const double* __restrict__ jt,
+                                              const uint16_t* __restrict__ orb, const float* __restrict__ sec,
+                                              const int* weight) {
+  constexpr int RS = BgmShape<6>::NROW, NO = 48, G = 16;
+  const int l = threadIdx.x & 63, j = l & 15, kq = l >> 4, w = threadIdx.x >> 6;
+  double sum = 0.0;
+  for (int grp = 0; grp < RS / 8; ++grp) {
+    const double* x = jt + (grp & 1) * RS + 16 * (grp >> 1);
+    for (int i = threadIdx.x; i < NO * 16; i += 64 * WAVES) {
+      const int o = i >> 4, c = i & 15;
+      double a[G];
+#pragma unroll
+      for (int b = 0; b < G; ++b) a[b] = x[(int)orb[o * G + b] * 2 * RS + c];
+      bgm_butterfly<G>(a);
+#pragma unroll
+      for (int s = 0; s < G; ++s) lds[(s * NO + o) * 16 + c] = a[s];
+    }
+    __syncthreads();
+    double f = 0.0;
+    for (int s = w; s < G; s += WAVES) {
+      double b[12];
+#pragma unroll
+      for (int q = 0; q < 12; ++q) b[q] = lds[(s * NO + 4 * q + kq) * 16 + j];
+      bgm_f64x4 acc[3];
+      const float* m = sec + (int64_t)s * 24 * 64 + l;
+#pragma unroll
+      for (int mb = 0; mb < 3; ++mb) {
+        acc[mb] = bgm_f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int kb = mb; kb < 3; ++kb)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            acc[mb] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)*m, b[4 * kb + q], acc[mb], 0, 0, 0);
+            m += 64;
+          }
+      }
+#pragma unroll
+      for (int mb = 0; mb < 3; ++mb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) f += b[4 * mb + v] * acc[mb][v];
+    }
+    const int row = 16 * (grp >> 1) + j;
+    sum += weight[row] ? (double)weight[row] * f : 0.0;
+    __syncthreads();
+  }
+  return sum;
+}
 
 // Split-precision colour matrix staged in LDS for the fused kernel: flows in blocks
 // of 32, the block-triangular form (blocks (mb, kb), kb >= mb: CF on the diagonal,
@@ -1108,7 +1336,10 @@ bgm_fused_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt
         if (l == 0) out[e0 + w] = scale * v;
       }
     } else {
-      const double v = bgm_wave_sum(bgm_colour5<WAVES>(slot, orb, sec, weight));
+      double v;
+      if constexpr (N == 5) v = bgm_colour5<WAVES>(slot, orb, sec, weight);
+      else v = bgm_colour6<WAVES>(bgm_lds, slot, orb, sec, weight);
+      v = bgm_wave_sum(v);
       if (l == 0) part[w] = v;
       __syncthreads();
       if (threadIdx.x == 0) {
@@ -1141,11 +1372,15 @@ constexpr size_t bgm_lds_bytes() {
 // least over the colour-sum formats.
 template <int N>
 int bgm_fused_per_cu() {
-  if constexpr (N == 4 || N == 5) {
+  if constexpr (N >= 4) {
     int best = 1 << 20;
-    for (const void* fn : {bgm_fused_fn<N, -1, true>(), bgm_fused_fn<N, CS_FMT_FP16, true>(),
-                           bgm_fused_fn<N, CS_FMT_BF16, true>(), bgm_fused_fn<N, -1, false>(),
-                           bgm_fused_fn<N, CS_FMT_FP16, false>(), bgm_fused_fn<N, CS_FMT_BF16, false>()}) {
+    std::initializer_list<const void*> fns;
+    if constexpr (N == 6)
+      fns = {bgm_fused_fn<N, -1, false>()};
+    else
+      fns = {bgm_fused_fn<N, -1, true>(),  bgm_fused_fn<N, CS_FMT_FP16, true>(),  bgm_fused_fn<N, CS_FMT_BF16, true>(),
+             bgm_fused_fn<N, -1, false>(), bgm_fused_fn<N, CS_FMT_FP16, false>(), bgm_fused_fn<N, CS_FMT_BF16, false>()};
+    for (const void* fn : fns) {
       if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bgm_lds_bytes<N>()) != hipSuccess)
         return 0;
       int nb = 0;
@@ -1163,7 +1398,7 @@ int bgm_fused_per_cu() {
 // Doubles of scratch and events per workgroup of the fused kernels (0 if not built).
 template <int N>
 int64_t bgm_fused_slot_doubles() {
-  if constexpr (N == 4 || N == 5) {
+  if constexpr (N >= 4) {
     return (int64_t)BgmLaunchShape<N>::EV * BgmShape<N>::SLOT;
   } else {
     return 0;
@@ -1171,7 +1406,7 @@ int64_t bgm_fused_slot_doubles() {
 }
 template <int N>
 int bgm_block_events() {
-  if constexpr (N == 4 || N == 5) {
+  if constexpr (N >= 4) {
     return BgmLaunchShape<N>::EV;
   } else {
     return 0;
@@ -1215,6 +1450,8 @@ hipError_t launch_bg(const BgArgs& a) {
       return a.variant == 5 ? launch_bgm_fused_p<N, true>(a) : launch_bgm_fused_p<N, false>(a);
     if (a.variant >= 3) return launch_bgh<N>(a);
   } else {
+    if constexpr (N == 6)
+      if (a.out) return launch_bgm_fused_fmt<N, -1, false>(a);
     if (a.variant >= 3) return hipErrorInvalidValue;
   }
   if (a.variant == 1) return launch_bg_v<N, 1>(a);

@@ -23,13 +23,14 @@ struct BgmShape {
   static constexpr int NGH = 1 << (N - 1);        // gluon helicities with gluon 0 fixed
   static constexpr int NROW = 4 * NGH;            // rows of an event: (u, v) x gluon helicities
   static constexpr int NCAN = fact(N - 1);        // orderings that start with gluon 0
-  static constexpr int QKK = N == 4 ? 3 : 6;      // most terms of an expansion over them
-  static constexpr bool TWO = N == 5;             // column spinors of two gluons are stored
-  // slots of stored four-vectors: currents of length 1, 2, 3 and, for five gluons, 4
-  // (canonical); row spinors of length 1, 2 per top helicity; column
+  static constexpr int QKK = comb(N - 1, (N - 1) / 2);   // most terms of an expansion over them
+  static constexpr bool TWO = N >= 5;             // column spinors of two gluons are stored
+  static constexpr bool BIG = N == 6;             // currents of length 5 and Q.J in memory, not in LDS
+  // slots of stored four-vectors: currents of length 1, 2, 3 and, from five gluons on,
+  // 4 (canonical); row spinors of length 1, 2 per top helicity; column
   // spinors of length 1 (2) per antitop helicity; ubar[2], v[2], Q[2][2]
   static constexpr int cslot(int L) { return L == 1 ? 0 : L == 2 ? V(1) : L == 3 ? V(1) + V(2) : V(1) + V(2) + SV(3); }
-  static constexpr int R1S = cslot(4) + (N == 5 ? CV(4) : 0);
+  static constexpr int R1S = cslot(4) + (N >= 5 ? CV(4) : 0);
   static constexpr int R2S = R1S + 2 * V(1);
   static constexpr int C1S = R2S + 2 * V(2);
   static constexpr int C2S = C1S + 2 * V(1);
@@ -38,11 +39,11 @@ struct BgmShape {
   static constexpr int QS = VS + 2;
   static constexpr int NS = QS + 4;
   // words of a record and items of each phase, in the order of the tables
-  static constexpr int F1 = 1, F2 = 3, FR2 = 6, F3 = 7, F4 = 11, F5 = 19;
+  static constexpr int F1 = 1, F2 = 3, FR2 = 6, F3 = 7, F4 = 11, F5 = 20, F6 = 35;
   static constexpr int VP = V(N - 1);             // prefix items
   static constexpr int VP2 = (N - 1) * perm(N - 1, N - 2) * (1 << (N - 2));   // those with gluon 0: two leaves
-  static constexpr int FP = N == 4 ? 5 + 1 + QKK + 1 : 5 + 2 + 4 + 1 + QKK + 1;
-  static constexpr int FL = N == 4 ? 4 : 8;
+  static constexpr int FP = (N == 4 ? 5 : N == 5 ? 11 : 26) + 1 + QKK + 1;
+  static constexpr int FL = N == 4 ? 4 : N == 5 ? 8 : 15;
   static constexpr int words(int f) { return (f + 1) / 2; }
   static constexpr int T1 = 0;
   static constexpr int T2 = T1 + words(F1) * V(1);
@@ -50,22 +51,26 @@ struct BgmShape {
   static constexpr int T3 = TR2 + words(FR2) * V(2);
   static constexpr int T4 = T3 + words(F3) * SV(3);
   static constexpr int T5 = T4 + words(F4) * CV(4);
-  static constexpr int TP = T5 + (N == 5 ? words(F5) * CV(5) : 0);
+  static constexpr int T6 = T5 + (N >= 5 ? words(F5) * CV(5) : 0);
+  static constexpr int TP = T6 + (BIG ? words(F6) * CV(6) : 0);
   static constexpr int TL0 = TP + words(FP) * VP;
   static constexpr int TL1 = TL0 + words(FL) * VP;
   static constexpr int TWORDS = TL1 + words(FL) * VP2;
   // frame in doubles: the slots (component-major: component c of slot s is the complex
-  // number at c NS + s), Q.J of the canonical orderings (complex [NCAN][4][NGH]),
-  // momentum sums and propagators of every subset, momenta, coupling
+  // number at c NS + s), Q.J of the canonical orderings (complex [NCAN][4][NGH]; up to
+  // five gluons), momentum sums and propagators of every subset, momenta, coupling
   static constexpr int QJOFF = 8 * NS;
-  static constexpr int PSOFF = QJOFF + 2 * NCAN * NROW;   // momentum sums [2^N][4]
+  static constexpr int PSOFF = QJOFF + (BIG ? 0 : 2 * NCAN * NROW);   // momentum sums [2^N][4]
   static constexpr int GIOFF = PSOFF + (4 << N);          // 1 / P(mask)^2
   static constexpr int TFOFF = GIOFF + (1 << N);          // 1 / (q^2 - mt^2), q = p3 - P(mask)
   static constexpr int MOFF = TFOFF + (1 << N);           // momenta [N + 2][4]
   static constexpr int GOFF = MOFF + 4 * (N + 2);         // coupling
   static constexpr int FRAME = GOFF + 2;
-  // doubles of an event's scratch: dual amplitudes [2 NCOL][NROW]
-  static constexpr int SLOT = 2 * NCOL * NROW;
+  // doubles of an event's scratch: dual amplitudes [2 NCOL][NROW]; for six gluons also
+  // Q.J and the canonical currents of length 5, complex [4][CV(5)]
+  static constexpr int XQOFF = 2 * NCOL * NROW;
+  static constexpr int XJOFF = XQOFF + (BIG ? 2 * NCAN * NROW : 0);
+  static constexpr int SLOT = XJOFF + (BIG ? 8 * CV(5) : 0);
 };
 
 }  // namespace me

@@ -30,15 +30,21 @@ template <int N>
 class BgmBuilder {
   using S = BgmShape<N>;
   typedef std::vector<int> Seq;
-  std::map<Seq, int> var_;        // first variant of every full sequence among those of its length
-  std::map<Seq, int> var3_;       // the same among the stored sequences of length 3 (first gluon < last)
-  std::map<Seq, int> canon_;      // the same for canonical sequences (lowest gluon first)
+  // by code(s): first variant of every sequence among those of its length, the same among
+  // the stored sequences of length 3 (first gluon < last) and the canonical sequences
+  // (lowest gluon first), and the sequence's rank among its length's
+  std::vector<int> var_, var3_, canon_, rank_;
   std::vector<std::vector<Seq>> full_, can_;   // by length, in variant order
 
   static int mask(const Seq& s, int a, int b) {
     int m = 0;
     for (int i = a; i < b; ++i) m |= 1 << s[i];
     return m;
+  }
+  static int code(const Seq& s) {
+    int c = 0;
+    for (int g : s) c = 8 * c + g + 1;
+    return c;
   }
   static int nvar(int m) { return 1 << __builtin_popcount(m >> 1); }
   // bits of hv deposited at the gluons of m other than gluon 0 (bit b - 1 = gluon b)
@@ -57,15 +63,15 @@ class BgmBuilder {
   static Seq part(const Seq& s, int a, int b) { return Seq(s.begin() + a, s.begin() + b); }
   static uint16_t slot(int s) { return (uint16_t)(16 * s); }   // byte offset of the slot's first component
 
-  int variant(const Seq& s, int gh) const { return var_.at(s) + extract(gh, mask(s, 0, (int)s.size())); }
-  int cvariant(const Seq& s, int gh) const { return canon_.at(s) + extract(gh, mask(s, 0, (int)s.size())); }
+  int variant(const Seq& s, int gh) const { return var_.at(code(s)) + extract(gh, mask(s, 0, (int)s.size())); }
+  int cvariant(const Seq& s, int gh) const { return canon_.at(code(s)) + extract(gh, mask(s, 0, (int)s.size())); }
 
   // stored current of s[a:b] at gluon helicities gh
   uint16_t cur(const Seq& s, int a, int b, int gh) const {
     const Seq p = part(s, a, b);
     const int L = b - a;
     if (L == 3 && p[0] > p[2]) return cur(Seq(p.rbegin(), p.rend()), 0, 3, gh);
-    if (L <= 3) return slot(S::cslot(L) + (L == 3 ? var3_.at(p) + extract(gh, mask(p, 0, 3)) : variant(p, gh)));
+    if (L <= 3) return slot(S::cslot(L) + (L == 3 ? var3_.at(code(p)) + extract(gh, mask(p, 0, 3)) : variant(p, gh)));
     return slot(S::cslot(L) + cvariant(p, gh));   // canonical sequences of length 4
   }
 
@@ -97,6 +103,14 @@ class BgmBuilder {
     r.push_back(info(e.size(), neg));
   }
 
+  // the same for s[a:b] of length 5 (variant numbers)
+  void kk5(std::vector<uint16_t>& r, const Seq& s, int a, int b, int gh) const {
+    bool neg;
+    const std::vector<Seq> e = expand(part(s, a, b), &neg);
+    for (int t = 0; t < 6; ++t) r.push_back((uint16_t)cvariant(e[t < (int)e.size() ? t : 0], gh));
+    r.push_back(info(e.size(), neg));
+  }
+
   static void perms(const Seq& from, int len, Seq& cur, std::vector<Seq>& out) {
     if ((int)cur.size() == len) {
       out.push_back(cur);
@@ -111,7 +125,8 @@ class BgmBuilder {
   }
 
  public:
-  BgmBuilder() : full_(N + 1), can_(N + 1) {
+  BgmBuilder()
+      : var_(1 << 3 * N, -1), var3_(var_), canon_(var_), rank_(var_), full_(N + 1), can_(N + 1) {
     Seq all;
     for (int g = 0; g < N; ++g) all.push_back(g);
     for (int L = 1; L <= N; ++L) {
@@ -120,13 +135,14 @@ class BgmBuilder {
       int nf = 0, nc = 0, n3 = 0;
       for (const Seq& s : full_[L]) {
         if (L == 3 && s[0] < s[2]) {
-          var3_[s] = n3;
+          var3_[code(s)] = n3;
           n3 += nvar(mask(s, 0, 3));
         }
-        var_[s] = nf;
+        rank_[code(s)] = &s - &full_[L][0];
+        var_[code(s)] = nf;
         nf += nvar(mask(s, 0, L));
         if (*std::min_element(s.begin(), s.end()) == s[0]) {
-          canon_[s] = nc;
+          canon_[code(s)] = nc;
           can_[L].push_back(s);
           nc += nvar(mask(s, 0, L));
         }
@@ -149,9 +165,8 @@ class BgmBuilder {
                             slot(S::R1S + variant(part(s, 0, 1), gh)), slot(S::C1S + variant(part(s, 1, 2), gh)),
                             (uint16_t)mask(s, 0, 2)});
       }
-    for (const auto& sv : var3_)
-      stored3.push_back(sv.first);
-    std::sort(stored3.begin(), stored3.end(), [&](const Seq& a, const Seq& b) { return var3_.at(a) < var3_.at(b); });
+    for (const Seq& s : full_[3])
+      if (s[0] < s[2]) stored3.push_back(s);
     for (const Seq& s : stored3)
       for (int hv = 0; hv < nvar(mask(s, 0, 3)); ++hv) {
         const int gh = deposit(hv, mask(s, 0, 3));
@@ -176,20 +191,43 @@ class BgmBuilder {
     rtwo.append(out);
     three.append(out);
     four.append(out);
-    if (N == 5) {
+    if (N >= 5) {
+      // canonical currents of length 5
       BgmPhase five(S::CV(5), S::F5);
-      for (const Seq& s : can_[N])
-        for (int gh = 0; gh < nvar(mask(s, 0, N)); ++gh) {
+      for (const Seq& s : can_[5])
+        for (int hv = 0; hv < nvar(mask(s, 0, 5)); ++hv) {
+          const int gh = deposit(hv, mask(s, 0, 5));
           std::vector<uint16_t> r;
           for (int L = 1; L <= 3; ++L)
-            for (int a = 0; a + L <= N; ++a) r.push_back(cur(s, a, a + L, gh));
+            for (int a = 0; a + L <= 5; ++a) r.push_back(cur(s, a, a + L, gh));
           r.push_back(cur(s, 0, 4, gh));
           kk4(r, s, 1, 5, gh);
           r.push_back((uint16_t)(mask(s, 0, 1) | mask(s, 0, 2) << 8));
           r.push_back((uint16_t)(mask(s, 0, 3) | mask(s, 0, 4) << 8));
+          r.push_back((uint16_t)mask(s, 0, 5));
           five.rec.push_back(r);
         }
       five.append(out);
+    }
+    if (N == 6) {
+      // orderings of all six gluons that start with gluon 0
+      BgmPhase six(S::CV(6), S::F6);
+      for (const Seq& s : can_[N])
+        for (int gh = 0; gh < S::NGH; ++gh) {
+          std::vector<uint16_t> r;
+          for (int L = 1; L <= 3; ++L)
+            for (int a = 0; a + L <= 6; ++a) r.push_back(cur(s, a, a + L, gh));
+          r.push_back(cur(s, 0, 4, gh));
+          kk4(r, s, 1, 5, gh);
+          kk4(r, s, 2, 6, gh);
+          r.push_back((uint16_t)cvariant(part(s, 0, 5), gh));
+          kk5(r, s, 1, 6, gh);
+          r.push_back((uint16_t)(mask(s, 0, 1) | mask(s, 0, 2) << 8));
+          r.push_back((uint16_t)(mask(s, 0, 3) | mask(s, 0, 4) << 8));
+          r.push_back((uint16_t)mask(s, 0, 5));
+          six.rec.push_back(r);
+        }
+      six.append(out);
     }
     // prefix items: sequences of length N - 1 (the last gluon follows from them), those
     // with gluon 0 inside first (two leaves each), by the position of gluon 0 and then
@@ -200,10 +238,6 @@ class BgmBuilder {
       const int a0 = pos(a, 0), b0 = pos(b, 0);
       return a0 != b0 ? a0 < b0 : pos(a, 1) < pos(b, 1);
     });
-    std::map<Seq, int> col;
-    for (int c = 0; c < (int)full_[N].size(); ++c) col[full_[N][c]] = c;
-    std::map<Seq, int> qrank;
-    for (int c = 0; c < (int)can_[N].size(); ++c) qrank[can_[N][c]] = c;
     BgmPhase pre(S::VP, S::FP), leaf0(S::VP, S::FL), leaf1(S::VP2, S::FL);
     for (const Seq& s : order) {
       const int m = mask(s, 0, N - 1);
@@ -222,8 +256,16 @@ class BgmBuilder {
           r.push_back(cur(f, 1, 4, gh));
           kk4(r, f, 0, 4, gh);
         }
-        r.push_back((uint16_t)col.at(f));
-        for (int t = 0; t < S::QKK; ++t) r.push_back((uint16_t)(16 * S::NROW * qrank.at(qe[t < (int)qe.size() ? t : 0])));
+        if (N == 6) {
+          kk4(r, f, 0, 4, gh);
+          for (int a : {1, 2, 3}) r.push_back(cur(f, a, 4, gh));
+          kk5(r, f, 0, 5, gh);
+          kk4(r, f, 1, 5, gh);
+          for (int a : {2, 3}) r.push_back(cur(f, a, 5, gh));
+          r.push_back((uint16_t)mask(f, 0, 3));
+        }
+        r.push_back((uint16_t)rank_.at(code(f)));
+        for (int t = 0; t < S::QKK; ++t) r.push_back((uint16_t)rank_.at(code(qe[t < (int)qe.size() ? t : 0])));
         r.push_back(info(qe.size(), neg));
         pre.rec.push_back(r);
         for (int h = 0; h < (last ? 2 : 1); ++h) {
@@ -233,6 +275,11 @@ class BgmBuilder {
             kk4(q, f, 1, 5, gl);
             q.push_back(cur(f, 2, 5, gl));
             q.push_back(slot(S::C2S + variant(part(f, 3, 5), gl)));
+          } else if (N == 6) {
+            kk5(q, f, 1, 6, gl);
+            kk4(q, f, 2, 6, gl);
+            q.push_back(cur(f, 3, 6, gl));
+            q.push_back(slot(S::C2S + variant(part(f, 4, 6), gl)));
           } else {
             q.push_back(cur(f, 1, 4, gl));
             q.push_back(cur(f, 2, 4, gl));
@@ -249,6 +296,13 @@ class BgmBuilder {
     return out;
   }
 };
+
+// The work-item tables of N gluons, built on first use (they depend on nothing else).
+template <int N>
+const std::vector<uint32_t>& bgm_items() {
+  static const std::vector<uint32_t> items = BgmBuilder<N>().build();
+  return items;
+}
 
 // Orbits of the orderings of n gluons under the exchanges of gluons 0 and 1, 2 and 3,
 // (4 and 5) and the reversal, all of which leave the colour matrix unchanged, and the
@@ -296,38 +350,41 @@ inline BgmSectors bgm_sectors(int n, const int* cf) {
     ++r.norb;
   }
   r.sec.assign((size_t)G * r.norb * r.norb, 0.0);
-  for (int sct = 0; sct < G; ++sct)
-    for (int o = 0; o < r.norb; ++o)
-      for (int p = 0; p < r.norb; ++p) {
-        // the projection of A on the sector is (-1)^popcount(s & b) a_s[o] / G at member
-        // b; each distinct member once
+  // members that coincide with an earlier one, and the sectors in which one coincides
+  // with its own negative (a_s[o] is zero there)
+  std::vector<bool> first((size_t)r.norb * G, true), null((size_t)r.norb * G, false);
+  for (int o = 0; o < r.norb; ++o)
+    for (int b = 0; b < G; ++b)
+      for (int d = 0; d < b; ++d)
+        if (r.orb[(size_t)o * G + b] == r.orb[(size_t)o * G + d]) {
+          first[(size_t)o * G + b] = false;
+          for (int s2 = 0; s2 < G; ++s2)
+            if (__builtin_popcount(s2 & (b ^ d)) & 1) null[(size_t)o * G + s2] = true;
+        }
+  for (int o = 0; o < r.norb; ++o)
+    for (int p = 0; p < r.norb; ++p) {
+      // the projection of A on a sector is (-1)^popcount(s & b) a_s[o] / G at member b;
+      // each distinct member once
+      std::vector<double> by(G, 0.0);
+      for (int b = 0; b < G; ++b)
+        for (int c = 0; c < G; ++c)
+          if (first[(size_t)o * G + b] && first[(size_t)p * G + c])
+            by[b ^ c] += cf[(size_t)r.orb[(size_t)o * G + b] * ncol + r.orb[(size_t)p * G + c]];
+      for (int s2 = 0; s2 < G; ++s2) {
+        if (null[(size_t)o * G + s2] || null[(size_t)p * G + s2]) continue;
         double m = 0.0;
-        bool null_o = false, null_p = false;
-        for (int b = 0; b < G; ++b)
-          for (int c = 0; c < G; ++c) {
-            const int x = r.orb[(size_t)o * G + b], y = r.orb[(size_t)p * G + c];
-            bool first = true;
-            for (int d = 0; d < b; ++d)
-              if (r.orb[(size_t)o * G + d] == x) {
-                first = false;
-                if (__builtin_popcount(sct & (b ^ d)) & 1) null_o = true;
-              }
-            for (int d = 0; d < c; ++d)
-              if (r.orb[(size_t)p * G + d] == y) {
-                first = false;
-                if (__builtin_popcount(sct & (c ^ d)) & 1) null_p = true;
-              }
-            if (first) m += (__builtin_popcount(sct & (b ^ c)) & 1 ? -1.0 : 1.0) * cf[(size_t)x * ncol + y];
-          }
-        // where a member coincides with its own negative, a_s[o] is zero
-        r.sec[((size_t)sct * r.norb + o) * r.norb + p] = null_o || null_p ? 0.0 : m / ((double)G * G);
+        for (int d = 0; d < G; ++d) m += __builtin_popcount(s2 & d) & 1 ? -by[d] : by[d];
+        r.sec[((size_t)s2 * r.norb + o) * r.norb + p] = m / ((double)G * G);
       }
+    }
   return r;
 }
 
 // The sectors as the kernels read them (FP32, exact): four orbits as they are, upper
-// triangle with the elements above the diagonal doubled [8][4][4]; sixteen in the lane
-// order of the matrix operand, element (s 4 + q) 64 + l = sec[s][l % 16][4 q + l / 16].
+// triangle with the elements above the diagonal doubled [8][4][4]; more orbits in the
+// lane order of the matrix operand, 16 x 16 blocks (mb, kb >= mb) of each sector in turn,
+// those above the diagonal doubled: element ((block) 4 + q) 64 + l =
+// sec[s][16 mb + l % 16][16 kb + 4 q + l / 16].
 inline std::vector<float> bgm_sector_operands(const BgmSectors& s) {
   std::vector<float> r;
   const int G = 1 << s.nsym, n = s.norb;
@@ -337,8 +394,11 @@ inline std::vector<float> bgm_sector_operands(const BgmSectors& s) {
       for (int i = 0; i < 4; ++i)
         for (int j = 0; j < 4; ++j) r.push_back(j < i ? 0.0f : j == i ? at(k, i, j) : 2.0f * at(k, i, j));
     } else {
-      for (int q = 0; q < 4; ++q)
-        for (int l = 0; l < 64; ++l) r.push_back(at(k, l % 16, 4 * q + l / 16));
+      for (int mb = 0; mb < n / 16; ++mb)
+        for (int kb = mb; kb < n / 16; ++kb)
+          for (int q = 0; q < 4; ++q)
+            for (int l = 0; l < 64; ++l)
+              r.push_back((kb > mb ? 2.0f : 1.0f) * at(k, 16 * mb + l % 16, 16 * kb + 4 * q + l / 16));
     }
   }
   return r;

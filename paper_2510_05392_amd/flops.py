@@ -195,7 +195,8 @@ def bgh_event(n):
 # Two-sided recursion (csrc/me_bgm.h), one event: operations of its phases, counted by
 # compiling it for the host with the operation-counting scalar (tests/test_bgm.py)
 BGM = {4: {'setup': 1194, 'currents': 37944, 'spinors': 18796, 'qj': 56880, 'prefixes': 151488},
-       5: {'setup': 1970, 'currents': 406744, 'spinors': 59020, 'qj': 738432, 'prefixes': 2260992}}
+       5: {'setup': 1970, 'currents': 406744, 'spinors': 59020, 'qj': 738432, 'prefixes': 2260992},
+       6: {'setup': 3610, 'currents': 6076924, 'spinors': 90516, 'qj': 11038464, 'prefixes': 42279168}}
 
 
 def bgm_event(n):
@@ -206,12 +207,13 @@ def bgm_event(n):
 
 def colour_sectors_flops(n):
     """FP64 flops of one row's colour form in symmetry sectors (real and imaginary parts):
-    three stages of butterflies per orbit of eight, and per sector of m orbits the
-    product with its matrix and the dot product."""
-    orbits = {4: 4, 5: 16}[n]
-    fixed = 2 if n in (4, 5) else 0          # orbits of half length: absent from half of the sectors
-    dims = [orbits] * 4 + [orbits - fixed] * 4
-    return 2 * (24 * orbits + sum(2 * m * m + 2 * m for m in dims))
+    butterflies over the members of each orbit (eight; sixteen for six gluons), and per
+    sector of m orbits the product with its matrix and the dot product."""
+    orbits, stages, fixed = {4: (4, 3, 2), 5: (16, 3, 2), 6: (48, 4, 6)}[n]
+    half = 2 ** (stages - 1)
+    # orbits of half length (fixed of them) are absent from half of the sectors
+    dims = [orbits] * half + [orbits - fixed] * half
+    return 2 * (stages * 2 * half * orbits + sum(2 * m * m + 2 * m for m in dims))
 
 
 def diagram_kernel(name, executor, bg_variant=0):
@@ -223,15 +225,15 @@ def diagram_kernel(name, executor, bg_variant=0):
     colour form is a kernel of its own; with helicity recycling (launch variant 3)
     the kernel's flops per event divided by the 2^npar helicity rows (every helicity
     of these processes is good), and with the FP64 colour form fused into it
-    (variants 4 and 5) the triangular colour form of each row on top (algorithmic
-    count; the matrix cores execute the block-triangular product)."""
+    (variants 4 and 5, six gluons in any) the colour form of each row in symmetry
+    sectors on top."""
     if executor == 2:
         return group_sums_flops(name) + QUARK_BRANCH_MEAN
     if executor == 3:
         from .gen import codegen
         npar = codegen.PROCESS_NPAR[name]
         # per event over every helicity, shared out over the 2^npar rows
-        if bg_variant in (4, 5):
+        if bg_variant in (4, 5) or npar == 8:
             n = npar - 2
             return (bgm_event(n)['total'] + 2 * QUARK_BRANCH_MEAN
                     + 2 ** (n + 1) * colour_sectors_flops(n)) / 2 ** npar

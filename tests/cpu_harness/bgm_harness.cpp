@@ -10,7 +10,7 @@ template <int N>
 void bgm_eval(const double* mom, int nevt, double g, double mt, double* jamps) {
   using namespace me;
   using S = BgmShape<N>;
-  const std::vector<uint32_t> t = BgmBuilder<N>().build();
+  const std::vector<uint32_t>& t = bgm_items<N>();
   std::vector<cx16> frame((S::FRAME + 1) / 2), slot(S::SLOT / 2);
   double* F = &frame[0].r;
   double* jt = &slot[0].r;
@@ -38,23 +38,34 @@ void bgm_eval(const double* mom, int nevt, double g, double mt, double* jamps) {
       bgm_row2_item<N>(F, t.data(), mt, i >> 1, i & 1);
       if (S::TWO) bgm_col2_item<N>(F, t.data(), mt, i >> 1, i & 1);
     }
-    if (N == 5)
+    if (N >= 5)
       for (int i = 0; i < S::CV(4); ++i) {
         bgm_current<N, 4>(F, BgmRec<S::F4>(t.data() + S::T4, S::CV(4), i), j);
         bgm_store<N>(F, S::cslot(4) + i, j);
       }
-    for (int i = 0; i < S::NCAN * S::NGH; ++i) bgm_qj_item<N>(F, t.data(), i);
+    cx16* j5 = &slot[S::XJOFF / 2];
+    cx16* qj = S::BIG ? &slot[S::XQOFF / 2] : &frame[S::QJOFF / 2];
+    if constexpr (S::BIG)
+      for (int i = 0; i < S::CV(5); ++i) {
+        bgm_current5<N>(F, BgmRec<S::F5>(t.data() + S::T5, S::CV(5), i), j);
+        for (int c = 0; c < 4; ++c) j5[c * S::CV(5) + i] = cx16{j[c].r, j[c].i};
+      }
+    for (int i = 0; i < S::NCAN * S::NGH; ++i) bgm_qj_item<N>(F, t.data(), j5, qj, i);
     BgmEnds ends;
     bgm_ends<N>(F, ends);
-    for (int i = 0; i < S::VP2; ++i) {
-      BgmPrefix<N, 2> p;
-      p.read(t.data(), i);
-      bgm_prefix_item<N, S::NROW, 2>(F, p, ends, jt, BghNoNote());
-    }
-    for (int i = S::VP2; i < S::VP; ++i) {
-      BgmPrefix<N, 1> p;
-      p.read(t.data(), i);
-      bgm_prefix_item<N, S::NROW, 1>(F, p, ends, jt, BghNoNote());
+    if constexpr (S::BIG) {
+      for (int i = 0; i < S::VP; ++i) bgm_prefix6_item<S::NROW>(F, t.data(), ends, mt, j5, qj, jt, i);
+    } else {
+      for (int i = 0; i < S::VP2; ++i) {
+        BgmPrefix<N, 2> p;
+        p.read(t.data(), i);
+        bgm_prefix_item<N, S::NROW, 2>(F, p, ends, jt, BghNoNote());
+      }
+      for (int i = S::VP2; i < S::VP; ++i) {
+        BgmPrefix<N, 1> p;
+        p.read(t.data(), i);
+        bgm_prefix_item<N, S::NROW, 1>(F, p, ends, jt, BghNoNote());
+      }
     }
     for (int r = 0; r < S::NROW; ++r)
       for (int c = 0; c < 2 * S::NCOL; ++c)
@@ -63,8 +74,9 @@ void bgm_eval(const double* mom, int nevt, double g, double mt, double* jamps) {
 }
 
 extern "C" int harness_bgm_words(int n) {
-  return n == 4 ? (int)me::BgmBuilder<4>().build().size() - me::BgmShape<4>::TWORDS
-                : (int)me::BgmBuilder<5>().build().size() - me::BgmShape<5>::TWORDS;
+  return n == 4   ? (int)me::bgm_items<4>().size() - me::BgmShape<4>::TWORDS
+         : n == 5 ? (int)me::bgm_items<5>().size() - me::BgmShape<5>::TWORDS
+                  : (int)me::bgm_items<6>().size() - me::BgmShape<6>::TWORDS;
 }
 
 // orbits (norb x 2^nsym columns) and sectors of the colour form; returns norb
@@ -77,10 +89,12 @@ extern "C" int harness_bgm_sectors(int n, const int* cf, int* orb, double* sec) 
 
 // jamps [nevt][NROW][n!][2]; hel[NROW] = helicity index of each row
 extern "C" int harness_bgm_eval(int n, const double* mom, int nevt, double g, double mt, double* jamps, int* hel) {
-  for (int r = 0; r < (2 << n); ++r) hel[r] = n == 4 ? me::bgm_helicity<4>(r) : me::bgm_helicity<5>(r);
+  for (int r = 0; r < (2 << n); ++r)
+    hel[r] = n == 4 ? me::bgm_helicity<4>(r) : n == 5 ? me::bgm_helicity<5>(r) : me::bgm_helicity<6>(r);
   switch (n) {
     case 4: bgm_eval<4>(mom, nevt, g, mt, jamps); return 0;
     case 5: bgm_eval<5>(mom, nevt, g, mt, jamps); return 0;
+    case 6: bgm_eval<6>(mom, nevt, g, mt, jamps); return 0;
     default: return -1;
   }
 }

@@ -47,7 +47,7 @@ template <int N>
 void count_event(const double* mom, long long* out) {
   using namespace me;
   using S = BgmShape<N>;
-  const std::vector<uint32_t> t = BgmBuilder<N>().build();
+  const std::vector<uint32_t>& t = bgm_items<N>();
   std::vector<cx16> frame((S::FRAME + 1) / 2), slot(S::SLOT / 2);
   CD* F = &frame[0].r;
   CD* jt = &slot[0].r;
@@ -74,10 +74,17 @@ void count_event(const double* mom, long long* out) {
     bgm_current<N, 3>(F, BgmRec<S::F3>(t.data() + S::T3, S::SV(3), i), j);
     bgm_store<N>(F, S::cslot(3) + i, j);
   }
-  if (N == 5)
+  if (N >= 5)
     for (int i = 0; i < S::CV(4); ++i) {
       bgm_current<N, 4>(F, BgmRec<S::F4>(t.data() + S::T4, S::CV(4), i), j);
       bgm_store<N>(F, S::cslot(4) + i, j);
+    }
+  cx16* j5 = &slot[S::XJOFF / 2];
+  cx16* qj = S::BIG ? &slot[S::XQOFF / 2] : &frame[S::QJOFF / 2];
+  if constexpr (S::BIG)
+    for (int i = 0; i < S::CV(5); ++i) {
+      bgm_current5<N>(F, BgmRec<S::F5>(t.data() + S::T5, S::CV(5), i), j);
+      for (int c = 0; c < 4; ++c) j5[c * S::CV(5) + i] = cx16{j[c].r, j[c].i};
     }
   lap(1);
   for (int i = 0; i < 2 * S::V(1); ++i) {
@@ -89,19 +96,23 @@ void count_event(const double* mom, long long* out) {
     if (S::TWO) bgm_col2_item<N>(F, t.data(), mt, i >> 1, i & 1);
   }
   lap(2);
-  for (int i = 0; i < S::NCAN * S::NGH; ++i) bgm_qj_item<N>(F, t.data(), i);
+  for (int i = 0; i < S::NCAN * S::NGH; ++i) bgm_qj_item<N>(F, t.data(), j5, qj, i);
   lap(3);
   BgmEnds ends;
   bgm_ends<N>(F, ends);
-  for (int i = 0; i < S::VP2; ++i) {
-    BgmPrefix<N, 2> p;
-    p.read(t.data(), i);
-    bgm_prefix_item<N, S::NROW, 2>(F, p, ends, jt, BghNoNote());
-  }
-  for (int i = S::VP2; i < S::VP; ++i) {
-    BgmPrefix<N, 1> p;
-    p.read(t.data(), i);
-    bgm_prefix_item<N, S::NROW, 1>(F, p, ends, jt, BghNoNote());
+  if constexpr (S::BIG) {
+    for (int i = 0; i < S::VP; ++i) bgm_prefix6_item<S::NROW>(F, t.data(), ends, mt, j5, qj, jt, i);
+  } else {
+    for (int i = 0; i < S::VP2; ++i) {
+      BgmPrefix<N, 2> p;
+      p.read(t.data(), i);
+      bgm_prefix_item<N, S::NROW, 2>(F, p, ends, jt, BghNoNote());
+    }
+    for (int i = S::VP2; i < S::VP; ++i) {
+      BgmPrefix<N, 1> p;
+      p.read(t.data(), i);
+      bgm_prefix_item<N, S::NROW, 1>(F, p, ends, jt, BghNoNote());
+    }
   }
   lap(4);
 }
@@ -110,6 +121,7 @@ extern "C" int count_bgm_event(int n, const double* mom, long long* out) {
   switch (n) {
     case 4: count_event<4>(mom, out); return 0;
     case 5: count_event<5>(mom, out); return 0;
+    case 6: count_event<6>(mom, out); return 0;
     default: return -1;
   }
 }

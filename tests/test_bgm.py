@@ -32,6 +32,20 @@ def test_amplitudes_flow_by_flow(n, nevt):
     assert np.max(np.minimum(plus, minus)) < 1e-12
 
 
+def test_amplitudes_of_six_gluons():
+    """A row of each quark helicity pair against the one-row recursion (1e-12 of the
+    largest amplitude: each rounds some thousand operations)."""
+    assert bgm_build.table_words_off(6) == 0
+    mom = rambo.generate(8, 2, 8)
+    g = math.sqrt(4 * math.pi * AS)
+    two, hel = bgm_build.jamps(6, mom, g, 173.0)
+    assert sorted(list(hel) + [255 - h for h in hel]) == list(range(256))
+    rows = [0, 31, 37, 64 - 1, 64 + 5, 127]
+    one = harness.build_bg().jamps(6, mom, g, 173.0, [int(h) for h in hel[rows]]).transpose(1, 0, 2)
+    scale = np.abs(two).max(axis=(1, 2), keepdims=True)
+    assert np.max(np.abs(two[:, rows] - one) / scale) < 1e-12
+
+
 @pytest.mark.parametrize('n', [4, 5, 6])
 def test_colour_sectors(n):
     """The sum over sectors is the quadratic form of the colour matrix (sums of n!^2
@@ -49,7 +63,7 @@ def test_colour_sectors(n):
     assert np.max(np.abs(form / np.einsum('ex,xy,ey->e', a, cf, a) - 1)) < 1e-12
 
 
-@pytest.mark.parametrize('n', [4, 5])
+@pytest.mark.parametrize('n', [4, 5, 6])
 def test_flops_equal_the_counted_operations(n):
     """flops.bgm_event equals the operations of the device functions for one event,
     counted with the operation-counting scalar, phase by phase (a quark with pz < 0

@@ -60,3 +60,25 @@ def test_running_coupling(binding, name, npar):
         _handle(binding, name, v).me_compute_alphas(mom, nevt, alphas, out)
         outs.append(out.cpu().numpy())
     assert np.max(np.abs(outs[1] / outs[0] - 1)) < BOUND[0]
+
+
+@pytest.mark.parametrize('nevt', [1, 257, 2305])
+def test_six_gluons(binding, nevt):
+    """Six gluons, FP64: sampled events against the team program (whose operations are
+    others: the bound of the recursions above), an event's result the same in any place
+    of the batch (one event, one more than the compute units hold, more than a launch),
+    and running coupling |M|^2 ~ alpha_s^6."""
+    _say(f'case two-sided gg_ttxgggg nevt={nevt}')
+    mom = torch.from_numpy(rambo.generate(8, nevt, 93)).cuda()
+    m = binding.MatrixElement('gg_ttxgggg')
+    m.me_set_executor(binding.ME_EXEC_BG)
+    got = m.compute(mom, AS).cpu().numpy()
+    pick = sorted({0, nevt // 2, nevt - 1})
+    ref = binding.MatrixElement('gg_ttxgggg').compute(mom[pick].contiguous(), AS).cpu().numpy()
+    assert np.max(np.abs(got[pick] / ref - 1)) < BOUND[0]
+    back = m.compute(mom.flip(0).contiguous(), AS).cpu().numpy()
+    assert np.array_equal(got, back[::-1])
+    alphas = torch.linspace(0.08, 0.2, nevt, dtype=torch.float64, device='cuda')
+    out = torch.empty(nevt, dtype=torch.float64, device='cuda')
+    m.me_compute_alphas(mom, nevt, alphas, out)
+    assert np.max(np.abs(out.cpu().numpy() / (got * (alphas.cpu().numpy() / AS) ** 6) - 1)) < BOUND[0]
