@@ -1515,6 +1515,37 @@ int me_compute_alphas(me_handle h, const double* momenta, int64_t nevt, const do
   return enqueue(h, momenta, nevt, 0.118, out_me2, (hipStream_t)stream, alpha_s);
 }
 
+static int select_two_sided(me_ctx* h, const double* momenta, int64_t nevt, double alpha_s, const double* r_hel,
+                            const double* r_col, double* out_me2, int32_t* sel_hel, int32_t* sel_col,
+                            hipStream_t s) {
+  int rc = ensure_bg_tables(h);
+  if (rc) return rc;
+  const int ev = h->bg->fused_block_events();
+  const int64_t slot = h->bg->fused_slot_doubles();
+  const int64_t most = (int64_t)(ME_BG_FUSED_SCRATCH_BYTES / (sizeof(double) * (uint64_t)slot));
+  const int64_t blocks = std::min<int64_t>(most, (nevt + ev - 1) / ev);
+  rc = ensure_sums(h, (size_t)blocks * (size_t)slot);
+  if (rc) return rc;
+  for (int64_t off = 0; off < nevt; off += blocks * ev) {
+    me::BgArgs a{momenta + off * h->desc->npar * 4, std::min<int64_t>(blocks * ev, nevt - off), coupling(alpha_s),
+                 h->params.mt, h->d_hels, (int)h->good.size(), h->d_bg_sub, h->d_bg_mask, h->d_bg_last, nullptr,
+                 h->d_sums, s};
+    a.bgm = h->d_bgm;
+    a.orb = h->d_bgm_orb;
+    a.sec = h->d_bgm_sec;
+    a.r_hel = r_hel + off;
+    a.r_col = r_col + off;
+    a.sel_hel = (int*)sel_hel + off;
+    a.sel_col = (int*)sel_col + off;
+    a.out = out_me2 + off;
+    a.out_scale = 1.0 / ((double)h->desc->iden * (double)h->desc->cf_den);
+    a.grid = (int)blocks;
+    hipError_t e = h->bg->launch(a);
+    if (e != hipSuccess) return hip_fail(e, "selection kernel launch");
+  }
+  return ME_OK;
+}
+
 int me_select(me_handle h, const double* momenta, int64_t nevt, double alpha_s, const double* r_hel,
               const double* r_col, double* out_me2, int32_t* sel_hel, int32_t* sel_col, void* stream) {
   int rc = check_handle(h);
@@ -1534,6 +1565,9 @@ int me_select(me_handle h, const double* momenta, int64_t nevt, double alpha_s, 
   const int nhel = (int)h->good.size();
   const int ncol = h->desc->ncol;
   const int npar = h->desc->npar;
+  // four and five gluons: recursion, forms and both draws of an event in one kernel
+  if (h->bg->recycle && nhel > 0)
+    return select_two_sided(h, momenta, nevt, alpha_s, r_hel, r_col, out_me2, sel_hel, sel_col, s);
   // scratch: per-helicity sums [nhel][nevt], later the flow weights of an event
   // chunk [ncol][chunk]; the dual amplitudes of an event chunk [chunk][ncol][2]
   const size_t row_doubles = (size_t)ncol * 2;

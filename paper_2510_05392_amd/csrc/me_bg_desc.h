@@ -45,6 +45,11 @@ struct BgArgs {
   int fmt = -1;                  // colour form: -1 FP64, 0 split FP16, 1 split BF16 (CS_FMT_*)
   const void* cf_hi = nullptr;   // split formats: colour-matrix tables [32 MB][16 KS] (lo may be null)
   const void* cf_lo = nullptr;
+  // selection (four and five gluons; out is given): random numbers and draws per event
+  const double* r_hel = nullptr;
+  const double* r_col = nullptr;
+  int* sel_hel = nullptr;
+  int* sel_col = nullptr;
   double* out = nullptr;         // per-event |M|^2 [n] (nullptr: variant 4 runs as 3)
   double out_scale = 1.0;        // 1 / (IDEN x colour denominator)
   int grid = 0;                  // workgroups (= scratch slots)

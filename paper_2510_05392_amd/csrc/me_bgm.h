@@ -963,18 +963,18 @@ __device__ __forceinline__ void bgm_butterfly(double* x) {
       }
 }
 
-// Five gluons: sum over the 64 rows of weight x form, by every wave of the workgroup.
-// A wave takes 16 rows: their real and then their imaginary parts are the columns of
+// Five gluons: the forms of the 64 rows, by every wave of the workgroup.  Four lanes of
+// a wave (l % 16 equal) hold shares of a row's form; each hands its own to take(row,
+// share), all lanes at the same time.  A wave takes 16 rows: their real and then their imaginary parts are the columns of
 // v_mfma_f64_16x16x4f64, a sector's matrix its A operand (lane l: row l % 16, K index
 // l / 16), the orbits the K index.  A lane's four orbits o = 4 q + l / 16 are those of
 // its accumulator rows, so the dots use the operands in hand.  64 products per 16 rows
 // against 288 of the block-triangular form, and no matrix staged in LDS.
-template <int WAVES>
-__device__ __forceinline__ double bgm_colour5(const double* __restrict__ jt, const uint16_t* __restrict__ orb,
-                                              const float* __restrict__ sec, const int* weight) {
+template <int WAVES, typename Take>
+__device__ __forceinline__ void bgm_colour5(const double* __restrict__ jt, const uint16_t* __restrict__ orb,
+                                            const float* __restrict__ sec, Take take) {
   constexpr int RS = BgmShape<5>::NROW;
   const int l = threadIdx.x & 63, j = l & 15, kq = l >> 4;
-  double sum = 0.0;
   for (int grp = threadIdx.x >> 6; grp < RS / 16; grp += WAVES) {
     const int row = 16 * grp + j;
     const double* x = jt + row;
@@ -1006,16 +1006,15 @@ __device__ __forceinline__ double bgm_colour5(const double* __restrict__ jt, con
 #pragma unroll
         for (int q = 0; q < 4; ++q) f += a[p][q][s] * acc[p][q];
     }
-    sum += weight[row] ? (double)weight[row] * f : 0.0;
+    take(row, f);
   }
-  return sum;
 }
 
 // Four gluons: the 32 rows x two parts of an event are the lanes of its wave; the
 // sectors (4 x 4, upper triangle with the elements above the diagonal doubled) are
-// uniform.
+// uniform.  Returns lane l's part of the form of row l % 32.
 __device__ __forceinline__ double bgm_colour4(const double* __restrict__ je, const uint16_t* __restrict__ orb,
-                                              const float* __restrict__ sec, const int* weight) {
+                                              const float* __restrict__ sec) {
   using S = BgmShape<4>;
   constexpr int RS = BgmLaunchShape<4>::EV * S::NROW;
   const int l = threadIdx.x & 63, row = l & 31;
@@ -1037,7 +1036,7 @@ __device__ __forceinline__ double bgm_colour4(const double* __restrict__ je, con
       for (int k = i + 1; k < 4; ++k) t += (double)sec[(s * 4 + i) * 4 + k] * a[k][s];
       f += a[i][s] * t;
     }
-  return weight[row] ? (double)weight[row] * f : 0.0;
+  return f;
 }
 
 // Records, for each row of an event, the largest |Re| and |Im| of its amplitudes
@@ -1332,13 +1331,17 @@ bgm_fused_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt
       }
     } else if constexpr (N == 4) {
       if (w < nev) {
-        const double v = bgm_wave_sum(bgm_colour4(slot + w * S::NROW, orb, sec, weight));
+        const double f = bgm_colour4(slot + w * S::NROW, orb, sec);
+        const int k = weight[l & 31];
+        const double v = bgm_wave_sum(k ? (double)k * f : 0.0);
         if (l == 0) out[e0 + w] = scale * v;
       }
     } else {
-      double v;
-      if constexpr (N == 5) v = bgm_colour5<WAVES>(slot, orb, sec, weight);
-      else v = bgm_colour6<WAVES>(bgm_lds, slot, orb, sec, weight);
+      double v = 0.0;
+      if constexpr (N == 5)
+        bgm_colour5<WAVES>(slot, orb, sec, [&](int row, double f) { v += weight[row] ? (double)weight[row] * f : 0.0; });
+      else
+        v = bgm_colour6<WAVES>(bgm_lds, slot, orb, sec, weight);
       v = bgm_wave_sum(v);
       if (l == 0) part[w] = v;
       __syncthreads();
@@ -1351,6 +1354,96 @@ bgm_fused_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt
     __builtin_amdgcn_s_setprio(0);
     // the frames, the staged matrix and the slot are reused by the next block
     if constexpr (PERSIST) __syncthreads();
+  }
+}
+
+// Inverse-CDF draw by one wave over the non-negative weights weight(k), k = 0 .. n - 1 <=
+// 64 K, lane l holding K consecutive ones: the first k whose running sum exceeds r times
+// the total, or the last with a positive weight.
+template <int K, typename Weight>
+__device__ __forceinline__ int bgm_draw(int n, double r, Weight weight, double* total) {
+  const int l = threadIdx.x & 63;
+  double v[K], s = 0.0;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    v[i] = l * K + i < n ? weight(l * K + i) : 0.0;
+    s += v[i];
+  }
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const double y = __shfl_up(s, d);
+    if (l >= d) s += y;
+  }
+  *total = __shfl(s, 63);
+  double cum = __shfl_up(s, 1);
+  if (l == 0) cum = 0.0;
+  const double t = r * *total;
+  int pick = -1, last = -1;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    cum += v[i];
+    if (v[i] > 0.0) last = l * K + i;
+    if (pick < 0 && l * K + i < n && t < cum) pick = l * K + i;
+  }
+  const unsigned long long hit = __ballot(pick >= 0), pos = __ballot(last >= 0);
+  if (hit) return __shfl(pick, __ffsll((long long)hit) - 1);
+  return pos ? __shfl(last, 63 - __clzll((long long)pos)) : 0;
+}
+
+// Selection: as the FP64 fused kernel, but each row's form is kept, and the event's wave
+// (five gluons: wave 0) draws a helicity with the forms of the good ones (a row's form is
+// that of both helicities of its mirror pair) and a flow with the |J_c|^2 of its row,
+// read back from the slot.  The row's amplitudes are there already: the one-lane route
+// formed every flow of every helicity from its diagrams and then those of the drawn one
+// once more.  16384 g g -> t t~ g g g on an MI355X: 1.88 ms, 106.7 by that route.
+template <int N>
+__global__ void __launch_bounds__(64 * BgmLaunchShape<N>::EV * BgmLaunchShape<N>::WPE)
+    __attribute__((amdgpu_waves_per_eu(BgmLaunchShape<N>::W)))
+bgm_select_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt, const int* __restrict__ hels,
+                  int nhel, const uint32_t* __restrict__ tabs, const uint16_t* __restrict__ orb,
+                  const float* __restrict__ sec, double* __restrict__ jt, const double* __restrict__ r_hel,
+                  const double* __restrict__ r_col, double* __restrict__ out, int* __restrict__ sel_hel,
+                  int* __restrict__ sel_col, double scale) {
+  using S = BgmShape<N>;
+  using B = BgmLaunchShape<N>;
+  constexpr int EV = B::EV, WAVES = EV * B::WPE, RS = EV * S::NROW;
+  extern __shared__ __attribute__((aligned(16))) double bgm_lds[];
+  __shared__ double form[RS];
+  const int64_t e0 = (int64_t)blockIdx.x * EV;
+  const int nev = (int)(n - e0 < EV ? n - e0 : EV);
+  double* slot = jt + e0 * S::SLOT;
+  bgm_events<N>(bgm_lds, tabs, mom + e0 * (N + 2) * 4, nullptr, nev, g0, mt, slot, BghNoNote());
+  __syncthreads();   // every amplitude of the block is stored
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  if constexpr (N == 4) {
+    if (w < nev) {
+      double f = bgm_colour4(slot + w * S::NROW, orb, sec);
+      f += __shfl_xor(f, 32);   // real and imaginary parts
+      if (l < 32) form[w * S::NROW + l] = f;
+    }
+  } else {
+    bgm_colour5<WAVES>(slot, orb, sec, [&](int row, double f) {
+      f += __shfl_xor(f, 32);
+      f += __shfl_xor(f, 16);
+      if (l < 16) form[row] = f;
+    });
+  }
+  __syncthreads();
+  if (w >= nev) return;
+  const double* fe = form + w * S::NROW;
+  double total;
+  const int k = bgm_draw<(4 << N) / 64>(nhel, r_hel[e0 + w], [&](int i) { return fe[bgm_row<N>(hels[i])]; }, &total);
+  const int h = hels[k];
+  const double* x = slot + w * S::NROW + bgm_row<N>(h);
+  double flows;
+  const int c = bgm_draw<(S::NCOL + 63) / 64>(S::NCOL, r_col[e0 + w], [&](int i) {
+    const double re = x[(int64_t)(2 * i) * RS], im = x[(int64_t)(2 * i + 1) * RS];
+    return re * re + im * im;
+  }, &flows);
+  if (l == 0) {
+    out[e0 + w] = scale * total;
+    sel_hel[e0 + w] = h;
+    sel_col[e0 + w] = c;
   }
 }
 
@@ -1433,6 +1526,23 @@ hipError_t launch_bgm_fused_fmt(const BgArgs& a) {
   return hipGetLastError();
 }
 
+template <int N>
+hipError_t launch_bgm_select(const BgArgs& a) {
+  constexpr int EV = BgmLaunchShape<N>::EV;
+  constexpr size_t lds = bgm_lds_bytes<N>();
+  static const hipError_t attr = hipFuncSetAttribute((const void*)bgm_select_kernel<N>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (attr != hipSuccess) return attr;
+  const int64_t blocks = (a.n + EV - 1) / EV;
+  if (!a.bgm || !a.orb || !a.sec || !a.out || !a.r_hel || !a.r_col || !a.sel_col || a.nhel < 1 ||
+      a.nhel > (4 << N) || blocks > a.grid)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(bgm_select_kernel<N>, dim3((unsigned)blocks), dim3(bgm_threads<N>()), lds, a.stream, a.mom, a.n,
+                     a.g, a.mt, a.hels, a.nhel, a.bgm, a.orb, a.sec, a.jt, a.r_hel, a.r_col, a.out, a.sel_hel,
+                     a.sel_col, a.out_scale);
+  return hipGetLastError();
+}
+
 template <int N, bool PERSIST>
 hipError_t launch_bgm_fused_p(const BgArgs& a) {
   if (a.fmt == CS_FMT_FP16) return launch_bgm_fused_fmt<N, CS_FMT_FP16, PERSIST>(a);
@@ -1446,6 +1556,7 @@ hipError_t launch_bgm_fused_p(const BgArgs& a) {
 template <int N>
 hipError_t launch_bg(const BgArgs& a) {
   if constexpr (N == 4 || N == 5) {
+    if (a.sel_hel) return launch_bgm_select<N>(a);
     if ((a.variant == 4 || a.variant == 5) && a.out)
       return a.variant == 5 ? launch_bgm_fused_p<N, true>(a) : launch_bgm_fused_p<N, false>(a);
     if (a.variant >= 3) return launch_bgh<N>(a);

@@ -82,3 +82,41 @@ def test_six_gluons(binding, nevt):
     out = torch.empty(nevt, dtype=torch.float64, device='cuda')
     m.me_compute_alphas(mom, nevt, alphas, out)
     assert np.max(np.abs(out.cpu().numpy() / (got * (alphas.cpu().numpy() / AS) ** 6) - 1)) < BOUND[0]
+
+
+@pytest.mark.parametrize('name,npar,nevt', [('gg_ttxgg', 6, 1), ('gg_ttxgg', 6, 67), ('gg_ttxggg', 7, 1),
+                                            ('gg_ttxggg', 7, 41)])
+def test_selection_against_the_one_lane_sums(binding, name, npar, nevt):
+    """Both draws of every event against the draws from the one-lane program's helicity
+    sums and dual amplitudes, except where r * total is within 1e-9 of a running sum
+    (there rounding decides): any r in [0, 1), with its ends."""
+    _say(f'case selection {name} nevt={nevt}')
+    mom = torch.from_numpy(rambo.generate(npar, nevt, 94)).cuda()
+    rng = np.random.default_rng(nevt)
+    rh, rc = rng.random(nevt), rng.random(nevt)
+    rh[0], rc[-1] = 0.0, 1.0 - 2.0 ** -53
+    m = binding.MatrixElement(name)
+    out = torch.empty(nevt, dtype=torch.float64, device='cuda')
+    sh, sc = (torch.full((nevt,), -1, dtype=torch.int32, device='cuda') for _ in range(2))
+    m.me_select(mom, nevt, AS, torch.from_numpy(rh).cuda(), torch.from_numpy(rc).cuda(), out, sh, sc)
+    good = m.me_good_helicities()
+    sums = torch.empty((len(good), nevt), dtype=torch.float64, device='cuda')
+    m.me_helicity_sums(mom, nevt, AS, good, sums)
+    jam = torch.empty((len(good), nevt, m.ncolor, 2), dtype=torch.float64, device='cuda')
+    m.me_jamps(mom, nevt, AS, good, jam)
+    me2 = m.compute(mom, AS).cpu().numpy()
+    assert np.max(np.abs(out.cpu().numpy() / me2 - 1)) < BOUND[0]
+    sums, flows = sums.cpu().numpy(), (jam ** 2).sum(-1).cpu().numpy()
+    sh, sc = sh.cpu().numpy(), sc.cpu().numpy()
+
+    def check(w, r, pick):
+        cum = np.cumsum(w)
+        t = r * cum[-1]
+        first = np.nonzero(cum > t)[0]
+        want = first[0] if len(first) else np.nonzero(w > 0)[0][-1]
+        assert pick == want or np.abs(cum - t).min() <= 1e-9 * cum[-1], (pick, want)
+
+    for e in range(nevt):
+        k = list(good).index(sh[e])
+        check(sums[:, e], rh[e], k)
+        check(flows[k, e], rc[e], sc[e])
