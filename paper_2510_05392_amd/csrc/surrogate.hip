@@ -821,46 +821,68 @@ __global__ void copy_col_kernel(const float* __restrict__ z, int64_t ld, int64_t
 
 // --- unweighting ------------------------------------------------------------
 
-// stage 1: keep[i] = r[i] < min(1, w_hat_i / what_max), w_hat = exp(y*ystd + ymean) * wps
-__global__ void stage1_kernel(const float* __restrict__ y, const double* __restrict__ wps,
-                              const double* __restrict__ r, int64_t n, double ymean, double ystd,
-                              double what_max, double* __restrict__ what, int* __restrict__ keep) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double wh = exp((double)y[i] * ystd + ymean) * wps[i];
-  what[i] = wh;
-  keep[i] = r[i] < fmin(1.0, wh / what_max) ? 1 : 0;
+// stage 1: event i is kept when r[i] < min(1, w_hat_i / what_max), w_hat = exp(y*ystd +
+// ymean) * wps.  Three launches with nothing read back between them: the weights and the
+// kept events of each block of 256, their exclusive sums, the ordered indices (which
+// decide again, from the stored weight: the same comparison).
+__device__ __forceinline__ bool stage1_kept(double wh, double r, double what_max) {
+  return r < fmin(1.0, wh / what_max);
+}
+__global__ void __launch_bounds__(256) stage1_kernel(const float* __restrict__ y, const double* __restrict__ wps,
+                                                     const double* __restrict__ r, int64_t n, double ymean,
+                                                     double ystd, double what_max, double* __restrict__ what,
+                                                     int64_t* __restrict__ counts) {
+  __shared__ int waves[4];
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  bool keep = false;
+  if (i < n) {
+    const double wh = exp((double)y[i] * ystd + ymean) * wps[i];
+    what[i] = wh;
+    keep = stage1_kept(wh, r[i], what_max);
+  }
+  const unsigned long long m = __ballot(keep);
+  if ((threadIdx.x & 63) == 0) waves[threadIdx.x >> 6] = __popcll(m);
+  __syncthreads();
+  if (threadIdx.x == 0) counts[blockIdx.x] = waves[0] + waves[1] + waves[2] + waves[3];
 }
 
-// per-block counts of kept entries (blocks of 256)
-__global__ void count_kernel(const int* __restrict__ keep, int64_t n, int* __restrict__ counts) {
-  __shared__ int red[256];
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  red[threadIdx.x] = (i < n) ? keep[i] : 0;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+// counts[n] to their exclusive sums in place, the total to counts[n], by one workgroup
+__global__ void __launch_bounds__(1024) scan_kernel(int64_t* __restrict__ counts, int64_t n) {
+  __shared__ int64_t pre[1024];
+  int64_t base = 0;
+  for (int64_t b = 0; b < n; b += 1024) {
+    const int64_t i = b + threadIdx.x;
+    const int64_t v = i < n ? counts[i] : 0;
+    pre[threadIdx.x] = v;
+    __syncthreads();
+    for (int d = 1; d < 1024; d <<= 1) {
+      const int64_t add = (int)threadIdx.x >= d ? pre[threadIdx.x - d] : 0;
+      __syncthreads();
+      pre[threadIdx.x] += add;
+      __syncthreads();
+    }
+    if (i < n) counts[i] = base + pre[threadIdx.x] - v;
+    base += pre[1023];
     __syncthreads();
   }
-  if (threadIdx.x == 0) counts[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) counts[n] = base;
 }
 
-// ordered scatter of kept indices: block offsets from an exclusive scan of counts
-__global__ void scatter_kernel(const int* __restrict__ keep, int64_t n, const int64_t* __restrict__ offs,
-                               int64_t* __restrict__ idx) {
-  __shared__ int pre[256];
+// ordered indices of the kept events, from the exclusive sums of the blocks' counts
+__global__ void __launch_bounds__(256) scatter_kernel(const double* __restrict__ what, const double* __restrict__ r,
+                                                      int64_t n, double what_max, const int64_t* __restrict__ offs,
+                                                      int64_t* __restrict__ idx) {
+  __shared__ int waves[4];
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int k = (i < n) ? keep[i] : 0;
-  pre[threadIdx.x] = k;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const bool keep = i < n && stage1_kept(what[i], r[i], what_max);
+  const unsigned long long m = __ballot(keep);
+  if (l == 0) waves[w] = __popcll(m);
   __syncthreads();
-  // inclusive scan (Hillis-Steele) within the block
-  for (int d = 1; d < 256; d <<= 1) {
-    const int add = (int)threadIdx.x >= d ? pre[threadIdx.x - d] : 0;
-    __syncthreads();
-    pre[threadIdx.x] += add;
-    __syncthreads();
-  }
-  if (k) idx[offs[blockIdx.x] + pre[threadIdx.x] - 1] = i;
+  if (!keep) return;
+  int64_t k = offs[blockIdx.x] + __popcll(m & ((1ull << l) - 1));
+  for (int v = 0; v < w; ++v) k += waves[v];
+  idx[k] = i;
 }
 
 __global__ void gather_kernel(const double* __restrict__ mom, const int64_t* __restrict__ idx, int64_t m,
@@ -974,50 +996,159 @@ __global__ void gather_rows_kernel(const uint16_t* __restrict__ feat, const floa
   if (c == 0) to[r] = t[src];
 }
 
-// surrogate weight w_hat = exp(y ystd + ymean) wps and ratio x = me2 wps / w_hat
+// surrogate weight w_hat = exp(y ystd + ymean) wps and ratio x = me2 wps / w_hat; clears
+// the nclear words of the selection's counters
 __global__ void weights_kernel(const float* __restrict__ y, const double* __restrict__ wps,
                                const double* __restrict__ me2, int64_t n, double ymean, double ystd,
-                               double* __restrict__ what, double* __restrict__ x) {
+                               double* __restrict__ what, double* __restrict__ x,
+                               unsigned long long* __restrict__ clear, int nclear) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t k = i; k < nclear; k += (int64_t)gridDim.x * blockDim.x) clear[k] = 0ull;
   if (i >= n) return;
   const double wh = exp((double)y[i] * ystd + ymean) * wps[i];
   what[i] = wh;
   x[i] = me2[i] * wps[i] / wh;
 }
 
-// per-block maxima of v[n]
+// per-block maxima of v[n] (blockIdx.y: of several arrays one after the other)
 __global__ void __launch_bounds__(256) max_kernel(const double* __restrict__ v, int64_t n, double* __restrict__ part) {
   __shared__ double red[256];
   double m = -INFINITY;
+  v += blockIdx.y * n;
   for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < n; r += (int64_t)gridDim.x * 256) m = fmax(m, v[r]);
   m = block_max(m, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = m;
+  if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = m;
 }
 
-// Radix selection over the bit patterns of non-negative doubles (ordered like
-// the values): counts[b] = number of entries whose bits agree with `prefix` on
-// the bits of `mask` and whose next byte (at `shift`) is b.  Integer atomics.
-__global__ void radix_hist_kernel(const double* __restrict__ v, int64_t n, unsigned long long prefix,
-                                  unsigned long long mask, int shift, unsigned long long* __restrict__ counts) {
-  __shared__ unsigned int h[256];
-  h[threadIdx.x] = 0;
+// Radix selection over the bit patterns of non-negative doubles (ordered like the
+// values) of blockIdx.y arrays v[n]: six passes of 11- and 10-bit digits, most
+// significant first, then the neighbour.  Each pass counts the digits of the entries
+// that agree with the digits found so far; the digit of a pass is found from its counts
+// by every workgroup of the next one, so the passes follow each other without the host.
+// Integer atomics.
+constexpr int kSelPasses = 6, kSelBins = 2048;
+struct SelectState {
+  unsigned long long prefix[kSelPasses + 1];   // digits found before pass p
+  unsigned long long rank[kSelPasses + 1];     // rank among the entries that agree with them
+  unsigned long long upto, above;              // entries <= the k-th, smallest bits above it
+};
+// words of one array: the states of all arrays, then the counts of each
+constexpr int kSelState = sizeof(SelectState) / 8, kSelCounts = kSelPasses * kSelBins;
+constexpr int kSelWords = kSelState + kSelCounts;
+__device__ __forceinline__ SelectState* select_state(unsigned long long* words) {
+  return reinterpret_cast<SelectState*>(words + blockIdx.y * kSelState);
+}
+__device__ __forceinline__ unsigned long long* select_counts(unsigned long long* words, int pass) {
+  return words + gridDim.y * kSelState + blockIdx.y * kSelCounts + pass * kSelBins;
+}
+
+__host__ __device__ inline int select_shift(int pass) { return pass < 5 ? 53 - 11 * pass + (pass > 3 ? 1 : 0) : 0; }
+
+// The state before pass p: from that before pass p - 1 and its counts.
+__device__ __forceinline__ void select_next(unsigned long long* words, int p, unsigned long long k0,
+                                            unsigned long long* prefix, unsigned long long* rank) {
+  __shared__ unsigned long long sums[256], found[2];
+  if (p == 0) {
+    *prefix = 0ull;
+    *rank = k0;
+    return;
+  }
+  const SelectState* st = select_state(words);
+  const unsigned long long* c = select_counts(words, p - 1) + 8 * threadIdx.x;
+  const unsigned long long k = p == 1 ? k0 : st->rank[p - 1], before = p == 1 ? 0ull : st->prefix[p - 1];
+  unsigned long long h[8], s = 0;
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    h[b] = c[b];
+    s += h[b];
+  }
+  sums[threadIdx.x] = s;
   __syncthreads();
-  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < n; r += (int64_t)gridDim.x * 256) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v[r]);
-    if ((b & mask) == prefix) atomicAdd(&h[(b >> shift) & 0xff], 1u);
+  for (int d = 1; d < 256; d <<= 1) {
+    const unsigned long long add = (int)threadIdx.x >= d ? sums[threadIdx.x - d] : 0;
+    __syncthreads();
+    sums[threadIdx.x] += add;
+    __syncthreads();
+  }
+  unsigned long long cum = sums[threadIdx.x] - s;
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    if (cum <= k && k < cum + h[b]) {   // one bin of one thread
+      found[0] = 8 * threadIdx.x + b;
+      found[1] = k - cum;
+    }
+    cum += h[b];
   }
   __syncthreads();
-  if (h[threadIdx.x]) atomicAdd(&counts[threadIdx.x], (unsigned long long)h[threadIdx.x]);
+  *prefix = before | found[0] << select_shift(p - 1);
+  *rank = found[1];
 }
 
-__global__ void clear_u64_kernel(unsigned long long* c, int n) {
-  if ((int)threadIdx.x < n) c[threadIdx.x] = 0ull;
+__global__ void __launch_bounds__(256) select_pass_kernel(const double* __restrict__ v, int64_t n,
+                                                          unsigned long long k0, int pass,
+                                                          unsigned long long* __restrict__ words) {
+  __shared__ unsigned int h[kSelBins];
+  v += blockIdx.y * n;
+  unsigned long long prefix, rank;
+  select_next(words, pass, k0, &prefix, &rank);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    SelectState* st = select_state(words);
+    st->prefix[pass] = prefix;
+    st->rank[pass] = rank;
+    if (pass == 0) st->above = ~0ull;
+  }
+  for (int b = threadIdx.x; b < kSelBins; b += 256) h[b] = 0;
+  __syncthreads();
+  const int shift = select_shift(pass);
+  // a pass's digit lies below the bits of the prefix: the first has none above it
+  const unsigned long long mask = pass == 0 ? 0ull : ~0ull << select_shift(pass - 1);
+  const unsigned long long digit = pass < 4 ? 0x7ffull : 0x3ffull;
+  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < n; r += (int64_t)gridDim.x * 256) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v[r]);
+    if ((b & mask) == prefix) atomicAdd(&h[(b >> shift) & digit], 1u);
+  }
+  __syncthreads();
+  unsigned long long* counts = select_counts(words, pass);
+  for (int b = threadIdx.x; b < kSelBins; b += 256)
+    if (h[b]) atomicAdd(&counts[b], (unsigned long long)h[b]);
 }
 
-// exact weights w = me2 wps
+// the k-th entry's bits to prefix[kSelPasses], the number of entries up to it and the
+// smallest bits above it
+__global__ void __launch_bounds__(256) select_last_kernel(const double* __restrict__ v, int64_t n,
+                                                          unsigned long long k0,
+                                                          unsigned long long* __restrict__ words) {
+  __shared__ unsigned long long upto, above;
+  SelectState* st = select_state(words);
+  v += blockIdx.y * n;
+  unsigned long long kth, rank;
+  select_next(words, kSelPasses, k0, &kth, &rank);
+  if (threadIdx.x == 0) {
+    upto = 0ull;
+    above = ~0ull;
+  }
+  __syncthreads();
+  unsigned long long cnt = 0, mn = ~0ull;
+  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < n; r += (int64_t)gridDim.x * 256) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v[r]);
+    if (b <= kth) ++cnt;
+    else if (b < mn) mn = b;
+  }
+  if (cnt) atomicAdd(&upto, cnt);
+  if (mn != ~0ull) atomicMin(&above, mn);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (blockIdx.x == 0) st->prefix[kSelPasses] = kth;
+    if (upto) atomicAdd(&st->upto, upto);
+    if (above != ~0ull) atomicMin(&st->above, above);
+  }
+}
+
+// exact weights w = me2 wps; clears the nclear words of the selection's counters
 __global__ void onestage_weights_kernel(const double* __restrict__ me2, const double* __restrict__ wps, int64_t n,
-                                        double* __restrict__ w) {
+                                        double* __restrict__ w, unsigned long long* __restrict__ clear, int nclear) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t k = i; k < nclear; k += (int64_t)gridDim.x * blockDim.x) clear[k] = 0ull;
   if (i < n) w[i] = me2[i] * wps[i];
 }
 
@@ -1089,60 +1220,54 @@ int block_records(int width, hipStream_t st, F launch, std::vector<double>* out)
   return e == hipSuccess ? ME_OK : shipfail(e, "reduction");
 }
 
-// k-th smallest (0-based) of n non-negative doubles on the device: eight passes of a
-// 256-bin histogram over the bytes of the bit patterns, most significant first.
-int select_kth(const double* v, int64_t n, int64_t k, hipStream_t st, double* out) {
-  unsigned long long* counts = nullptr;
-  hipError_t e = hipMalloc(&counts, 256 * sizeof(unsigned long long));
-  if (e != hipSuccess) return sfail(ME_ENOMEM, "selection buffer");
-  unsigned long long prefix = 0, mask = 0;
-  std::vector<unsigned long long> h(256);
-  for (int shift = 56; shift >= 0 && e == hipSuccess; shift -= 8) {
-    hipLaunchKernelGGL(clear_u64_kernel, dim3(1), dim3(256), 0, st, counts, 256);
-    hipLaunchKernelGGL(radix_hist_kernel, dim3(kRedBlocks), dim3(256), 0, st, v, n, prefix, mask, shift, counts);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(h.data(), counts, 256 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) break;
-    int b = 0;
-    while (b < 255 && (int64_t)h[b] <= k) {
-      k -= (int64_t)h[b];
-      ++b;
-    }
-    prefix |= (unsigned long long)b << shift;
-    mask |= 0xffull << shift;
-  }
-  (void)hipFree(counts);
-  if (e != hipSuccess) return shipfail(e, "selection");
-  std::memcpy(out, &prefix, sizeof(double));
-  return ME_OK;
-}
-
-// q-quantile of v[n] (n >= 1, entries >= 0) with linear interpolation between the
-// order statistics at q (n - 1) (the usual "linear" definition); q >= 1 is the maximum.
-int quantile(const double* v, int64_t n, double q, hipStream_t st, double* out) {
+// q-quantiles of `arrays` (1 or 2) arrays v[n] one after the other (n >= 1, entries >= 0)
+// with linear interpolation between the order statistics at q (n - 1) (the usual "linear"
+// definition); q >= 1 is the maximum.  words: kSelWords cleared words an array, in use on
+// st only; waits for st.  Bound by its eight launches one after the other and the one
+// copy back: both 0.99 quantiles of 65536 events 0.10 ms on an MI355X, 0.81 ms with a
+// copy to the host for each byte of each order statistic.
+int quantiles(const double* v, int arrays, int64_t n, double q, unsigned long long* words, hipStream_t st,
+              double** out) {
+  const unsigned nblk = (unsigned)std::min<int64_t>(kRedBlocks, (n + 255) / 256);
   if (q >= 1.0) {
-    std::vector<double> rec;
-    int rc = block_records(1, st, [&](double* part) {
-      hipLaunchKernelGGL(max_kernel, dim3(kRedBlocks), dim3(256), 0, st, v, n, part);
-    }, &rec);
-    if (rc) return rc;
-    double m = rec[0];
-    for (double x : rec) m = std::max(m, x);
-    *out = m;
+    double rec[2 * kRedBlocks];
+    double* part = reinterpret_cast<double*>(words);
+    hipLaunchKernelGGL(max_kernel, dim3(nblk, arrays), dim3(256), 0, st, v, n, part);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(rec, part, sizeof(double) * nblk * arrays, hipMemcpyDeviceToHost, st);
+    const hipError_t es = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = es;
+    if (e != hipSuccess) return shipfail(e, "reduction");
+    for (int a = 0; a < arrays; ++a) {
+      double m = rec[a * nblk];
+      for (unsigned b = 0; b < nblk; ++b) m = std::max(m, rec[a * nblk + b]);
+      *out[a] = m;
+    }
     return ME_OK;
   }
   const double pos = q * (double)(n - 1);
   const int64_t lo = (int64_t)std::floor(pos);
-  double a = 0.0, b = 0.0;
-  int rc = select_kth(v, n, lo, st, &a);
-  if (rc) return rc;
-  if (lo + 1 < n && pos > (double)lo) {
-    rc = select_kth(v, n, lo + 1, st, &b);
-    if (rc) return rc;
-    *out = a + (b - a) * (pos - (double)lo);
-  } else {
-    *out = a;
+  for (int pass = 0; pass < kSelPasses; ++pass)
+    hipLaunchKernelGGL(select_pass_kernel, dim3(nblk, arrays), dim3(256), 0, st, v, n, (unsigned long long)lo, pass,
+                       words);
+  hipLaunchKernelGGL(select_last_kernel, dim3(nblk, arrays), dim3(256), 0, st, v, n, (unsigned long long)lo, words);
+  hipError_t e = hipGetLastError();
+  SelectState state[2];
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(state, words, sizeof(SelectState) * arrays, hipMemcpyDeviceToHost, st);
+  const hipError_t es = hipStreamSynchronize(st);
+  if (e == hipSuccess) e = es;
+  if (e != hipSuccess) return shipfail(e, "selection");
+  for (int k = 0; k < arrays; ++k) {
+    double a, b;
+    std::memcpy(&a, &state[k].prefix[kSelPasses], sizeof(double));
+    *out[k] = a;
+    if (lo + 1 < n && pos > (double)lo) {
+      // the next order statistic: the k-th again where it is repeated
+      std::memcpy(&b, (int64_t)state[k].upto > lo + 1 ? &state[k].prefix[kSelPasses] : &state[k].above, sizeof(double));
+      *out[k] = a + (b - a) * (pos - (double)lo);
+    }
   }
   return ME_OK;
 }
@@ -1665,37 +1790,22 @@ int me_unweight_stage1(const float* y, const double* wps, const double* r1, int6
   if (n == 0) return ME_OK;
   if (!y || !wps || !r1 || !what || !idx) return sfail(ME_EINVAL, "null pointer");
   hipStream_t st = (hipStream_t)stream;
-  int* keep = nullptr;
-  int* counts = nullptr;
-  int64_t* offs = nullptr;
+  int64_t* counts = nullptr;   // kept events of each block, then their exclusive sums and the total
   const int64_t nblk = (n + 255) / 256;
-  hipError_t e = hipMalloc(&keep, n * sizeof(int));
-  if (e == hipSuccess) e = hipMalloc(&counts, nblk * sizeof(int));
-  if (e == hipSuccess) e = hipMalloc(&offs, nblk * sizeof(int64_t));
+  int64_t tot = 0;
+  hipError_t e = hipMalloc(&counts, (nblk + 1) * sizeof(int64_t));
   if (e == hipSuccess) {
     hipLaunchKernelGGL(stage1_kernel, dim3((unsigned)nblk), dim3(256), 0, st, y, wps, r1, n, ymean, ystd,
-                       what_max, what, keep);
-    hipLaunchKernelGGL(count_kernel, dim3((unsigned)nblk), dim3(256), 0, st, keep, n, counts);
+                       what_max, what, counts);
+    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, counts, nblk);
+    hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)nblk), dim3(256), 0, st, what, r1, n, what_max, counts, idx);
     e = hipGetLastError();
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(&tot, counts + nblk, sizeof(int64_t), hipMemcpyDeviceToHost, st);
+    const hipError_t es = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = es;
   }
-  std::vector<int> hc(nblk);
-  if (e == hipSuccess) e = hipMemcpyAsync(hc.data(), counts, nblk * sizeof(int), hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  std::vector<int64_t> ho(nblk);
-  int64_t tot = 0;
-  for (int64_t b = 0; b < nblk; ++b) {
-    ho[b] = tot;
-    tot += hc[b];
-  }
-  if (e == hipSuccess) e = hipMemcpyAsync(offs, ho.data(), nblk * sizeof(int64_t), hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)nblk), dim3(256), 0, st, keep, n, offs, idx);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  (void)hipFree(keep);
   (void)hipFree(counts);
-  (void)hipFree(offs);
   if (e != hipSuccess) return shipfail(e, "unweighting stage 1");
   *n_keep = tot;
   return ME_OK;
@@ -1825,14 +1935,14 @@ int me_unweight_maxima(const float* y, const double* wps, const double* me2, int
   if (!(quantile_q > 0.0)) return sfail(ME_EINVAL, "quantile must be in (0, 1]");
   hipStream_t st = (hipStream_t)stream;
   double* buf = nullptr;
-  hipError_t e = hipMalloc(&buf, 2 * n * sizeof(double));
+  hipError_t e = hipMalloc(&buf, (2 * n + 2 * kSelWords) * sizeof(double));
   if (e != hipSuccess) return sfail(ME_ENOMEM, "maxima buffer");
+  unsigned long long* words = reinterpret_cast<unsigned long long*>(buf + 2 * n);
   hipLaunchKernelGGL(weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, y, wps, me2, n, ymean,
-                     ystd, buf, buf + n);
+                     ystd, buf, buf + n, words, 2 * kSelWords);
   e = hipGetLastError();
-  int rc = e == hipSuccess ? quantile(buf, n, quantile_q, st, what_max) : shipfail(e, "weights kernel");
-  if (rc == ME_OK) rc = quantile(buf + n, n, quantile_q, st, x_max);
-  (void)hipStreamSynchronize(st);
+  double* outs[2] = {what_max, x_max};
+  int rc = e == hipSuccess ? quantiles(buf, 2, n, quantile_q, words, st, outs) : shipfail(e, "weights kernel");
   (void)hipFree(buf);
   return rc;
 }
@@ -1844,13 +1954,14 @@ int me_unweight_quantile(const double* me2, const double* wps, int64_t n, double
   if (!(quantile_q > 0.0)) return sfail(ME_EINVAL, "quantile must be in (0, 1]");
   hipStream_t st = (hipStream_t)stream;
   double* buf = nullptr;
-  hipError_t e = hipMalloc(&buf, n * sizeof(double));
+  hipError_t e = hipMalloc(&buf, (n + kSelWords) * sizeof(double));
   if (e != hipSuccess) return sfail(ME_ENOMEM, "quantile buffer");
+  unsigned long long* words = reinterpret_cast<unsigned long long*>(buf + n);
   // w = me2 wps: the ratio kernel with a unit surrogate weight would divide; use a plain product
-  hipLaunchKernelGGL(onestage_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, me2, wps, n, buf);
+  hipLaunchKernelGGL(onestage_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, me2, wps, n, buf,
+                     words, kSelWords);
   e = hipGetLastError();
-  int rc = e == hipSuccess ? quantile(buf, n, quantile_q, st, w_max) : shipfail(e, "weights kernel");
-  (void)hipStreamSynchronize(st);
+  int rc = e == hipSuccess ? quantiles(buf, 1, n, quantile_q, words, st, &w_max) : shipfail(e, "weights kernel");
   (void)hipFree(buf);
   return rc;
 }
