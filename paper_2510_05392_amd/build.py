@@ -26,6 +26,11 @@ LIB = os.path.join(HERE, 'libmegpu.so')
 PROCESSES = ['gg_ttx', 'gg_ttxg', 'gg_ttxgg', 'gg_ttxggg', 'gg_ttxgggg']
 # headers the generated process units include
 PROC_HEADERS = ['me_device.h', 'me_kernels.h', 'me_process.h', 'colour_mfma.h', 'me_team.h']
+PAIR_HEADERS = ['me_pair.h', 'me_pair_desc.h']
+# particles of the largest process with a one-launch kernel: g g -> t t~ g, whose 16
+# mirror pairs of 16 events are one workgroup's lanes; with another gluon the one-lane
+# code no longer fits the registers
+PAIR_MAX_NPAR = 5
 SDE_HEADERS = ['me_sde.h', 'me_sde_desc.h']
 BG_HEADERS = ['me_device.h', 'me_bg.h', 'me_bgh.h', 'me_bgm.h', 'me_bgm_shape.h', 'me_bg_desc.h', 'colour_mfma.h',
               'me_colour_big.h']
@@ -116,6 +121,16 @@ def generate_sources(procs, build_dir):
                     f'#include "{name}.inc"\n#include "me_kernels.h"\n'
                     f'namespace me {{\nconst ProcessDesc* process_{name}() '
                     f'{{ return describe<me::{name}>(nullptr); }}\n}}\n')
+        if codegen.PROCESS_NPAR[name] <= PAIR_MAX_NPAR:
+            # few flows: all helicities of an event in one launch
+            pair = (f'// One-launch kernel of process {name} (generated).\n'
+                    f'#include "{name}.inc"\n#include "me_kernels.h"\n#include "me_pair.h"\n'
+                    f'namespace me {{\nhipError_t pair_{name}(const PairArgs& a) '
+                    f'{{ return launch_pair<me::{name}>(a); }}\n}}\n')
+            ppath = os.path.join(GEN, f'pair_{name}.hip')
+            _write_if_changed(ppath, pair)
+            units.append((ppath, os.path.join(OBJ, f'pair_{name}.o'),
+                          [inc] + [os.path.join(CSRC, h) for h in PROC_HEADERS + PAIR_HEADERS]))
         bgpath = os.path.join(GEN, f'bg_{name}.hip')
         _write_if_changed(bgpath, bg_unit(name, codegen.PROCESS_NPAR[name] - 2))
         units.append((bgpath, os.path.join(OBJ, f'bg_{name}.o'), [os.path.join(CSRC, h) for h in BG_HEADERS]))
@@ -141,6 +156,11 @@ def generate_sources(procs, build_dir):
     reg += [f'const SdeDesc* sde_{n}();' for n in lane]
     reg.append('static const SdeDesc* (*const kSde[])() = {'
                + ', '.join(f'sde_{n}' if n in lane else 'nullptr' for n in procs) + '};')
+    # one-launch kernels, aligned with kProcesses (none beyond PAIR_MAX_NPAR)
+    small = [n for n in procs if codegen.PROCESS_NPAR[n] <= PAIR_MAX_NPAR]
+    reg += [f'hipError_t pair_{n}(const PairArgs& a);' for n in small]
+    reg.append('static const PairLauncher kPair[] = {'
+               + ', '.join(f'pair_{n}' if n in small else 'nullptr' for n in procs) + '};')
     # Berends-Giele executors, aligned with kProcesses
     reg += [f'const BgDesc* bg_{n}();' for n in procs]
     reg.append('static const BgDesc* (*const kBg[])() = {' + ', '.join(f'bg_{n}' for n in procs) + '};')
@@ -159,6 +179,7 @@ def generate_sources(procs, build_dir):
     units.append((os.path.join(CSRC, 'me_api.hip'), os.path.join(build_dir, 'me_api.o'),
                   [regfile, os.path.join(INCLUDE, 'megpu.h'), os.path.join(CSRC, 'me_process.h'),
                    os.path.join(CSRC, 'me_error.h'), os.path.join(CSRC, 'me_sde_desc.h'),
+                   os.path.join(CSRC, 'me_pair_desc.h'),
                    os.path.join(CSRC, 'me_bg_desc.h'), os.path.join(CSRC, 'me_bg_tables.h'),
                    os.path.join(CSRC, 'me_bgm_tables.h'), os.path.join(CSRC, 'me_bgm_shape.h')]))
     units.append((os.path.join(CSRC, 'surrogate.hip'), os.path.join(OBJ, 'surrogate.o'),

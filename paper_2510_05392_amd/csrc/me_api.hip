@@ -21,6 +21,7 @@
 #include "me_error.h"
 #include "me_process.h"
 #include "me_sde_desc.h"
+#include "me_pair_desc.h"
 #include "me_bg_desc.h"
 #include "me_bg_tables.h"
 #include "me_bgm_tables.h"
@@ -183,6 +184,8 @@ struct me_ctx {
   int proc_index = 0;         // position in the library's process list (batch kernel)
   const me::SdeDesc* sde = nullptr;  // single-diagram-enhancement kernel, or nullptr
   const me::BgDesc* bg = nullptr;    // Berends-Giele executor
+  me::PairLauncher pair = nullptr;   // one-launch kernel (few flows), or nullptr
+  int npair = 0;                     // its mirror pairs, in d_hels after the helicities
   uint16_t* d_bg_sub = nullptr;      // its sequence tables (device)
   uint8_t* d_bg_mask = nullptr;
   uint8_t* d_bg_last = nullptr;
@@ -285,8 +288,16 @@ int ensure_partial(me_ctx* c, size_t n) {
 }
 
 int upload_good(me_ctx* c, hipStream_t s) {
-  hipError_t e = hipMemcpyAsync(c->d_hels, c->good.data(), c->good.size() * sizeof(int),
-                                hipMemcpyHostToDevice, s);
+  // the good helicities (capacity nhel), then the mirror pairs that hold one: the lower
+  // index of the pair, its number of good helicities in the upper half
+  const int all = c->desc->nhel;
+  std::vector<int> list(c->good), count(all, 0);
+  list.resize(2 * all, 0);
+  for (int h : c->good) ++count[std::min(h, all - 1 - h)];
+  c->npair = 0;
+  for (int h = 0; h < all; ++h)
+    if (count[h]) list[all + c->npair++] = h | count[h] << 16;
+  hipError_t e = hipMemcpyAsync(c->d_hels, list.data(), list.size() * sizeof(int), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(helicities)");
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
@@ -664,11 +675,12 @@ int me_init(const char* process, const me_params* p, me_handle* out) {
   c->proc_index = proc_index;
   c->sde = me::kSde[proc_index] ? me::kSde[proc_index]() : nullptr;
   c->bg = me::kBg[proc_index]();
+  c->pair = me::kPair[proc_index];
   c->params = prm;
   if (!desc->launch) c->executor = ME_EXEC_TEAM;
   c->good.resize(desc->nhel);
   for (int k = 0; k < desc->nhel; ++k) c->good[k] = k;
-  hipError_t e = hipMalloc(&c->d_hels, desc->nhel * sizeof(int));
+  hipError_t e = hipMalloc(&c->d_hels, 2 * desc->nhel * sizeof(int));
   if (e == hipSuccess) e = hipMalloc(&c->d_scratch_hels, desc->nhel * sizeof(int));
   if (e != hipSuccess) {
     if (c->d_hels) (void)hipFree(c->d_hels);
@@ -903,8 +915,22 @@ int me_filter_helicities(me_handle h, const double* momenta, int64_t nevt, doubl
 
 namespace {
 
+// The one-lane executor's FP64 path of a process with few flows is one launch, without
+// scratch.
+bool one_launch(const me_ctx* h) {
+  return h->pair && h->executor == ME_EXEC_LANE && h->params.colorsum_mode == ME_CS_FP64;
+}
+int enqueue_pairs(me_ctx* h, const double* momenta, int64_t nevt, double alpha_s, double* out_me2, hipStream_t s,
+                  const double* alphas) {
+  const me::PairArgs a{momenta, nevt, coupling(alpha_s), h->params.mt, h->d_hels + h->desc->nhel, h->npair, alphas,
+                       out_me2, 1.0 / ((double)h->desc->iden * (double)h->desc->cf_den), s};
+  const hipError_t e = h->pair(a);
+  return e == hipSuccess ? ME_OK : hip_fail(e, "matrix-element kernel launch");
+}
+
 // Size the scratch of one me_compute call (outside any capture).
 int prepare(me_ctx* h, int64_t nevt) {
+  if (one_launch(h)) return ME_OK;
   const int nhel = (int)h->good.size();
   if (h->executor == ME_EXEC_BG) {
     int rc = ensure_bg_tables(h);
@@ -983,6 +1009,12 @@ int enqueue(me_ctx* h, const double* momenta, int64_t nevt, double alpha_s, doub
             hipStream_t s, const double* alphas = nullptr) {
   const int nhel = (int)h->good.size();
   const double g = coupling(alpha_s);
+  if (one_launch(h)) {
+    KernelMark kd(h, ME_KT_DIAGRAM, s);
+    const int rc = enqueue_pairs(h, momenta, nevt, alpha_s, out_me2, s, alphas);
+    kd.done();
+    return rc;
+  }
   if (h->executor == ME_EXEC_BG) {
     // event chunks: dual amplitudes of every (helicity, event) row by the recursion,
     // the colour form of every row (FP64 on the matrix cores, or split FP16 / BF16),
@@ -1311,6 +1343,7 @@ int me_compute_noalloc(me_handle h, const double* momenta, int64_t nevt, double 
                                " bytes of scratch, more than ME_NOALLOC_SCRATCH_BYTES = " +
                                std::to_string((unsigned long long)ME_NOALLOC_SCRATCH_BYTES));
   hipStream_t s = (hipStream_t)stream;
+  if (h->pair) return enqueue_pairs(h, momenta, nevt, alpha_s, out_me2, s, nullptr);
   double* soa = h->d_static;
   double* partial = h->d_static + soa_doubles;
   me::LaunchArgs a{momenta, nevt, coupling(alpha_s), h->params.mt, h->d_hels, nhel, hpc, nchunk, partial, nullptr, s};
