@@ -470,18 +470,19 @@ __device__ __forceinline__ void bgm_col2_item(double* F, const uint32_t* tabs, d
 }
 
 // Q.J of canonical ordering it >> (N-1), gluon helicities it & (NGH - 1), for the four
-// quark helicity pairs, to qj [ordering][2 u + v][gh] (j5: the currents of length 5 of
-// six gluons).
+// quark helicity pairs, from the item's record, to qj [ordering][2 u + v][gh] (j5: the
+// currents of length 5 of six gluons).
 template <int N>
-__device__ __forceinline__ void bgm_qj_item(const double* F, const uint32_t* tabs, const cx16* j5, cx16* qj, int it) {
+__device__ __forceinline__ void bgm_qj_item(const double* F, const BgmRec<BgmShape<N>::FQ>& rec, const cx16* j5,
+                                            cx16* qj, int it) {
   using S = BgmShape<N>;
   cx j[4];
   if constexpr (N == 5)
-    bgm_current5<N>(F, BgmRec<S::F5>(tabs + S::T5, S::CV(5), it), j);
+    bgm_current5<N>(F, rec, j);
   else if constexpr (N == 6)
-    bgm_current6(F, j5, BgmRec<S::F6>(tabs + S::T6, S::CV(6), it), j);
+    bgm_current6(F, j5, rec, j);
   else
-    bgm_current<N, 4>(F, BgmRec<S::F4>(tabs + S::T4, S::CV(4), it), j);
+    bgm_current<N, 4>(F, rec, j);
   cx16* dst = qj + (it >> (N - 1)) * S::NROW + (it & (S::NGH - 1));
 #pragma unroll
   for (int uv = 0; uv < 4; ++uv) {
@@ -777,17 +778,35 @@ __device__ __forceinline__ int bgm_row(int h) {
 // unit.  Six waves would divide its 384 currents of length 5 and 1152 prefix items
 // evenly, but three waves a SIMD leave room for 168 registers each, and workgroups of
 // six waves were seen to run one at a time on a compute unit (65 ms for 262144 events
-// where four waves took 40, before later changes).  A four-gluon event (19 KB) is one wave's work; four share a
-// workgroup so that the set-up, which differs from lane to lane, is shared by kind.  A
+// where four waves took 40, before later changes).  A four-gluon event (18 KB) is one
+// wave's work; four share a workgroup so that the set-up, which differs from lane to lane, is shared by kind.  A
 // six-gluon event (124 KB) has a compute unit to itself: eight waves, two a SIMD.
 template <int N> struct BgmLaunchShape;
-template <> struct BgmLaunchShape<4> { static constexpr int EV = 4, WPE = 1, W = 2; };
-template <> struct BgmLaunchShape<5> { static constexpr int EV = 1, WPE = 4, W = 2; };
-template <> struct BgmLaunchShape<6> { static constexpr int EV = 1, WPE = 8, W = 2; };
+// LTAB: the work-item tables are copied to LDS first (four gluons: 7 KB, which leave two
+// workgroups to a compute unit; a record is then an LDS read, not one through the vector
+// cache in front of every item of the short phases: 524288 g g -> t t~ g g 5.51 ms
+// instead of 5.72).
+template <> struct BgmLaunchShape<4> { static constexpr int EV = 4, WPE = 1, W = 2; static constexpr bool LTAB = true; };
+template <> struct BgmLaunchShape<5> { static constexpr int EV = 1, WPE = 4, W = 2; static constexpr bool LTAB = false; };
+template <> struct BgmLaunchShape<6> { static constexpr int EV = 1, WPE = 8, W = 2; static constexpr bool LTAB = false; };
 
 // The items of a level to the threads, whole waves: the items of the next kind start
 // on a wave of their own.
 constexpr int bgm_waves(int n) { return (n + 63) & ~63; }
+
+// The tables as the phases read them: copied to LDS behind the frames (to be used after
+// the next barrier), or where they are.
+template <int N>
+__device__ __forceinline__ const uint32_t* bgm_tables(double* lds, const uint32_t* __restrict__ tabs) {
+  using B = BgmLaunchShape<N>;
+  if constexpr (B::LTAB) {
+    uint32_t* t = reinterpret_cast<uint32_t*>(lds + B::EV * BgmShape<N>::FRAME);
+    for (int i = threadIdx.x; i < BgmShape<N>::TWORDS; i += 64 * B::EV * B::WPE) t[i] = tabs[i];
+    return t;
+  } else {
+    return tabs;
+  }
+}
 
 // All phases of nev <= EV events by the whole workgroup, barriers between them: momenta
 // and couplings, set-up, currents of length 2 with the spinors of one gluon and Q, of
@@ -795,12 +814,21 @@ constexpr int bgm_waves(int n) { return (n + 63) & ~63; }
 // The dual amplitudes are in jt [2 NCOL][EV NROW] (row = event NROW + row of the event)
 // after the next barrier.
 template <int N, typename Note>
-__device__ __forceinline__ void bgm_events(double* lds, const uint32_t* __restrict__ tabs,
+__device__ __forceinline__ void bgm_events(double* lds, const uint32_t* tabs,
                                            const double* __restrict__ mom, const double* __restrict__ alphas,
                                            int nev, double g0, double mt, double* jt, Note note) {
   using S = BgmShape<N>;
   using B = BgmLaunchShape<N>;
   constexpr int EV = B::EV, TE = 64 * B::WPE, THREADS = EV * TE;
+  // tables in memory (one event): the records of a phase are read a phase ahead (262144
+  // g g -> t t~ g g g 27.7 ms, 28.4 with each read where it is used)
+  constexpr bool AHEAD = !B::LTAB;
+  static_assert(!AHEAD || (EV == 1 && S::V(2) <= THREADS && S::SV(3) <= THREADS), "one round of the short phases");
+  auto read = [&](auto& rec, int table, int items, int i) {
+    if (i < items) rec.read(tabs + table, items, i);
+  };
+  BgmRec<S::F2> r2;
+  if constexpr (AHEAD) read(r2, S::T2, S::V(2), threadIdx.x);
   for (int i = threadIdx.x; i < nev * (N + 2) * 4; i += THREADS)
     lds[(i / ((N + 2) * 4)) * S::FRAME + S::MOFF + i % ((N + 2) * 4)] = mom[i];
   for (int i = threadIdx.x; i < nev; i += THREADS)
@@ -822,6 +850,8 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* __restri
     }
   }
   __syncthreads();
+  BgmRec<S::F3> r3;
+  if constexpr (AHEAD) read(r3, S::T3, S::SV(3), threadIdx.x);
   {
     constexpr int A = bgm_waves(EV * S::V(2)), R = A + bgm_waves(EV * 2 * S::V(1)), C = R + bgm_waves(EV * 2 * S::V(1)),
                   Z = C + 4 * EV;
@@ -831,7 +861,8 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* __restri
         if (e < nev) {
           double* F = lds + e * S::FRAME;
           cx j[4];
-          bgm_current<N, 2>(F, BgmRec<S::F2>(tabs + S::T2, S::V(2), k), j);
+          if constexpr (!AHEAD) r2.read(tabs + S::T2, S::V(2), k);
+          bgm_current<N, 2>(F, r2, j);
           bgm_store<N>(F, S::cslot(2) + k, j);
         }
       } else if (i < C) {
@@ -860,6 +891,8 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* __restri
       else if constexpr (S::TWO) bgm_col2_item<N>(lds + e * S::FRAME, tabs, mt, m % S::V(2), m / S::V(2));
     }
   };
+  BgmRec<S::F4> r4;
+  if constexpr (AHEAD) read(r4, S::T4, S::CV(4), threadIdx.x);
   {
     constexpr int A = bgm_waves(EV * S::SV(3));
     for (int i = threadIdx.x; i < EV * S::SV(3); i += THREADS) {
@@ -867,7 +900,8 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* __restri
       if (e >= nev) continue;
       double* F = lds + e * S::FRAME;
       cx j[4];
-      bgm_current<N, 3>(F, BgmRec<S::F3>(tabs + S::T3, S::SV(3), k), j);
+      if constexpr (!AHEAD) r3.read(tabs + S::T3, S::SV(3), k);
+      bgm_current<N, 3>(F, r3, j);
       bgm_store<N>(F, S::cslot(3) + k, j);
     }
     if constexpr (N == 4) pairs((threadIdx.x + THREADS - A % THREADS) % THREADS, THREADS);
@@ -878,13 +912,18 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* __restri
   double* F = lds + ev * S::FRAME;
   double* je = jt + ev * S::NROW;
   const bool on = ev < nev;
+  BgmRec<S::FQ> rq;
+  if constexpr (N == 5) read(rq, S::TQ, S::CV(N), t);
+  BgmRec<S::F5> r5;
+  if constexpr (S::BIG) read(r5, S::T5, S::CV(5), t);
   if constexpr (N >= 5) {
-    if (on)
-      for (int i = t; i < S::CV(4); i += TE) {
-        cx j[4];
-        bgm_current<N, 4>(F, BgmRec<S::F4>(tabs + S::T4, S::CV(4), i), j);
-        bgm_store<N>(F, S::cslot(4) + i, j);
-      }
+    for (int i = t; i < S::CV(4); i += TE) {
+      const BgmRec<S::F4> rec = r4;
+      read(r4, S::T4, S::CV(4), i + TE);
+      cx j[4];
+      bgm_current<N, 4>(F, rec, j);
+      bgm_store<N>(F, S::cslot(4) + i, j);
+    }
     __syncthreads();
   }
   // currents of length 5 and Q.J of six gluons are in the event's scratch
@@ -892,19 +931,34 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* __restri
   cx16* qj = S::BIG ? reinterpret_cast<cx16*>(je + S::XQOFF) : reinterpret_cast<cx16*>(F + S::QJOFF);
   if constexpr (S::BIG) {
     for (int i = t; i < S::CV(5); i += TE) {
+      const BgmRec<S::F5> rec = r5;
+      read(r5, S::T5, S::CV(5), i + TE);
       cx j[4];
-      bgm_current5<N>(F, BgmRec<S::F5>(tabs + S::T5, S::CV(5), i), j);
+      bgm_current5<N>(F, rec, j);
 #pragma unroll
       for (int c = 0; c < 4; ++c) j5[c * S::CV(5) + i] = cx16{j[c].r, j[c].i};
     }
     pairs(t, TE);
+    read(rq, S::TQ, S::CV(N), t);
     __syncthreads();
   }
   if (on) {
     constexpr int NQ = S::NCAN * S::NGH;
-    for (int i = t; i < NQ; i += TE) bgm_qj_item<N>(F, tabs, j5, qj, i);
+    for (int i = t; i < NQ; i += TE) {
+      if constexpr (!AHEAD) rq.read(tabs + S::TQ, NQ, i);
+      const BgmRec<S::FQ> rec = rq;
+      if constexpr (AHEAD) read(rq, S::TQ, NQ, i + TE);
+      bgm_qj_item<N>(F, rec, j5, qj, i);
+    }
     if (N == 5 && t >= NQ % TE) pairs(t - NQ % TE, TE - NQ % TE);   // the waves without a second current
   }
+  // the prefixes with gluon 0 have two leaves, the others one (one wave's two rounds of
+  // four gluons take all as having two); the records of the next item are read while
+  // this one is worked on
+  constexpr int V2 = N == 4 ? S::VP : S::VP2;
+  BgmPrefix<N, 2> next;
+  if constexpr (!S::BIG)
+    if (t < V2) next.read(tabs, t);
   __syncthreads();
   if constexpr (S::BIG) {
     BgmEnds ends;
@@ -916,25 +970,17 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* __restri
     BgmEnds ends;
     bgm_ends<N>(F, ends);
     auto observe = [&](int r, double re, double im) { note(ev * S::NROW + r, re, im); };
-    // the prefixes with gluon 0 have two leaves, the others one (one wave's two rounds of
-    // four gluons take all as having two); the records of the next item are read while
-    // this one is worked on
-    constexpr int V2 = N == 4 ? S::VP : S::VP2;
-    {
-      BgmPrefix<N, 2> next;
-      if (t < V2) next.read(tabs, t);
-      for (int i = t; i < V2; i += TE) {
-        const BgmPrefix<N, 2> p = next;
-        if (i + TE < V2) next.read(tabs, i + TE);
-        bgm_prefix_item<N, EV * S::NROW, 2>(F, p, ends, je, observe);
-      }
+    for (int i = t; i < V2; i += TE) {
+      const BgmPrefix<N, 2> p = next;
+      if (i + TE < V2) next.read(tabs, i + TE);
+      bgm_prefix_item<N, EV * S::NROW, 2>(F, p, ends, je, observe);
     }
     if constexpr (V2 < S::VP) {
-      BgmPrefix<N, 1> next;
-      if (V2 + t < S::VP) next.read(tabs, V2 + t);
+      BgmPrefix<N, 1> single;
+      if (V2 + t < S::VP) single.read(tabs, V2 + t);
       for (int i = V2 + t; i < S::VP; i += TE) {
-        const BgmPrefix<N, 1> p = next;
-        if (i + TE < S::VP) next.read(tabs, i + TE);
+        const BgmPrefix<N, 1> p = single;
+        if (i + TE < S::VP) single.read(tabs, i + TE);
         bgm_prefix_item<N, EV * S::NROW, 1>(F, p, ends, je, observe);
       }
     }
@@ -1302,14 +1348,15 @@ bgm_fused_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt
   if constexpr (FMT < 0)   // equal forms: counted together
     for (int i = threadIdx.x; i < S::NROW; i += THREADS) weight[i] += mirror[i];
   double* slot = jt + (int64_t)blockIdx.x * EV * S::SLOT;
+  const uint32_t* items = bgm_tables<N>(bgm_lds, tabs);
   for (int64_t e0 = (int64_t)blockIdx.x * EV; e0 < n; e0 += PERSIST ? (int64_t)gridDim.x * EV : n) {
     const int nev = (int)(n - e0 < EV ? n - e0 : EV);
     const double* al = alphas ? alphas + e0 : nullptr;
     if constexpr (FMT == CS_FMT_FP16) {
       for (int i = threadIdx.x; i < RS; i += THREADS) rmax[i] = 0ull;
-      bgm_events<N>(bgm_lds, tabs, mom + e0 * (N + 2) * 4, al, nev, g0, mt, slot, BgmRowMax{rmax});
+      bgm_events<N>(bgm_lds, items, mom + e0 * (N + 2) * 4, al, nev, g0, mt, slot, BgmRowMax{rmax});
     } else {
-      bgm_events<N>(bgm_lds, tabs, mom + e0 * (N + 2) * 4, al, nev, g0, mt, slot, BghNoNote());
+      bgm_events<N>(bgm_lds, items, mom + e0 * (N + 2) * 4, al, nev, g0, mt, slot, BghNoNote());
     }
     // every amplitude of the block is stored (workgroup-scope fence and barrier) and
     // the frames are no longer read
@@ -1412,7 +1459,7 @@ bgm_select_kernel(const double* __restrict__ mom, int64_t n, double g0, double m
   const int64_t e0 = (int64_t)blockIdx.x * EV;
   const int nev = (int)(n - e0 < EV ? n - e0 : EV);
   double* slot = jt + e0 * S::SLOT;
-  bgm_events<N>(bgm_lds, tabs, mom + e0 * (N + 2) * 4, nullptr, nev, g0, mt, slot, BghNoNote());
+  bgm_events<N>(bgm_lds, bgm_tables<N>(bgm_lds, tabs), mom + e0 * (N + 2) * 4, nullptr, nev, g0, mt, slot, BghNoNote());
   __syncthreads();   // every amplitude of the block is stored
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   if constexpr (N == 4) {
@@ -1458,7 +1505,8 @@ constexpr int bgm_threads() {
 }
 template <int N>
 constexpr size_t bgm_lds_bytes() {
-  return (size_t)BgmLaunchShape<N>::EV * BgmShape<N>::FRAME * sizeof(double);
+  return (size_t)BgmLaunchShape<N>::EV * BgmShape<N>::FRAME * sizeof(double) +
+         (BgmLaunchShape<N>::LTAB ? BgmShape<N>::TWORDS * sizeof(uint32_t) : 0);
 }
 
 // Resident workgroups per compute unit of the fused kernels (0 if not built), the

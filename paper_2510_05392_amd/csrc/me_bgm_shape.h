@@ -53,6 +53,9 @@ struct BgmShape {
   static constexpr int T5 = T4 + words(F4) * CV(4);
   static constexpr int T6 = T5 + (N >= 5 ? words(F5) * CV(5) : 0);
   static constexpr int TP = T6 + (BIG ? words(F6) * CV(6) : 0);
+  // those of the currents of all gluons
+  static constexpr int FQ = N == 4 ? F4 : N == 5 ? F5 : F6;
+  static constexpr int TQ = N == 4 ? T4 : N == 5 ? T5 : T6;
   static constexpr int TL0 = TP + words(FP) * VP;
   static constexpr int TL1 = TL0 + words(FL) * VP;
   static constexpr int TWORDS = TL1 + words(FL) * VP2;

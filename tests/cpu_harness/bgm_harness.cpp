@@ -50,7 +50,7 @@ void bgm_eval(const double* mom, int nevt, double g, double mt, double* jamps) {
         bgm_current5<N>(F, BgmRec<S::F5>(t.data() + S::T5, S::CV(5), i), j);
         for (int c = 0; c < 4; ++c) j5[c * S::CV(5) + i] = cx16{j[c].r, j[c].i};
       }
-    for (int i = 0; i < S::NCAN * S::NGH; ++i) bgm_qj_item<N>(F, t.data(), j5, qj, i);
+    for (int i = 0; i < S::NCAN * S::NGH; ++i) bgm_qj_item<N>(F, BgmRec<S::FQ>(t.data() + S::TQ, S::CV(N), i), j5, qj, i);
     BgmEnds ends;
     bgm_ends<N>(F, ends);
     if constexpr (S::BIG) {

@@ -96,7 +96,7 @@ void count_event(const double* mom, long long* out) {
     if (S::TWO) bgm_col2_item<N>(F, t.data(), mt, i >> 1, i & 1);
   }
   lap(2);
-  for (int i = 0; i < S::NCAN * S::NGH; ++i) bgm_qj_item<N>(F, t.data(), j5, qj, i);
+  for (int i = 0; i < S::NCAN * S::NGH; ++i) bgm_qj_item<N>(F, BgmRec<S::FQ>(t.data() + S::TQ, S::CV(N), i), j5, qj, i);
   lap(3);
   BgmEnds ends;
   bgm_ends<N>(F, ends);
