@@ -406,7 +406,7 @@ int ensure_bg_tables(me_ctx* c) {
 // The Berends-Giele executor runs the two-sided recursion with the colour form and the
 // helicity sum fused: four and five gluons in launch variants 4 and 5 (FP64, or split
 // FP16 / BF16 on the matrix cores); six gluons in FP64 whatever the launch shape (4096
-// events 12.6 ms, 284 ms with the fastest shape of the one-row kernel).
+// events 11.1 ms, 284 ms with the fastest shape of the one-row kernel).
 bool bg_fused(const me_ctx* h) {
   if (h->executor != ME_EXEC_BG || h->bg->fused_slot_doubles() == 0) return false;
   return h->bg->recycle ? h->bg_variant >= 4 : h->params.colorsum_mode == ME_CS_FP64;

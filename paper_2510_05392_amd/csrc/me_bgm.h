@@ -35,7 +35,7 @@
 // an MI355X, FP64 colour, against the one-sided kernel: 262144 g g -> t t~ g g g 28.5 ms
 // (149.7), 524288 g g -> t t~ g g 5.7 ms (18.8), 1000 g g -> t t~ g g g 0.12 ms (0.63);
 // split FP16 colour, 100003 g g -> t t~ g g g 11.6 ms (51.1); six gluons against the
-// one-row kernel of me_bg.h, 4096 events 12.6 ms (284).
+// one-row kernel of me_bg.h, 4096 events 11.1 ms (284).
 //
 // Frame of an event in LDS: slots of four complex numbers, component-major (component
 // c of slot s is the 16-byte element c NS + s), so that the 16-byte reads of lanes on
@@ -154,15 +154,26 @@ __device__ __forceinline__ void bgm_load5(const cx16* j5, int k, cx* v) {
 template <typename Var>
 __device__ __forceinline__ void bgm_expand5(const cx16* j5, int info, Var var, cx* v) {
   const int cnt = info & 0x7fff;
+  // the terms in two steps, the loads of each in flight together
   bgm_load5(j5, var(0), v);
+  if (cnt > 1) {
+    cx a[3][4];
 #pragma unroll
-  for (int t = 1; t < 6; ++t)
-    if (t < cnt) {
-      cx a[4];
-      bgm_load5(j5, var(t), a);
+    for (int t = 0; t < 3; ++t) bgm_load5(j5, var(1 + t), a[t]);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) v[c] = v[c] + a[c];
-    }
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[c] = v[c] + a[t][c];
+  }
+  if (cnt > 4) {
+    cx a[2][4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) bgm_load5(j5, var(4 + t), a[t]);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[c] = v[c] + a[t][c];
+  }
   const double s = (info & 0x8000) ? -1.0 : 1.0;
 #pragma unroll
   for (int c = 0; c < 4; ++c) v[c] = s * v[c];
@@ -645,15 +656,23 @@ __device__ __forceinline__ void bgm_prefix_item(const double* F, const BgmPrefix
   }
 }
 
+template <int K>
+struct BgmInt {
+  static constexpr int value = K;
+};
+
 // The same for six gluons, cut at position 3: the row spinor of three gluons is formed
 // here, R(sigma[:3]) = S . i g X_3, currents of length 5 and Q.J come from memory, and
-// each leaf is formed after the other (register space).
+// each leaf is formed after the other (register space).  Two thirds of an event's time,
+// bound by the latency of those loads at two waves a SIMD: the terms of an expansion are
+// loaded in steps that the lanes of a wave mostly share, several in flight (4096 events
+// 11.1 ms; one after the other, and the colour form's loads not ahead, 12.5).
 template <int RS>
-__device__ __forceinline__ void bgm_prefix6_item(const double* F, const uint32_t* tabs, const BgmEnds& ends, double mt,
+__device__ __forceinline__ void bgm_prefix6_item(const double* F, const uint32_t* tabs,
+                                                 const BgmRec<BgmShape<6>::FP>& rec, const BgmEnds& ends, double mt,
                                                  const cx16* j5, const cx16* qj, double* __restrict__ jt, int it) {
   constexpr int N = 6;
   using S = BgmShape<N>;
-  const BgmRec<S::FP> rec(tabs + S::TP, S::VP, it);
   constexpr int FC = 26;
   const double g = F[S::GOFF];
   cx r3[2][4], x4[2][4], x5[2][4];
@@ -722,16 +741,25 @@ __device__ __forceinline__ void bgm_prefix6_item(const double* F, const uint32_t
     cx a[4];
 #pragma unroll
     for (int uv = 0; uv < 4; ++uv) a[uv] = cx{0.0, 0.0};
+    // 1, 5 or 10 terms, the loads of each step in flight together
+    auto terms = [&](auto first, auto last) {
+      constexpr int T0 = decltype(first)::value, T1 = decltype(last)::value;
 #pragma unroll
-    for (int t = 0; t < S::QKK; ++t)
-      if (t < qn) {
-        const cx16* q = qj + rec(FC + 1 + t) * S::NROW + gh;
+      for (int half = 0; half < 4; half += 2) {
+        cx16 x[T1 - T0][2];
 #pragma unroll
-        for (int uv = 0; uv < 4; ++uv) {
-          const cx16 x = q[uv * S::NGH];
-          a[uv] = a[uv] + cx{x.r, x.i};
-        }
+        for (int t = T0; t < T1; ++t)
+#pragma unroll
+          for (int k = 0; k < 2; ++k) x[t - T0][k] = qj[rec(FC + 1 + t) * S::NROW + gh + (half + k) * S::NGH];
+#pragma unroll
+        for (int t = T0; t < T1; ++t)
+#pragma unroll
+          for (int k = 0; k < 2; ++k) a[half + k] = a[half + k] + cx{x[t - T0][k].r, x[t - T0][k].i};
       }
+    };
+    terms(BgmInt<0>{}, BgmInt<1>{});
+    if (qn > 1) terms(BgmInt<1>{}, BgmInt<5>{});
+    if (qn > 5) terms(BgmInt<5>{}, BgmInt<S::QKK>{});
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
       cx c[4], w[2];
@@ -957,13 +985,18 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* tabs,
   // this one is worked on
   constexpr int V2 = N == 4 ? S::VP : S::VP2;
   BgmPrefix<N, 2> next;
-  if constexpr (!S::BIG)
-    if (t < V2) next.read(tabs, t);
+  BgmRec<S::FP> r6;
+  if constexpr (S::BIG) read(r6, S::TP, S::VP, t);
+  else if (t < V2) next.read(tabs, t);
   __syncthreads();
   if constexpr (S::BIG) {
     BgmEnds ends;
     bgm_ends<N>(F, ends);
-    for (int i = t; i < S::VP; i += TE) bgm_prefix6_item<S::NROW>(F, tabs, ends, mt, j5, qj, je, i);
+    for (int i = t; i < S::VP; i += TE) {
+      const BgmRec<S::FP> rec = r6;
+      read(r6, S::TP, S::VP, i + TE);
+      bgm_prefix6_item<S::NROW>(F, tabs, rec, ends, mt, j5, qj, je, i);
+    }
     return;
   }
   if (on) {
@@ -993,8 +1026,8 @@ typedef double bgm_f64x4 __attribute__((ext_vector_type(4)));
 // reversing the ordering, each map orderings to orderings and leave the colour matrix
 // unchanged, and they commute: in the sums and differences over their orbits the
 // matrix falls into eight blocks (bgm_sectors), one row per orbit (4, 16).  Six gluons
-// have the exchange of (4 5) too: sixteen blocks of 48.  An orbit's members are read once and combined by
-// stages of butterflies in registers:
+// have the exchange of (4 5) too: sixteen blocks of 48.  An orbit's members are read once
+// and combined by stages of butterflies in registers:
 //   a_s[o] = sum_b (-1)^popcount(s & b) A(member b of orbit o).
 template <int G>
 __device__ __forceinline__ void bgm_butterfly(double* x) {
@@ -1099,44 +1132,63 @@ struct BgmRowMax {
 // Six gluons: 16 rows' real or imaginary parts at a time.  The workgroup transforms the
 // 48 orbits of the 16 columns into LDS ([sector][orbit][column]); each wave then takes
 // two sectors, three 16-row blocks each, on the matrix cores as above (blocks below the
-// diagonal skipped, those above doubled).  192 x 2 products per column group of 16
+// diagonal skipped, those above doubled), its matrix operands held in registers, while
+// the next columns' amplitudes are on their way.  192 x 2 products per column group of 16
 // against 2 x 4140 of the block-triangular form of 720 flows.
 template <int WAVES>
 __device__ __forceinline__ double bgm_colour6(double* lds, const double* __restrict__ jt,
                                               const uint16_t* __restrict__ orb, const float* __restrict__ sec,
                                               const int* weight) {
-  constexpr int RS = BgmShape<6>::NROW, NO = 48, G = 16;
+  constexpr int RS = BgmShape<6>::NROW, NO = 48, G = 16, THREADS = 64 * WAVES, NI = (NO * 16 + THREADS - 1) / THREADS,
+                SW = G / WAVES, NP = 24;
   const int l = threadIdx.x & 63, j = l & 15, kq = l >> 4, w = threadIdx.x >> 6;
-  double sum = 0.0;
-  for (int grp = 0; grp < RS / 8; ++grp) {
+  double a[NI][G];
+  auto gather = [&](int grp) {
     const double* x = jt + (grp & 1) * RS + 16 * (grp >> 1);
-    for (int i = threadIdx.x; i < NO * 16; i += 64 * WAVES) {
-      const int o = i >> 4, c = i & 15;
-      double a[G];
 #pragma unroll
-      for (int b = 0; b < G; ++b) a[b] = x[(int)orb[o * G + b] * 2 * RS + c];
-      bgm_butterfly<G>(a);
+    for (int k = 0; k < NI; ++k) {
+      const int i = threadIdx.x + THREADS * k;
+      if (i < NO * 16)
 #pragma unroll
-      for (int s = 0; s < G; ++s) lds[(s * NO + o) * 16 + c] = a[s];
+        for (int b = 0; b < G; ++b) a[k][b] = x[(int)orb[(i >> 4) * G + b] * 2 * RS + (i & 15)];
+    }
+  };
+  float m[SW][NP];
+#pragma unroll
+  for (int q = 0; q < SW; ++q)
+#pragma unroll
+    for (int p = 0; p < NP; ++p) m[q][p] = sec[((w + WAVES * q) * NP + p) * 64 + l];
+  gather(0);
+  double sum = 0.0;
+#pragma unroll 1
+  for (int grp = 0; grp < RS / 8; ++grp) {
+#pragma unroll
+    for (int k = 0; k < NI; ++k) {
+      const int i = threadIdx.x + THREADS * k;
+      if (i < NO * 16) {
+        bgm_butterfly<G>(a[k]);
+#pragma unroll
+        for (int s = 0; s < G; ++s) lds[(s * NO + (i >> 4)) * 16 + (i & 15)] = a[k][s];
+      }
     }
     __syncthreads();
+    if (grp + 1 < RS / 8) gather(grp + 1);
     double f = 0.0;
-    for (int s = w; s < G; s += WAVES) {
+#pragma unroll
+    for (int q = 0; q < SW; ++q) {
       double b[12];
 #pragma unroll
-      for (int q = 0; q < 12; ++q) b[q] = lds[(s * NO + 4 * q + kq) * 16 + j];
+      for (int k = 0; k < 12; ++k) b[k] = lds[((w + WAVES * q) * NO + 4 * k + kq) * 16 + j];
       bgm_f64x4 acc[3];
-      const float* m = sec + (int64_t)s * 24 * 64 + l;
+      int p = 0;
 #pragma unroll
       for (int mb = 0; mb < 3; ++mb) {
         acc[mb] = bgm_f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int kb = mb; kb < 3; ++kb)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            acc[mb] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)*m, b[4 * kb + q], acc[mb], 0, 0, 0);
-            m += 64;
-          }
+        for (int k = 4 * mb; k < 12; ++k) {
+          asm volatile("" : "+v"(m[q][p]));   // converted here, not held as doubles
+          acc[mb] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)m[q][p++], b[k], acc[mb], 0, 0, 0);
+        }
       }
 #pragma unroll
       for (int mb = 0; mb < 3; ++mb)

@@ -231,11 +231,15 @@ class BgmBuilder {
     }
     // prefix items: sequences of length N - 1 (the last gluon follows from them), those
     // with gluon 0 inside first (two leaves each), by the position of gluon 0 and then
-    // of gluon 1, so that the lanes of a wave expand into the same numbers of terms
+    // of gluon 1, so that the lanes of a wave expand into the same numbers of terms; six
+    // gluons first by the gluons inside, so that items at work at the same time read the
+    // same currents of length 5 from memory
     std::vector<Seq> order = full_[N - 1];
     auto pos = [](const Seq& s, int g) { return (int)(std::find(s.begin(), s.end(), g) - s.begin()); };
     std::stable_sort(order.begin(), order.end(), [&](const Seq& a, const Seq& b) {
       const int a0 = pos(a, 0), b0 = pos(b, 0);
+      if (N == 6 && mask(a, 0, N - 1) != mask(b, 0, N - 1))
+        return (a0 == N - 1) != (b0 == N - 1) ? a0 < b0 : mask(a, 0, N - 1) < mask(b, 0, N - 1);
       return a0 != b0 ? a0 < b0 : pos(a, 1) < pos(b, 1);
     });
     BgmPhase pre(S::VP, S::FP), leaf0(S::VP, S::FL), leaf1(S::VP2, S::FL);

@@ -54,7 +54,8 @@ void bgm_eval(const double* mom, int nevt, double g, double mt, double* jamps) {
     BgmEnds ends;
     bgm_ends<N>(F, ends);
     if constexpr (S::BIG) {
-      for (int i = 0; i < S::VP; ++i) bgm_prefix6_item<S::NROW>(F, t.data(), ends, mt, j5, qj, jt, i);
+      for (int i = 0; i < S::VP; ++i) 
+        bgm_prefix6_item<S::NROW>(F, t.data(), BgmRec<S::FP>(t.data() + S::TP, S::VP, i), ends, mt, j5, qj, jt, i);
     } else {
       for (int i = 0; i < S::VP2; ++i) {
         BgmPrefix<N, 2> p;
