@@ -4,6 +4,8 @@ workgroup's 32 rows, the smallest and the largest hidden widths, one and several
 import numpy as np
 import pytest
 
+from paper_2510_05392_amd import rambo
+
 torch = pytest.importorskip('torch')
 pytestmark = pytest.mark.gpu
 
@@ -59,3 +61,30 @@ def test_whole_network_step_against_layers(binding, width, depth, nfeat, nb):
     # than its rounding the step's direction is not determined
     assert np.abs(fp - lp).max() <= 6.1e-3
     assert np.linalg.norm(fp - lp) <= 2e-2 * np.linalg.norm(lp)
+
+
+@pytest.mark.parametrize('npar', [4, 5, 6, 7, 8])
+@pytest.mark.parametrize('nb', [1, 127, 128, 129, 1000])
+def test_feature_rows_against_the_event_kernel(binding, npar, nb):
+    """The same expressions as the kernel that unaligned rows take: raw features equal to
+    1e-6 (a rounding of the FP64 products, which is all there is of log 1 for the two
+    incoming gluons), rows to one BF16 unit, padding zero."""
+    _say(f'case features npar={npar} nb={nb}')
+    nfeat = npar * (npar - 1) // 2
+    mom = torch.from_numpy(rambo.generate(npar, nb, 6)).cuda()
+    sur = binding.Surrogate(nfeat, 32, 1, seed=3)
+    rng = np.random.default_rng(npar)
+    sur.me_sur_set_normalisation(rng.normal(size=nfeat).astype(np.float32),
+                                 rng.uniform(0.5, 2, nfeat).astype(np.float32))
+    got = []
+    for shift in (0, 1):
+        store = torch.full((nb * sur.kpad + 8,), 0x7f7f, dtype=torch.int16, device='cuda')
+        raw = torch.empty((nb, nfeat), dtype=torch.float32, device='cuda')
+        sur.me_sur_features(mom, nb, npar, store[shift:], raw)
+        torch.cuda.synchronize()
+        row = store[shift:shift + nb * sur.kpad].clone().view(torch.bfloat16).float().reshape(nb, sur.kpad)
+        assert torch.all(store[shift + nb * sur.kpad:] == 0x7f7f)
+        assert torch.all(row[:, nfeat:] == 0)
+        got.append((raw.cpu().numpy(), row.cpu().numpy()))
+    assert np.allclose(got[0][0], got[1][0], rtol=1e-6, atol=1e-6)
+    assert np.allclose(got[0][1], got[1][1], rtol=2.0 ** -7, atol=1e-6)
