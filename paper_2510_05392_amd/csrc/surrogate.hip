@@ -385,19 +385,23 @@ struct MlpTrain {
 
 // Forward pass, loss and the backward pass through every dZ, 32 rows a workgroup.  Each
 // layer is the transposed product Z^T = W H^T (dH^T = W^T dZ^T) with the rows as the 32
-// columns; the four waves share its 32-row output blocks (wave w: blocks w and w + 4)
-// and exchange the activations (gradients) through LDS.  The weights of a block are
+// columns; the waves (four, eight beyond four blocks) share its 32-row output blocks and
+// exchange the activations (gradients) through LDS.  The weights of a block are
 // read straight into the operand registers, all of a layer in flight, the next layer's
 // behind this one's epilogue: with 32 rows a workgroup nothing is used twice, and 4096
 // rows are only 128 workgroups, so the bound is the latency of one layer after the
 // other, not traffic or matrix rate.  Every product sums its K steps in the order of
 // the layer-by-layer kernels: activations and gradients are the same bits.  A step
-// (this, the weight gradients, Adam) on 4096 rows of a 21-256x4-1 network takes 124 us
-// on an MI355X, layer by layer 1620.
+// (this, the weight gradients, Adam) on 4096 rows of a 21-256x4-1 network, gradients
+// read back, takes 119 us on an MI355X (four waves throughout: 124), layer by layer 1620.
 template <int MB>
-__global__ void __launch_bounds__(256) mlp_train_kernel(const __bf16* __restrict__ feat, const float* __restrict__ target,
+struct MlpTrainShape {
+  static constexpr int WAVES = MB > 4 ? 8 : 4;
+};
+template <int MB>
+__global__ void __launch_bounds__(64 * MlpTrainShape<MB>::WAVES) mlp_train_kernel(const __bf16* __restrict__ feat, const float* __restrict__ target,
                                                         int64_t nb, int64_t nbs, MlpTrain net) {
-  constexpr int W = 32 * MB, KS = 2 * MB, NB = (MB + 3) / 4, AS = W + 8, FS = W + 4;
+  constexpr int WV = MlpTrainShape<MB>::WAVES, W = 32 * MB, KS = 2 * MB, NB = (MB + WV - 1) / WV, AS = W + 8, FS = W + 4;
   __shared__ __attribute__((aligned(16))) __bf16 act[2][32 * AS];
   __shared__ __attribute__((aligned(16))) float dzs[32 * FS];
   __shared__ float dlast[32];
@@ -415,9 +419,9 @@ __global__ void __launch_bounds__(256) mlp_train_kernel(const __bf16* __restrict
     const bf16x8* q = reinterpret_cast<const bf16x8*>(p) + l;
 #pragma unroll
     for (int n = 0; n < NB; ++n)
-      if (w + 4 * n < MB) {
+      if (w + WV * n < MB) {
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) a[n][kk] = q[(int64_t)((w + 4 * n) * KS + kk) * 64];
+        for (int kk = 0; kk < KS; ++kk) a[n][kk] = q[(int64_t)((w + WV * n) * KS + kk) * 64];
       }
   };
   f32x16 acc[NB];
@@ -435,17 +439,17 @@ __global__ void __launch_bounds__(256) mlp_train_kernel(const __bf16* __restrict
       const bf16x8 b = *reinterpret_cast<const bf16x8*>(buf + j * AS + 16 * kk + 8 * h);
 #pragma unroll
       for (int n = 0; n < NB; ++n)
-        if (w + 4 * n < MB) acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[n][kk], b, acc[n], 0, 0, 0);
+        if (w + WV * n < MB) acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[n][kk], b, acc[n], 0, 0, 0);
     }
   };
   // bias, pre-activations, SiLU and the activations of hidden layer ly to LDS and memory
   auto activate = [&](int ly, __bf16* buf) {
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
-      if (w + 4 * n >= MB) continue;
+      if (w + WV * n >= MB) continue;
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
-        const int o = 32 * (w + 4 * n) + 16 * p + 8 * h;
+        const int o = 32 * (w + WV * n) + 16 * p + 8 * h;
         float z[8];
         bf16x8 hv;
 #pragma unroll
@@ -481,9 +485,9 @@ __global__ void __launch_bounds__(256) mlp_train_kernel(const __bf16* __restrict
       const bf16x8 b = on ? *reinterpret_cast<const bf16x8*>(feat + e * net.kin0 + 16 * kk + 8 * h) : zero8;
 #pragma unroll
       for (int n = 0; n < NB; ++n)
-        if (w + 4 * n < MB)
-          acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q0[(int64_t)((w + 4 * n) * ks0 + kk) * 64], b, acc[n], 0, 0, 0);
-      if ((kk & 3) == w) {
+        if (w + WV * n < MB)
+          acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q0[(int64_t)((w + WV * n) * ks0 + kk) * 64], b, acc[n], 0, 0, 0);
+      if (kk % WV == w) {
         if (on) *reinterpret_cast<bf16x8*>(net.h[0] + e * net.kin0 + 16 * kk + 8 * h) = b;
         __bf16* ht = net.ht[0] + (int64_t)(16 * kk + 8 * h) * nbs + e;
 #pragma unroll
@@ -540,10 +544,10 @@ __global__ void __launch_bounds__(256) mlp_train_kernel(const __bf16* __restrict
   auto gradient = [&](int ly, auto dh, __bf16* buf) {
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
-      if (w + 4 * n >= MB) continue;
+      if (w + WV * n >= MB) continue;
 #pragma unroll
       for (int p = 0; p < 2; ++p) {
-        const int o = 32 * (w + 4 * n) + 16 * p + 8 * h;
+        const int o = 32 * (w + WV * n) + 16 * p + 8 * h;
         float g[8];
         bf16x8 gv;
 #pragma unroll
@@ -587,9 +591,10 @@ __global__ void __launch_bounds__(256) mlp_train_kernel(const __bf16* __restrict
 
 // Weight and bias gradients of every layer from the transposed activations and output
 // gradients: block = one 32 x 32 tile of a layer's dW = dZ^T H (both operands have the
-// rows of the batch consecutive), its four waves on interleaved K steps, their sums
-// added in order; the last blocks add the workgroups' column sums (one layer each) and
+// rows of the batch consecutive), its eight waves on interleaved K steps (there are only
+// some 200 tiles: latency of the loads is what it takes), their sums added in order; the last blocks add the workgroups' column sums (one layer each) and
 // squared errors.
+constexpr int kGradWaves = 8;
 struct MlpGrad {
   const __bf16* dzt[17];
   const __bf16* ht[17];
@@ -600,8 +605,8 @@ struct MlpGrad {
   int layers, width, groups;   // workgroups of the pass before
   float* loss;
 };
-__global__ void __launch_bounds__(256) mlp_wgrad_kernel(int64_t nbs, MlpGrad net) {
-  __shared__ float red[3][64][17];
+__global__ void __launch_bounds__(64 * kGradWaves) mlp_wgrad_kernel(int64_t nbs, MlpGrad net) {
+  __shared__ float red[kGradWaves - 1][64][17];
   const int t = threadIdx.x, w = t >> 6, l = t & 63;
   const int L = net.layers, ntile = net.tile0[L], rec = (L - 1) * net.width + 2;
   if ((int)blockIdx.x >= ntile) {
@@ -632,11 +637,11 @@ __global__ void __launch_bounds__(256) mlp_wgrad_kernel(int64_t nbs, MlpGrad net
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
   constexpr int U = 8;   // K steps in flight
-  for (int64_t k0 = 16 * w; k0 < nbs; k0 += 64 * U) {
+  for (int64_t k0 = 16 * w; k0 < nbs; k0 += 16 * kGradWaves * U) {
     bf16x8 a[U], b[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t k = k0 + 64 * u;
+      const int64_t k = k0 + 16 * kGradWaves * u;
       a[u] = k < nbs && oa < out ? *reinterpret_cast<const bf16x8*>(A + k) : zero8;
       b[u] = k < nbs ? *reinterpret_cast<const bf16x8*>(B + k) : zero8;
     }
@@ -651,7 +656,10 @@ __global__ void __launch_bounds__(256) mlp_wgrad_kernel(int64_t nbs, MlpGrad net
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int o = o0 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
-    if (o < out) net.gw[ly][(int64_t)o * in + ib] = ((acc[v] + red[0][l][v]) + red[1][l][v]) + red[2][l][v];
+    float sum = acc[v];
+#pragma unroll
+    for (int r = 0; r < kGradWaves - 1; ++r) sum += red[r][l][v];
+    if (o < out) net.gw[ly][(int64_t)o * in + ib] = sum;
   }
 }
 
@@ -1181,8 +1189,16 @@ __global__ void __launch_bounds__(256) select_last_kernel(const double* __restri
     if (b <= kth) ++cnt;
     else if (b < mn) mn = b;
   }
-  if (cnt) atomicAdd(&upto, cnt);
-  if (mn != ~0ull) atomicMin(&above, mn);
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    cnt += __shfl_xor(cnt, d);
+    const unsigned long long m = __shfl_xor(mn, d);
+    mn = m < mn ? m : mn;
+  }
+  if ((threadIdx.x & 63) == 0) {
+    atomicAdd(&upto, cnt);
+    atomicMin(&above, mn);
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
     if (blockIdx.x == 0) st->prefix[kSelPasses] = kth;
@@ -1271,7 +1287,7 @@ int block_records(int width, hipStream_t st, F launch, std::vector<double>* out)
 // with linear interpolation between the order statistics at q (n - 1) (the usual "linear"
 // definition); q >= 1 is the maximum.  words: kSelWords cleared words an array, in use on
 // st only; waits for st.  Bound by its eight launches one after the other and the one
-// copy back: both 0.99 quantiles of 65536 events 0.10 ms on an MI355X, 0.81 ms with a
+// copy back: both 0.99 quantiles of 65536 events 91 us on an MI355X, 0.81 ms with a
 // copy to the host for each byte of each order statistic.
 int quantiles(const double* v, int arrays, int64_t n, double q, unsigned long long* words, hipStream_t st,
               double** out) {
@@ -1298,7 +1314,8 @@ int quantiles(const double* v, int arrays, int64_t n, double q, unsigned long lo
   for (int pass = 0; pass < kSelPasses; ++pass)
     hipLaunchKernelGGL(select_pass_kernel, dim3(nblk, arrays), dim3(256), 0, st, v, n, (unsigned long long)lo, pass,
                        words);
-  hipLaunchKernelGGL(select_last_kernel, dim3(nblk, arrays), dim3(256), 0, st, v, n, (unsigned long long)lo, words);
+  // one sum and one minimum for all workgroups: no more of them than keep memory busy
+  hipLaunchKernelGGL(select_last_kernel, dim3(std::min(nblk, 64u), arrays), dim3(256), 0, st, v, n, (unsigned long long)lo, words);
   hipError_t e = hipGetLastError();
   SelectState state[2];
   if (e == hipSuccess)
@@ -1547,10 +1564,10 @@ int train_grads(me_sur_ctx* c, const uint16_t* feat, const float* target, int64_
   const __bf16* f = reinterpret_cast<const __bf16*>(feat);
   int64_t n = nb, stride = nbs;
   void* args[] = {&f, &target, &n, &stride, &a};
-  hipError_t e = hipLaunchKernel(fns[mb - 1], dim3((unsigned)groups), dim3(256), args, 0, st);
+  hipError_t e = hipLaunchKernel(fns[mb - 1], dim3((unsigned)groups), dim3(mb > 4 ? 512 : 256), args, 0, st);
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return shipfail(e, "training pass");
-  hipLaunchKernelGGL(mlp_wgrad_kernel, dim3((unsigned)(g.tile0[L] + L)), dim3(256), 0, st, nbs, g);
+  hipLaunchKernelGGL(mlp_wgrad_kernel, dim3((unsigned)(g.tile0[L] + L)), dim3(64 * kGradWaves), 0, st, nbs, g);
   e = hipGetLastError();
   return e == hipSuccess ? ME_OK : shipfail(e, "weight gradients");
 }
