@@ -31,7 +31,10 @@ FP64_VALU_PEAK_TFLOPS = 78.6      # MI355X: 256 CUs x 2.4 GHz x 128 FP64 flops/c
 # key: (process, nevt, (persistent, hel_per_item, executor, split_wpe, split_rounds, bg_variant)) as me_autotune
 # reports them.
 TRAFFIC_KEY = ('persistent', 'hel_per_item', 'executor', 'split_wpe', 'split_rounds', 'bg_variant')
-MEASURED_TRAFFIC = {}
+MEASURED_TRAFFIC = {
+    # two-sided recursion with the colour form and helicity sum fused, 8 launches per call
+    ('gg_ttxggg', 262144, (0, 0, 3, 0, 0, 4)): (7.941e9, 'profiles/bgm_kernel_gg_ttxggg_262144.md'),
+}
 
 NPAR = {'gg_ttx': 4, 'gg_ttxg': 5, 'gg_ttxgg': 6, 'gg_ttxggg': 7, 'gg_ttxgggg': 8}
 SEED = {'gg_ttx': 1001, 'gg_ttxg': 1004, 'gg_ttxgg': 1002, 'gg_ttxggg': 1003, 'gg_ttxgggg': 1005}

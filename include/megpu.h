@@ -266,7 +266,8 @@ int me_set_colorsum_mode(me_handle h, int mode);
  * (64-event tile, hel_per_item helicities; 0 = all) from an atomic counter;
  * persistent = 0 launches one workgroup per item, splitting the helicities so
  * that about target_waves wavefronts are launched.  Results do not depend on
- * the configuration beyond rounding order of the helicity sum. */
+ * the configuration beyond rounding order of the helicity sum; g g -> t tbar and
+ * g g -> t tbar g are one launch for all helicities whatever it is. */
 int me_set_launch(me_handle h, int persistent, int waves_per_simd, int hel_per_item, int target_waves);
 
 /* Executor of the diagrams (the paper's kernel splitting into diagram groups,

@@ -30,11 +30,11 @@
 // this code on a counting double): 3.47e6 for g g -> t t~ g g g against 19.1e6 of the
 // one-sided kernel of me_bgh.h, 0.27e6 against 1.24e6 for g g -> t t~ g g, 59.5e6 for
 // g g -> t t~ g g g g.  Bound by the issue of FP64 vector instructions: 42e3 a wave and
-// event on each of a compute unit's SIMDs, 18 ms of the 28.5 for 262144 five-gluon
+// event on each of a compute unit's SIMDs, 18 ms of the 27.7 for 262144 five-gluon
 // events; the rest is latency of LDS and of the work-item records between barriers.  On
-// an MI355X, FP64 colour, against the one-sided kernel: 262144 g g -> t t~ g g g 28.5 ms
-// (149.7), 524288 g g -> t t~ g g 5.7 ms (18.8), 1000 g g -> t t~ g g g 0.12 ms (0.63);
-// split FP16 colour, 100003 g g -> t t~ g g g 11.6 ms (51.1); six gluons against the
+// an MI355X, FP64 colour, against the one-sided kernel: 262144 g g -> t t~ g g g 27.7 ms
+// (149.7), 524288 g g -> t t~ g g 5.5 ms (18.8), 1000 g g -> t t~ g g g 0.12 ms (0.63);
+// split FP16 colour, 100003 g g -> t t~ g g g 11.5 ms (51.0); six gluons against the
 // one-row kernel of me_bg.h, 4096 events 11.1 ms (284).
 //
 // Frame of an event in LDS: slots of four complex numbers, component-major (component
