@@ -800,6 +800,25 @@ __device__ __forceinline__ int bgm_row(int h) {
   return ((h >> (NPAR - 3)) & 1) * 2 * BgmShape<N>::NGH + ((h >> (NPAR - 4)) & 1) * BgmShape<N>::NGH + gh;
 }
 
+// Lane's part of an inverse-CDF draw: of its K consecutive weights v, entries first ..
+// first + K - 1 of n, the first whose running sum (cum before them) exceeds t, and the
+// last that is positive (-1: none).  An entry that adds nothing is never the one at which
+// the sum passes t; where cum, a tree's rounding of the weights before, is above the sum
+// with which the lane before ended, t may lie between the two, and the next entry that
+// adds something is the one.
+template <int K>
+__device__ __forceinline__ int bgm_pick(const double* v, int first, int n, double cum, double t, int* last) {
+  int pick = -1;
+  *last = -1;
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    cum += v[i];
+    if (v[i] > 0.0) *last = first + i;
+    if (pick < 0 && first + i < n && t < cum && (v[i] > 0.0 || first + i == 0)) pick = first + i;
+  }
+  return pick;
+}
+
 #ifdef __HIPCC__
 // Workgroup of the fused kernels: EV events of WPE waves each, W waves per SIMD.
 // A five-gluon event (a frame of 67 KB) takes four waves, two workgroups to a compute
@@ -1476,14 +1495,8 @@ __device__ __forceinline__ int bgm_draw(int n, double r, Weight weight, double* 
   *total = __shfl(s, 63);
   double cum = __shfl_up(s, 1);
   if (l == 0) cum = 0.0;
-  const double t = r * *total;
-  int pick = -1, last = -1;
-#pragma unroll
-  for (int i = 0; i < K; ++i) {
-    cum += v[i];
-    if (v[i] > 0.0) last = l * K + i;
-    if (pick < 0 && l * K + i < n && t < cum) pick = l * K + i;
-  }
+  int last;
+  const int pick = bgm_pick<K>(v, l * K, n, cum, r * *total, &last);
   const unsigned long long hit = __ballot(pick >= 0), pos = __ballot(last >= 0);
   if (hit) return __shfl(pick, __ffsll((long long)hit) - 1);
   return pos ? __shfl(last, 63 - __clzll((long long)pos)) : 0;

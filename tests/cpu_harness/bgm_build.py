@@ -49,6 +49,13 @@ def sectors(n, cf):
     return orb[:no * g].reshape(no, g), sec[:g * no * no].reshape(g, no, no)
 
 
+def draw(w, t):
+    """(entry drawn from the weights w at running sum t, the running sum before each lane's two)."""
+    w, cum = np.ascontiguousarray(w, dtype=np.float64), np.zeros(64)
+    p = lambda a: a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
+    return _lib('bgm_harness', '-O2').harness_bgm_draw(len(w), p(w), ctypes.c_double(t), p(cum)), cum
+
+
 def count_event(n, mom):
     """Counted operations of one event: set-up, stored currents, spinors, Q.J, prefix items."""
     m = np.ascontiguousarray(mom, dtype=np.float64)

@@ -88,6 +88,30 @@ extern "C" int harness_bgm_sectors(int n, const int* cf, int* orb, double* sec) 
   return s.norb;
 }
 
+// The draw of bgm_draw<2> with the wave's steps in turn: running sums of the lanes' weights
+// by doubling distances, then every lane's pick; cum[64] = the running sum before each lane.
+extern "C" int harness_bgm_draw(int n, const double* w, double t, double* cum) {
+  constexpr int K = 2;
+  double v[64][K], s[64], up[64];
+  for (int l = 0; l < 64; ++l) {
+    s[l] = 0.0;
+    for (int i = 0; i < K; ++i) s[l] += v[l][i] = l * K + i < n ? w[l * K + i] : 0.0;
+  }
+  for (int d = 1; d < 64; d <<= 1) {
+    std::copy(s, s + 64, up);
+    for (int l = d; l < 64; ++l) s[l] += up[l - d];
+  }
+  int last = -1;
+  for (int l = 0; l < 64; ++l) cum[l] = l ? s[l - 1] : 0.0;
+  for (int l = 0; l < 64; ++l) {
+    int pos;
+    const int pick = me::bgm_pick<K>(v[l], l * K, n, cum[l], t, &pos);
+    if (pick >= 0) return pick;
+    if (pos >= 0) last = pos;
+  }
+  return last < 0 ? 0 : last;
+}
+
 // jamps [nevt][NROW][n!][2]; hel[NROW] = helicity index of each row
 extern "C" int harness_bgm_eval(int n, const double* mom, int nevt, double g, double mt, double* jamps, int* hel) {
   for (int r = 0; r < (2 << n); ++r)

@@ -74,3 +74,29 @@ def test_flops_equal_the_counted_operations(n):
         setup, currents, spinors, qj, prefixes = bgm_build.count_event(n, m)
         assert setup == f['setup'] + 2 * int((m[2:4, 3] < 0).sum())
         assert (currents, spinors, qj, prefixes) == (f['currents'], f['spinors'], f['qj'], f['prefixes'])
+
+
+def test_draw_never_takes_an_entry_of_no_weight():
+    """Random weights, half of them zero: at the end of every lane's running sum, where the
+    next lane's start is rounded otherwise, and at random points, the entry drawn has a
+    weight and its running sum is the one that passes t but for that rounding; before the
+    first entry and beyond the total as the rule says."""
+    rng = np.random.default_rng(5)
+    gaps = 0
+    for _ in range(200):
+        n = int(rng.integers(3, 129))
+        w = rng.random(n) * (rng.random(n) < 0.5)
+        w[rng.integers(n)] = 0.5
+        _, start = bgm_build.draw(w, 0.0)
+        pad = np.concatenate([w, np.zeros(128 - n)]).reshape(64, 2)
+        ends = (start + pad[:, 0]) + pad[:, 1]
+        gaps += int((start[1:] > ends[:-1]).sum())
+        cum = np.cumsum(w)
+        for t in np.concatenate([ends[ends < cum[-1]], rng.random(20) * cum[-1], [0.0]]):
+            k, _ = bgm_build.draw(w, t)
+            assert w[k] > 0.0
+            assert cum[k] >= t * (1 - 1e-13) and (k == 0 or cum[k - 1] <= t + 1e-13 * cum[-1])
+        assert bgm_build.draw(w, 2 * cum[-1])[0] == np.nonzero(w)[0][-1]
+        assert bgm_build.draw(w, -1.0)[0] == 0
+    assert gaps > 50
+    assert bgm_build.draw(np.zeros(7), 0.0)[0] == 0
