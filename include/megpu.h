@@ -209,7 +209,9 @@ int me_num_channels(me_handle h, int32_t* nchan);
  *   out_me2[i] = as me_compute (FP64).
  * All outputs are device arrays of nevt entries.  Costs one me_compute plus
  * one helicity's dual amplitudes per event; with four and five gluons both draws come
- * out of the two-sided recursion's launch (me_set_bg 4) whatever the executor. */
+ * out of the two-sided recursion's launch (me_set_bg 4) whatever the executor, with one
+ * slot of scratch per resident workgroup (63 MB with five gluons, 25 MB with four;
+ * fewer events, fewer slots). */
 int me_select(me_handle h, const double* momenta, int64_t nevt, double alpha_s, const double* r_hel,
               const double* r_col, double* out_me2, int32_t* sel_hel, int32_t* sel_col, void* stream);
 

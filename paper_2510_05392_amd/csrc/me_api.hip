@@ -1553,30 +1553,32 @@ static int select_two_sided(me_ctx* h, const double* momenta, int64_t nevt, doub
                             hipStream_t s) {
   int rc = ensure_bg_tables(h);
   if (rc) return rc;
+  // one slot per resident workgroup, whatever the batch
+  const int per_cu = h->bg->fused_per_cu();
+  if (per_cu < 1) return fail(ME_EHIP, "selection kernel: no resident workgroup fits");
   const int ev = h->bg->fused_block_events();
-  const int64_t slot = h->bg->fused_slot_doubles();
-  const int64_t most = (int64_t)(ME_BG_FUSED_SCRATCH_BYTES / (sizeof(double) * (uint64_t)slot));
-  const int64_t blocks = std::min<int64_t>(most, (nevt + ev - 1) / ev);
-  rc = ensure_sums(h, (size_t)blocks * (size_t)slot);
+  const int64_t blocks = (nevt + ev - 1) / ev;
+  const int64_t slots = std::min<int64_t>((int64_t)per_cu * std::max(1, h->simds / 4), blocks);
+  rc = ensure_sums(h, (size_t)slots * (size_t)h->bg->fused_slot_doubles());
   if (rc) return rc;
-  for (int64_t off = 0; off < nevt; off += blocks * ev) {
-    me::BgArgs a{momenta + off * h->desc->npar * 4, std::min<int64_t>(blocks * ev, nevt - off), coupling(alpha_s),
-                 h->params.mt, h->d_hels, (int)h->good.size(), h->d_bg_sub, h->d_bg_mask, h->d_bg_last, nullptr,
-                 h->d_sums, s};
-    a.bgm = h->d_bgm;
-    a.orb = h->d_bgm_orb;
-    a.sec = h->d_bgm_sec;
-    a.r_hel = r_hel + off;
-    a.r_col = r_col + off;
-    a.sel_hel = (int*)sel_hel + off;
-    a.sel_col = (int*)sel_col + off;
-    a.out = out_me2 + off;
-    a.out_scale = 1.0 / ((double)h->desc->iden * (double)h->desc->cf_den);
-    a.grid = (int)blocks;
-    hipError_t e = h->bg->launch(a);
-    if (e != hipSuccess) return hip_fail(e, "selection kernel launch");
+  me::BgArgs a{momenta, nevt, coupling(alpha_s), h->params.mt, h->d_hels, (int)h->good.size(), h->d_bg_sub,
+               h->d_bg_mask, h->d_bg_last, nullptr, h->d_sums, s};
+  a.bgm = h->d_bgm;
+  a.orb = h->d_bgm_orb;
+  a.sec = h->d_bgm_sec;
+  a.r_hel = r_hel;
+  a.r_col = r_col;
+  a.sel_hel = (int*)sel_hel;
+  a.sel_col = (int*)sel_col;
+  a.out = out_me2;
+  a.out_scale = 1.0 / ((double)h->desc->iden * (double)h->desc->cf_den);
+  a.grid = (int)slots;
+  if (blocks > slots) {
+    hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, s, h->d_counter);
+    a.counter = reinterpret_cast<unsigned*>(h->d_counter);
   }
-  return ME_OK;
+  const hipError_t e = h->bg->launch(a);
+  return e == hipSuccess ? ME_OK : hip_fail(e, "selection kernel launch");
 }
 
 int me_select(me_handle h, const double* momenta, int64_t nevt, double alpha_s, const double* r_hel,

@@ -863,7 +863,7 @@ __device__ __forceinline__ const uint32_t* bgm_tables(double* lds, const uint32_
 template <int N, typename Note>
 __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* tabs,
                                            const double* __restrict__ mom, const double* __restrict__ alphas,
-                                           int nev, double g0, double mt, double* jt, Note note) {
+                                           int nev, double g0, double mt, double* jt, int tid, Note note) {
   using S = BgmShape<N>;
   using B = BgmLaunchShape<N>;
   constexpr int EV = B::EV, TE = 64 * B::WPE, THREADS = EV * TE;
@@ -875,16 +875,16 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* tabs,
     if (i < items) rec.read(tabs + table, items, i);
   };
   BgmRec<S::F2> r2;
-  if constexpr (AHEAD) read(r2, S::T2, S::V(2), threadIdx.x);
-  for (int i = threadIdx.x; i < nev * (N + 2) * 4; i += THREADS)
+  if constexpr (AHEAD) read(r2, S::T2, S::V(2), tid);
+  for (int i = tid; i < nev * (N + 2) * 4; i += THREADS)
     lds[(i / ((N + 2) * 4)) * S::FRAME + S::MOFF + i % ((N + 2) * 4)] = mom[i];
-  for (int i = threadIdx.x; i < nev; i += THREADS)
+  for (int i = tid; i < nev; i += THREADS)
     lds[i * S::FRAME + S::GOFF] = alphas ? sqrt(4.0 * 3.14159265358979323846 * alphas[i]) : g0;
   __syncthreads();
   {
     // the kinds of every event on waves of their own
     constexpr int NG = 2 * N - 1, A = bgm_waves(EV << N), G = A + bgm_waves(EV * NG), Z = G + 4 * EV;
-    for (int i = threadIdx.x; i < Z; i += THREADS) {
+    for (int i = tid; i < Z; i += THREADS) {
       if (i < A) {
         if (i < nev << N) bgm_setup_subset<N>(lds + (i >> N) * S::FRAME, mt, i & ((1 << N) - 1));
       } else if (i < G) {
@@ -898,11 +898,11 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* tabs,
   }
   __syncthreads();
   BgmRec<S::F3> r3;
-  if constexpr (AHEAD) read(r3, S::T3, S::SV(3), threadIdx.x);
+  if constexpr (AHEAD) read(r3, S::T3, S::SV(3), tid);
   {
     constexpr int A = bgm_waves(EV * S::V(2)), R = A + bgm_waves(EV * 2 * S::V(1)), C = R + bgm_waves(EV * 2 * S::V(1)),
                   Z = C + 4 * EV;
-    for (int i = threadIdx.x; i < Z; i += THREADS) {
+    for (int i = tid; i < Z; i += THREADS) {
       if (i < A) {
         const int e = i / S::V(2), k = i % S::V(2);
         if (e < nev) {
@@ -939,10 +939,10 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* tabs,
     }
   };
   BgmRec<S::F4> r4;
-  if constexpr (AHEAD) read(r4, S::T4, S::CV(4), threadIdx.x);
+  if constexpr (AHEAD) read(r4, S::T4, S::CV(4), tid);
   {
     constexpr int A = bgm_waves(EV * S::SV(3));
-    for (int i = threadIdx.x; i < EV * S::SV(3); i += THREADS) {
+    for (int i = tid; i < EV * S::SV(3); i += THREADS) {
       const int e = i / S::SV(3), k = i % S::SV(3);
       if (e >= nev) continue;
       double* F = lds + e * S::FRAME;
@@ -951,11 +951,11 @@ __device__ __forceinline__ void bgm_events(double* lds, const uint32_t* tabs,
       bgm_current<N, 3>(F, r3, j);
       bgm_store<N>(F, S::cslot(3) + k, j);
     }
-    if constexpr (N == 4) pairs((threadIdx.x + THREADS - A % THREADS) % THREADS, THREADS);
+    if constexpr (N == 4) pairs((tid + THREADS - A % THREADS) % THREADS, THREADS);
   }
   __syncthreads();
   // from here on the waves of an event work on it alone
-  const int ev = threadIdx.x / TE, t = threadIdx.x % TE;
+  const int ev = tid / TE, t = tid % TE;
   double* F = lds + ev * S::FRAME;
   double* je = jt + ev * S::NROW;
   const bool on = ev < nev;
@@ -1070,52 +1070,51 @@ __device__ __forceinline__ void bgm_butterfly(double* x) {
 // against 288 of the block-triangular form, and no matrix staged in LDS.
 template <int WAVES, typename Take>
 __device__ __forceinline__ void bgm_colour5(const double* __restrict__ jt, const uint16_t* __restrict__ orb,
-                                            const float* __restrict__ sec, Take take) {
+                                            const float* __restrict__ sec, int tid, Take take) {
   constexpr int RS = BgmShape<5>::NROW;
-  const int l = threadIdx.x & 63, j = l & 15, kq = l >> 4;
-  for (int grp = threadIdx.x >> 6; grp < RS / 16; grp += WAVES) {
-    const int row = 16 * grp + j;
-    const double* x = jt + row;
-    double a[2][4][8];
+  static_assert(WAVES == RS / 16, "16 rows a wave");
+  const int l = tid & 63, j = l & 15, kq = l >> 4;
+  const int row = 16 * (tid >> 6) + j;
+  const double* x = jt + row;
+  double a[2][4][8];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+  for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int b = 0; b < 8; ++b) {
-        const double* y = x + (int)orb[(4 * q + kq) * 8 + b] * 2 * RS;
-        a[0][q][b] = y[0];
-        a[1][q][b] = y[RS];
-      }
-    double f = 0.0;
+    for (int b = 0; b < 8; ++b) {
+      const double* y = x + (int)orb[(4 * q + kq) * 8 + b] * 2 * RS;
+      a[0][q][b] = y[0];
+      a[1][q][b] = y[RS];
+    }
+  double f = 0.0;
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bgm_butterfly<8>(a[p][q]);
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    bgm_f64x4 acc[2] = {bgm_f64x4{0.0, 0.0, 0.0, 0.0}, bgm_f64x4{0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double m = (double)sec[(s * 4 + q) * 64 + l];
+#pragma unroll
+      for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(m, a[p][q][s], acc[p], 0, 0, 0);
+    }
 #pragma unroll
     for (int p = 0; p < 2; ++p)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) bgm_butterfly<8>(a[p][q]);
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      bgm_f64x4 acc[2] = {bgm_f64x4{0.0, 0.0, 0.0, 0.0}, bgm_f64x4{0.0, 0.0, 0.0, 0.0}};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const double m = (double)sec[(s * 4 + q) * 64 + l];
-#pragma unroll
-        for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f64_16x16x4f64(m, a[p][q][s], acc[p], 0, 0, 0);
-      }
-#pragma unroll
-      for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) f += a[p][q][s] * acc[p][q];
-    }
-    take(row, f);
+      for (int q = 0; q < 4; ++q) f += a[p][q][s] * acc[p][q];
   }
+  take(row, f);
 }
 
 // Four gluons: the 32 rows x two parts of an event are the lanes of its wave; the
 // sectors (4 x 4, upper triangle with the elements above the diagonal doubled) are
 // uniform.  Returns lane l's part of the form of row l % 32.
 __device__ __forceinline__ double bgm_colour4(const double* __restrict__ je, const uint16_t* __restrict__ orb,
-                                              const float* __restrict__ sec) {
+                                              const float* __restrict__ sec, int tid) {
   using S = BgmShape<4>;
   constexpr int RS = BgmLaunchShape<4>::EV * S::NROW;
-  const int l = threadIdx.x & 63, row = l & 31;
+  const int l = tid & 63, row = l & 31;
   const double* x = je + (l >> 5) * RS + row;
   double a[4][8];
 #pragma unroll
@@ -1425,9 +1424,9 @@ bgm_fused_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt
     const double* al = alphas ? alphas + e0 : nullptr;
     if constexpr (FMT == CS_FMT_FP16) {
       for (int i = threadIdx.x; i < RS; i += THREADS) rmax[i] = 0ull;
-      bgm_events<N>(bgm_lds, items, mom + e0 * (N + 2) * 4, al, nev, g0, mt, slot, BgmRowMax{rmax});
+      bgm_events<N>(bgm_lds, items, mom + e0 * (N + 2) * 4, al, nev, g0, mt, slot, threadIdx.x, BgmRowMax{rmax});
     } else {
-      bgm_events<N>(bgm_lds, items, mom + e0 * (N + 2) * 4, al, nev, g0, mt, slot, BghNoNote());
+      bgm_events<N>(bgm_lds, items, mom + e0 * (N + 2) * 4, al, nev, g0, mt, slot, threadIdx.x, BghNoNote());
     }
     // every amplitude of the block is stored (workgroup-scope fence and barrier) and
     // the frames are no longer read
@@ -1449,7 +1448,7 @@ bgm_fused_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt
       }
     } else if constexpr (N == 4) {
       if (w < nev) {
-        const double f = bgm_colour4(slot + w * S::NROW, orb, sec);
+        const double f = bgm_colour4(slot + w * S::NROW, orb, sec, threadIdx.x);
         const int k = weight[l & 31];
         const double v = bgm_wave_sum(k ? (double)k * f : 0.0);
         if (l == 0) out[e0 + w] = scale * v;
@@ -1457,7 +1456,7 @@ bgm_fused_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt
     } else {
       double v = 0.0;
       if constexpr (N == 5)
-        bgm_colour5<WAVES>(slot, orb, sec, [&](int row, double f) { v += weight[row] ? (double)weight[row] * f : 0.0; });
+        bgm_colour5<WAVES>(slot, orb, sec, threadIdx.x, [&](int row, double f) { v += weight[row] ? (double)weight[row] * f : 0.0; });
       else
         v = bgm_colour6<WAVES>(bgm_lds, slot, orb, sec, weight);
       v = bgm_wave_sum(v);
@@ -1479,8 +1478,7 @@ bgm_fused_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt
 // 64 K, lane l holding K consecutive ones: the first k whose running sum exceeds r times
 // the total, or the last with a positive weight.
 template <int K, typename Weight>
-__device__ __forceinline__ int bgm_draw(int n, double r, Weight weight, double* total) {
-  const int l = threadIdx.x & 63;
+__device__ __forceinline__ int bgm_draw(int l, int n, double r, Weight weight, double* total) {
   double v[K], s = 0.0;
 #pragma unroll
   for (int i = 0; i < K; ++i) {
@@ -1507,7 +1505,12 @@ __device__ __forceinline__ int bgm_draw(int n, double r, Weight weight, double* 
 // that of both helicities of its mirror pair) and a flow with the |J_c|^2 of its row,
 // read back from the slot.  The row's amplitudes are there already: the one-lane route
 // formed every flow of every helicity from its diagrams and then those of the drawn one
-// once more.  16384 g g -> t t~ g g g on an MI355X: 1.88 ms, 106.7 by that route.
+// once more.  16384 g g -> t t~ g g g on an MI355X: 1.77 ms, 106.7 by that route.  A
+// workgroup has one slot for all the blocks that it takes: a slot a block would be 2 GB of
+// scratch for these events, one a resident workgroup is 63 MB.  The first block is its
+// own, the others come from the counter (null: there are no others), as compute units do
+// not keep the same pace: block b + gridDim.x after b took 6 % more for 16384 events, 13 %
+// for 100003.
 template <int N>
 __global__ void __launch_bounds__(64 * BgmLaunchShape<N>::EV * BgmLaunchShape<N>::WPE)
     __attribute__((amdgpu_waves_per_eu(BgmLaunchShape<N>::W)))
@@ -1515,47 +1518,64 @@ bgm_select_kernel(const double* __restrict__ mom, int64_t n, double g0, double m
                   int nhel, const uint32_t* __restrict__ tabs, const uint16_t* __restrict__ orb,
                   const float* __restrict__ sec, double* __restrict__ jt, const double* __restrict__ r_hel,
                   const double* __restrict__ r_col, double* __restrict__ out, int* __restrict__ sel_hel,
-                  int* __restrict__ sel_col, double scale) {
+                  int* __restrict__ sel_col, double scale, unsigned* __restrict__ counter) {
   using S = BgmShape<N>;
   using B = BgmLaunchShape<N>;
   constexpr int EV = B::EV, WAVES = EV * B::WPE, RS = EV * S::NROW;
   extern __shared__ __attribute__((aligned(16))) double bgm_lds[];
   __shared__ double form[RS];
-  const int64_t e0 = (int64_t)blockIdx.x * EV;
-  const int nev = (int)(n - e0 < EV ? n - e0 : EV);
-  double* slot = jt + e0 * S::SLOT;
-  bgm_events<N>(bgm_lds, bgm_tables<N>(bgm_lds, tabs), mom + e0 * (N + 2) * 4, nullptr, nev, g0, mt, slot, BghNoNote());
-  __syncthreads();   // every amplitude of the block is stored
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  if constexpr (N == 4) {
-    if (w < nev) {
-      double f = bgm_colour4(slot + w * S::NROW, orb, sec);
-      f += __shfl_xor(f, 32);   // real and imaginary parts
-      if (l < 32) form[w * S::NROW + l] = f;
+  __shared__ unsigned ticket;
+  double* slot = jt + (int64_t)blockIdx.x * EV * S::SLOT;
+  const uint32_t* items = bgm_tables<N>(bgm_lds, tabs);
+  int64_t e0 = (int64_t)blockIdx.x * EV;
+  while (e0 < n) {
+    // the block after this one, asked for now
+    unsigned next = 0;
+    if (counter && threadIdx.x == 0) next = gridDim.x + atomicAdd(counter, 1u);
+    // an opaque zero: records and operands are read in each round, not held across rounds
+    int o = 0, tid = threadIdx.x;
+    asm volatile("" : "+s"(o), "+v"(tid));
+    __builtin_assume(tid >= 0 && tid < 64 * WAVES);
+    const int nev = (int)(n - e0 < EV ? n - e0 : EV);
+    bgm_events<N>(bgm_lds, items + o, mom + e0 * (N + 2) * 4, nullptr, nev, g0, mt, slot + o, tid, BghNoNote());
+    __syncthreads();   // every amplitude of the block is stored
+    const int w = tid >> 6, l = tid & 63;
+    if constexpr (N == 4) {
+      if (w < nev) {
+        double f = bgm_colour4(slot + w * S::NROW, orb + o, sec + o, tid);
+        f += __shfl_xor(f, 32);   // real and imaginary parts
+        if (l < 32) form[w * S::NROW + l] = f;
+      }
+    } else {
+      bgm_colour5<WAVES>(slot, orb + o, sec + o, tid, [&](int row, double f) {
+        f += __shfl_xor(f, 32);
+        f += __shfl_xor(f, 16);
+        if (l < 16) form[row] = f;
+      });
     }
-  } else {
-    bgm_colour5<WAVES>(slot, orb, sec, [&](int row, double f) {
-      f += __shfl_xor(f, 32);
-      f += __shfl_xor(f, 16);
-      if (l < 16) form[row] = f;
-    });
-  }
-  __syncthreads();
-  if (w >= nev) return;
-  const double* fe = form + w * S::NROW;
-  double total;
-  const int k = bgm_draw<(4 << N) / 64>(nhel, r_hel[e0 + w], [&](int i) { return fe[bgm_row<N>(hels[i])]; }, &total);
-  const int h = hels[k];
-  const double* x = slot + w * S::NROW + bgm_row<N>(h);
-  double flows;
-  const int c = bgm_draw<(S::NCOL + 63) / 64>(S::NCOL, r_col[e0 + w], [&](int i) {
-    const double re = x[(int64_t)(2 * i) * RS], im = x[(int64_t)(2 * i + 1) * RS];
-    return re * re + im * im;
-  }, &flows);
-  if (l == 0) {
-    out[e0 + w] = scale * total;
-    sel_hel[e0 + w] = h;
-    sel_col[e0 + w] = c;
+    __syncthreads();
+    if (w < nev) {
+      const double* fe = form + w * S::NROW;
+      double total;
+      const int k =
+          bgm_draw<(4 << N) / 64>(l, nhel, r_hel[e0 + w], [&](int i) { return fe[bgm_row<N>(hels[o + i])]; }, &total);
+      const int h = hels[o + k];
+      const double* x = slot + w * S::NROW + bgm_row<N>(h);
+      double flows;
+      const int c = bgm_draw<(S::NCOL + 63) / 64>(l, S::NCOL, r_col[e0 + w], [&](int i) {
+        const double re = x[(int64_t)(2 * i) * RS], im = x[(int64_t)(2 * i + 1) * RS];
+        return re * re + im * im;
+      }, &flows);
+      if (l == 0) {
+        out[e0 + w] = scale * total;
+        sel_hel[e0 + w] = h;
+        sel_col[e0 + w] = c;
+      }
+    }
+    if (!counter) return;
+    if (threadIdx.x == 0) ticket = next;
+    __syncthreads();   // the frames, the forms and the slot are the next block's
+    e0 = (int64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)ticket) * EV;
   }
 }
 
@@ -1648,11 +1668,11 @@ hipError_t launch_bgm_select(const BgArgs& a) {
   if (attr != hipSuccess) return attr;
   const int64_t blocks = (a.n + EV - 1) / EV;
   if (!a.bgm || !a.orb || !a.sec || !a.out || !a.r_hel || !a.r_col || !a.sel_col || a.nhel < 1 ||
-      a.nhel > (4 << N) || blocks > a.grid)
+      a.nhel > (4 << N) || a.grid < 1 || (!a.counter && blocks > a.grid))
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(bgm_select_kernel<N>, dim3((unsigned)blocks), dim3(bgm_threads<N>()), lds, a.stream, a.mom, a.n,
+  hipLaunchKernelGGL(bgm_select_kernel<N>, dim3((unsigned)(blocks < a.grid ? blocks : a.grid)), dim3(bgm_threads<N>()), lds, a.stream, a.mom, a.n,
                      a.g, a.mt, a.hels, a.nhel, a.bgm, a.orb, a.sec, a.jt, a.r_hel, a.r_col, a.out, a.sel_hel,
-                     a.sel_col, a.out_scale);
+                     a.sel_col, a.out_scale, a.counter);
   return hipGetLastError();
 }
 
