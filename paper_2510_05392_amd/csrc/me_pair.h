@@ -58,13 +58,21 @@ pair_kernel(const double* __restrict__ mom, int64_t n, double g, double mt, cons
   }
 }
 
+// A launch has fewer than 2^32 threads: larger batches take several (of 5.4e8 events of
+// g g -> t t~, 2.7e8 of g g -> t t~ g).
 template <class P>
 hipError_t launch_pair(const PairArgs& a) {
+  constexpr int64_t THREADS = PairShape<P>::THREADS, most = 0xffffffffll / THREADS * kPairEvents;
   if (a.npair < 0 || a.npair > PairShape<P>::PAIRS) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(pair_kernel<P>, dim3((unsigned)((a.n + kPairEvents - 1) / kPairEvents)),
-                     dim3(PairShape<P>::THREADS), 0, a.stream, a.mom, a.n, a.g, a.mt, a.pairs, a.npair, a.alphas,
-                     a.out, a.scale);
-  return hipGetLastError();
+  for (int64_t off = 0; off < a.n; off += most) {
+    const int64_t n = a.n - off < most ? a.n - off : most;
+    hipLaunchKernelGGL(pair_kernel<P>, dim3((unsigned)((n + kPairEvents - 1) / kPairEvents)), dim3((unsigned)THREADS), 0,
+                       a.stream, a.mom + off * (P::NPAR * 4), n, a.g, a.mt, a.pairs, a.npair,
+                       a.alphas ? a.alphas + off : nullptr, a.out + off, a.scale);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace me

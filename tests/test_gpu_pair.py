@@ -45,3 +45,26 @@ def test_one_launch_against_helicity_sums(binding, name, nevt):
     torch.cuda.synchronize()
     k = NPAR[name] - 2
     assert np.max(np.abs(out.cpu().numpy() / (g * (alphas.cpu().numpy() / AS) ** k) - 1)) < 1e-12
+
+
+def test_more_events_than_threads_of_a_launch(binding):
+    """A batch whose lanes (16 an event) are more than the 2^32 - 1 threads of a launch:
+    copies of 4096 events, each with the bits of the batch of 4096."""
+    name, base, nevt = 'gg_ttxg', 4096, 2 ** 28 + 4096
+    _say(f'case one launch {name} nevt={nevt}')
+    free = torch.cuda.mem_get_info()[0]
+    if free < 60 << 30:
+        pytest.skip('needs 60 GB of device memory')
+    few = torch.from_numpy(rambo.generate(NPAR[name], base, 96)).cuda()
+    coupling = torch.linspace(0.08, 0.2, base, dtype=torch.float64, device='cuda')
+    m = binding.MatrixElement(name)
+    want = torch.empty(base, dtype=torch.float64, device='cuda')
+    m.me_compute_alphas(few, base, coupling, want)
+    mom = few.repeat(nevt // base, 1, 1)
+    alphas = coupling.repeat(nevt // base)
+    out = torch.zeros(nevt, dtype=torch.float64, device='cuda')
+    m.me_compute_alphas(mom, nevt, alphas, out)
+    torch.cuda.synchronize()
+    assert bool((out.view(-1, base) == want).all())
+    del mom, alphas, out
+    torch.cuda.empty_cache()
