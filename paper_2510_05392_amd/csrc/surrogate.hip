@@ -877,26 +877,29 @@ __global__ void copy_col_kernel(const float* __restrict__ z, int64_t ld, int64_t
 // --- unweighting ------------------------------------------------------------
 
 // stage 1: event i is kept when r[i] < min(1, w_hat_i / what_max), w_hat = exp(y*ystd +
-// ymean) * wps.  Three launches with nothing read back between them: the weights and the
-// kept events of each block of 256, their exclusive sums, the ordered indices (which
-// decide again, from the stored weight: the same comparison).
-__device__ __forceinline__ bool stage1_kept(double wh, double r, double what_max) {
-  return r < fmin(1.0, wh / what_max);
-}
+// ymean) * wps.  Three launches with nothing read back between them: the weights, and the
+// decisions of each block of 256 as four words of bits with their number; the exclusive
+// sums; the ordered indices.  The last reads the bits alone: idx may be the storage of an
+// input.
 __global__ void __launch_bounds__(256) stage1_kernel(const float* __restrict__ y, const double* __restrict__ wps,
                                                      const double* __restrict__ r, int64_t n, double ymean,
                                                      double ystd, double what_max, double* __restrict__ what,
-                                                     int64_t* __restrict__ counts) {
+                                                     int64_t* __restrict__ counts,
+                                                     unsigned long long* __restrict__ bits) {
   __shared__ int waves[4];
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int w = threadIdx.x >> 6;
   bool keep = false;
   if (i < n) {
     const double wh = exp((double)y[i] * ystd + ymean) * wps[i];
     what[i] = wh;
-    keep = stage1_kept(wh, r[i], what_max);
+    keep = r[i] < fmin(1.0, wh / what_max);
   }
   const unsigned long long m = __ballot(keep);
-  if ((threadIdx.x & 63) == 0) waves[threadIdx.x >> 6] = __popcll(m);
+  if ((threadIdx.x & 63) == 0) {
+    waves[w] = __popcll(m);
+    bits[4 * (int64_t)blockIdx.x + w] = m;
+  }
   __syncthreads();
   if (threadIdx.x == 0) counts[blockIdx.x] = waves[0] + waves[1] + waves[2] + waves[3];
 }
@@ -924,20 +927,15 @@ __global__ void __launch_bounds__(1024) scan_kernel(int64_t* __restrict__ counts
 }
 
 // ordered indices of the kept events, from the exclusive sums of the blocks' counts
-__global__ void __launch_bounds__(256) scatter_kernel(const double* __restrict__ what, const double* __restrict__ r,
-                                                      int64_t n, double what_max, const int64_t* __restrict__ offs,
-                                                      int64_t* __restrict__ idx) {
-  __shared__ int waves[4];
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__global__ void __launch_bounds__(256) scatter_kernel(const unsigned long long* __restrict__ bits,
+                                                      const int64_t* __restrict__ offs, int64_t* __restrict__ idx) {
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const bool keep = i < n && stage1_kept(what[i], r[i], what_max);
-  const unsigned long long m = __ballot(keep);
-  if (l == 0) waves[w] = __popcll(m);
-  __syncthreads();
-  if (!keep) return;
+  const unsigned long long* b = bits + 4 * (int64_t)blockIdx.x;
+  const unsigned long long m = b[w];
+  if (!(m >> l & 1)) return;
   int64_t k = offs[blockIdx.x] + __popcll(m & ((1ull << l) - 1));
-  for (int v = 0; v < w; ++v) k += waves[v];
-  idx[k] = i;
+  for (int v = 0; v < w; ++v) k += __popcll(b[v]);
+  idx[k] = (int64_t)blockIdx.x * 256 + threadIdx.x;
 }
 
 __global__ void gather_kernel(const double* __restrict__ mom, const int64_t* __restrict__ idx, int64_t m,
@@ -1866,15 +1864,17 @@ int me_unweight_stage1(const float* y, const double* wps, const double* r1, int6
   if (n == 0) return ME_OK;
   if (!y || !wps || !r1 || !what || !idx) return sfail(ME_EINVAL, "null pointer");
   hipStream_t st = (hipStream_t)stream;
-  int64_t* counts = nullptr;   // kept events of each block, then their exclusive sums and the total
+  // kept events of each block, then their exclusive sums and the total; the blocks' bits
+  int64_t* counts = nullptr;
   const int64_t nblk = (n + 255) / 256;
   int64_t tot = 0;
-  hipError_t e = hipMalloc(&counts, (nblk + 1) * sizeof(int64_t));
+  hipError_t e = hipMalloc(&counts, (5 * nblk + 1) * sizeof(int64_t));
   if (e == hipSuccess) {
+    unsigned long long* bits = reinterpret_cast<unsigned long long*>(counts + nblk + 1);
     hipLaunchKernelGGL(stage1_kernel, dim3((unsigned)nblk), dim3(256), 0, st, y, wps, r1, n, ymean, ystd,
-                       what_max, what, counts);
+                       what_max, what, counts, bits);
     hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, counts, nblk);
-    hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)nblk), dim3(256), 0, st, what, r1, n, what_max, counts, idx);
+    hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)nblk), dim3(256), 0, st, bits, counts, idx);
     e = hipGetLastError();
     if (e == hipSuccess)
       e = hipMemcpyAsync(&tot, counts + nblk, sizeof(int64_t), hipMemcpyDeviceToHost, st);

@@ -75,3 +75,20 @@ def test_stage1_indices(binding, n):
         assert np.array_equal(what.cpu().numpy(), wps)
         assert m == len(want) and np.array_equal(idx[:m].cpu().numpy(), want)
         assert torch.all(idx[m:] == -1)
+
+
+@pytest.mark.parametrize('n', [257, 300000])
+def test_stage1_indices_over_the_random_numbers(binding, n):
+    """idx in the storage of r1, which the call no longer needs once it has decided: the
+    same indices."""
+    _say(f'case stage 1 in place n={n}')
+    rng = np.random.default_rng(n)
+    wps, r = rng.uniform(0.5, 2.0, n), rng.random(n)
+    y = torch.zeros(n, dtype=torch.float32, device='cuda')
+    what = torch.empty(n, dtype=torch.float64, device='cuda')
+    for _ in range(5):
+        rd = torch.from_numpy(r).cuda()
+        idx = rd.view(torch.int64)
+        m = binding.me_unweight_stage1(y, torch.from_numpy(wps).cuda(), rd, n, 0.0, 1.0, 1.5, what, idx)
+        want = np.nonzero(r < np.minimum(1.0, wps / 1.5))[0]
+        assert m == len(want) and np.array_equal(idx[:m].cpu().numpy(), want)
