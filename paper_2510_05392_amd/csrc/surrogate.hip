@@ -610,16 +610,21 @@ __global__ void __launch_bounds__(64 * kGradWaves) mlp_wgrad_kernel(int64_t nbs,
   const int t = threadIdx.x, w = t >> 6, l = t & 63;
   const int L = net.layers, ntile = net.tile0[L], rec = (L - 1) * net.width + 2;
   if ((int)blockIdx.x >= ntile) {
-    // column sums of layer ly = blockIdx.x - ntile (the output layer: one column, and
-    // the loss)
-    const int ly = (int)blockIdx.x - ntile, n = ly < L - 1 ? net.width : 2;
-    if (t < n) {
-      const float* p = net.part + ly * net.width + t;
+    // column sums of layer ly = blockIdx.x - ntile (the output layer: one column, and the
+    // loss, both in FP64: the workgroups' squared errors are as many terms of one sign)
+    const int ly = (int)blockIdx.x - ntile;
+    const float* p = net.part + ly * net.width + t;
+    if (ly < L - 1 && t < net.width) {
       float s = 0.0f;
 #pragma unroll 8
       for (int g = 0; g < net.groups; ++g) s += p[(int64_t)g * rec];
-      if (ly < L - 1 || t == 0) net.gb[ly][t] = s;
-      else if (net.loss) *net.loss += s;
+      net.gb[ly][t] = s;
+    } else if (ly == L - 1 && t < 2) {
+      double s = 0.0;
+#pragma unroll 8
+      for (int g = 0; g < net.groups; ++g) s += (double)p[(int64_t)g * rec];
+      if (t == 0) net.gb[ly][0] = (float)s;
+      else if (net.loss) *net.loss += (float)s;
     }
     return;
   }

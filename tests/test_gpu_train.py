@@ -88,3 +88,22 @@ def test_feature_rows_against_the_event_kernel(binding, npar, nb):
         got.append((raw.cpu().numpy(), row.cpu().numpy()))
     assert np.allclose(got[0][0], got[1][0], rtol=1e-6, atol=1e-6)
     assert np.allclose(got[0][1], got[1][1], rtol=2.0 ** -7, atol=1e-6)
+
+
+@pytest.mark.parametrize('nb,width', [(262144, 32), (100003, 160)])
+def test_loss_of_many_rows(binding, nb, width):
+    """The summed squared error of a network of zeros (outputs 0, so the errors are the
+    targets) against 64 bits: FP32 sums over the 32 rows of a workgroup (five roundings) and
+    one of the total are all that is rounded, 6 2^-24 of it.  Targets all alike, whose
+    roundings in a running sum do not average out, and spread ones."""
+    rng = np.random.default_rng(nb)
+    sur = binding.Surrogate(10, width, 1, seed=3)
+    sur.me_sur_set_params(np.zeros(sur.nparams, np.float32))
+    feat = torch.zeros(nb * sur.kpad, dtype=torch.int16, device='cuda')
+    for kind, t in (('alike', np.full(nb, 0.3)), ('spread', rng.normal(size=nb))):
+        _say(f'case loss {kind} width={width} nb={nb}')
+        t = t.astype(np.float32)
+        loss = torch.zeros(1, dtype=torch.float32, device='cuda')
+        sur.me_sur_grads(feat, torch.from_numpy(t).cuda(), nb, loss)
+        want = (t * t).astype(np.float64).sum()
+        assert abs(float(loss.item()) - want) <= 6 * 2.0 ** -24 * want
