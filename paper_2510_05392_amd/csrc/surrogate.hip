@@ -16,6 +16,7 @@
 #include <mutex>
 #include <set>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "megpu.h"
@@ -1356,13 +1357,13 @@ struct me_sur_ctx {
   float* mean = nullptr;
   float* inv_std = nullptr;
   int step = 0;
-  // activations for a batch capacity
+  // activations for a batch capacity, in one block
   int64_t cap = 0;
+  char* batch = nullptr;
   std::vector<float*> z;               // pre-activations per layer [cap][outp]
   std::vector<__bf16*> h;              // inputs of each layer, h[0] = features [cap][kin0]
-  // layer-by-layer backward pass, for a batch capacity of its own
-  int64_t bcap = 0;
-  float* dzf = nullptr;                // [bcap][maxw]
+  // layer-by-layer backward pass
+  float* dzf = nullptr;                // [cap][maxw]
   __bf16* dzh = nullptr;
   float* dh = nullptr;
   float* partial = nullptr;            // per-block loss partial sums
@@ -1394,15 +1395,11 @@ void sfree(me_sur_ctx* c) {
     if (p) (void)hipFree(p);
   };
   for (float* p : {c->params, c->grads, c->mom1, c->mom2, c->tpart}) f(p);
-  for (float* p : c->z) f(p);
-  for (auto v : {&c->w16, &c->wf, &c->wb, &c->h, &c->ht, &c->dzt})
+  for (auto v : {&c->w16, &c->wf, &c->wb, &c->ht, &c->dzt})
     for (__bf16* p : *v) f(p);
   f(c->mean);
   f(c->inv_std);
-  f(c->dzf);
-  f(c->dzh);
-  f(c->dh);
-  f(c->partial);
+  f(c->batch);
 }
 
 // splitmix64 (Steele, Lea, Flood 2014) for the weight initialisation
@@ -1428,42 +1425,39 @@ void drop(T*& p) {
   p = nullptr;
 }
 
-// Activations of nb rows.
+// Activations of nb rows and the buffers of the layer-by-layer backward pass: all at once,
+// so that a call that may not allocate (one that is captured) finds what the eager calls of
+// its size, whichever way they took, have left; in one block, as each allocation of a first
+// call costs some 15 us.
 int ensure_batch(me_sur_ctx* c, int64_t nb) {
   if (nb <= c->cap) return ME_OK;
   const int L = (int)c->in.size();
   c->cap = 0;
-  drop(c->z, L);
-  drop(c->h, L + 1);
-  hipError_t e = dalloc(&c->h[0], (size_t)nb * c->kin0);
-  for (int l = 0; l < L && e == hipSuccess; ++l) {
-    e = dalloc(&c->z[l], (size_t)nb * c->outp[l]);
-    if (e == hipSuccess && l + 1 < L) e = dalloc(&c->h[l + 1], (size_t)nb * c->kin[l + 1]);
-  }
-  if (e != hipSuccess) return sfail(ME_ENOMEM, std::string("surrogate activations: ") + hipGetErrorString(e));
-  // zero the padded columns once: GEMMs write only the valid ones
-  for (int l = 0; l + 1 < L; ++l)
-    (void)hipMemset(c->h[l + 1], 0, (size_t)nb * c->kin[l + 1] * sizeof(__bf16));
-  c->cap = nb;
-  return ME_OK;
-}
-
-// Buffers of the layer-by-layer backward pass.
-int ensure_backward(me_sur_ctx* c, int64_t nb) {
-  if (nb <= c->bcap) return ME_OK;
-  c->bcap = 0;
-  drop(c->dzf);
-  drop(c->dzh);
-  drop(c->dh);
-  drop(c->partial);
+  drop(c->batch);
   int maxw = c->kin0;
-  for (size_t l = 0; l < c->in.size(); ++l) maxw = std::max(maxw, std::max(c->outp[l], c->kin[l]));
-  hipError_t e = dalloc(&c->dzf, (size_t)nb * maxw);
-  if (e == hipSuccess) e = dalloc(&c->dzh, (size_t)nb * maxw);
-  if (e == hipSuccess) e = dalloc(&c->dh, (size_t)nb * maxw);
-  if (e == hipSuccess) e = dalloc(&c->partial, (size_t)(nb + 255) / 256 + 1);
-  if (e != hipSuccess) return sfail(ME_ENOMEM, std::string("surrogate gradients: ") + hipGetErrorString(e));
-  c->bcap = nb;
+  for (int l = 0; l < L; ++l) maxw = std::max(maxw, std::max(c->outp[l], c->kin[l]));
+  size_t used = 0;
+  // two passes: the size, then the addresses
+  for (int pass = 0; pass < 2; ++pass) {
+    if (pass == 1 && dalloc(&c->batch, used) != hipSuccess) {
+      (void)hipGetLastError();
+      return sfail(ME_ENOMEM, "surrogate activations: " + std::to_string(used) + " bytes");
+    }
+    used = 0;
+    auto take = [&](auto*& p, size_t n) {
+      if (pass == 1) p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(c->batch + used);
+      used += (n * sizeof(*p) + 255) / 256 * 256;
+    };
+    for (int l = 0; l < L; ++l) take(c->h[l], (size_t)nb * c->kin[l]);
+    for (int l = 0; l < L; ++l) take(c->z[l], (size_t)nb * c->outp[l]);
+    take(c->dzf, (size_t)nb * maxw);
+    take(c->dzh, (size_t)nb * maxw);
+    take(c->dh, (size_t)nb * maxw);
+    take(c->partial, (size_t)(nb + 255) / 256 + 1);
+  }
+  // zero the padded columns once: GEMMs write only the valid ones
+  for (int l = 1; l < L; ++l) (void)hipMemset(c->h[l], 0, (size_t)nb * c->kin[l] * sizeof(__bf16));
+  c->cap = nb;
   return ME_OK;
 }
 
@@ -1645,7 +1639,8 @@ int me_sur_init(const me_sur_params* p, me_surrogate* out) {
     e = hipMemcpy(c->mean, zero.data(), c->nfeat * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->inv_std, one.data(), c->nfeat * 4, hipMemcpyHostToDevice);
   }
-  c->h.assign(L + 1, nullptr);
+  c->h.assign(L, nullptr);
+  c->z.assign(L, nullptr);
   int rc = e == hipSuccess ? refresh_bf16(c, nullptr) : shipfail(e, "surrogate allocation");
   if (rc == ME_OK) {
     e = hipDeviceSynchronize();
@@ -1807,8 +1802,6 @@ int me_sur_grads(me_surrogate s, const uint16_t* feat, const float* target, int6
   // the whole-network kernels read the feature rows 16 bytes at a time
   if (whole_net(s) && ((uintptr_t)feat & 15) == 0 && (nb + 31) / 32 < (1ll << 31))
     return train_grads(s, feat, target, nb, loss, st);
-  rc = ensure_backward(s, nb);
-  if (rc) return rc;
   hipError_t e = hipMemcpyAsync(s->h[0], feat, (size_t)nb * s->kin0 * 2, hipMemcpyDeviceToDevice, st);
   if (e != hipSuccess) return shipfail(e, "feature copy");
   rc = forward(s, nb, st);

@@ -107,3 +107,35 @@ def test_loss_of_many_rows(binding, nb, width):
         sur.me_sur_grads(feat, torch.from_numpy(t).cuda(), nb, loss)
         want = (t * t).astype(np.float64).sum()
         assert abs(float(loss.item()) - want) <= 6 * 2.0 ** -24 * want
+
+
+@pytest.mark.parametrize('width,shift', [(48, 0), (64, 1)])
+def test_captured_gradients_need_no_allocation(binding, width, shift):
+    """Gradients captured into a graph after an eager call of that size had been through the
+    handle another way (48: prediction; 64: gradients of aligned rows, then captured ones of
+    rows that are not): every replay equals the eager result of a handle of its own."""
+    nfeat, depth, nb = 10, 2, 200
+    _say(f'case captured gradients width={width}')
+    rng = np.random.default_rng(width)
+    sur, ref = (binding.Surrogate(nfeat, width, depth, seed=3) for _ in range(2))
+    store = torch.zeros(nb * sur.kpad + 8, dtype=torch.int16, device='cuda')
+    feat = store[shift:shift + nb * sur.kpad]
+    target = torch.from_numpy(rng.normal(size=nb).astype(np.float32)).cuda()
+    out = torch.empty(nb, dtype=torch.float32, device='cuda')
+    if width == 48:
+        sur.me_sur_predict(store, nb, out)
+    else:
+        sur.me_sur_grads(store, target, nb)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sur.me_sur_grads(feat, target, nb, None, torch.cuda.current_stream())
+    for _ in range(3):
+        rows = np.zeros((nb, sur.kpad), np.float32)
+        rows[:, :nfeat] = rng.normal(size=(nb, nfeat))
+        feat.copy_(torch.from_numpy(rows).bfloat16().view(torch.int16).reshape(-1))
+        ref.me_sur_grads(feat, target, nb)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(sur.me_sur_get_grads(), ref.me_sur_get_grads())
