@@ -303,7 +303,8 @@ int me_kernel_times(me_handle h, double* total_ms, int64_t* launches);
  * section "Studies of a 2->6 process"; here the library times the candidates).
  * Times every candidate on these events (writing out_me2, synchronising the
  * stream) and keeps the fastest.  Candidates: the one-lane kernel's grid and
- * persistent launches (FP64 mode; one staged launch in the matrix-core modes), the
+ * persistent launches (FP64 mode; one staged launch in the matrix-core modes; one where
+ * the fields have no effect: g g -> t tbar and g g -> t tbar g in FP64), the
  * team program's helicity chunkings, and the split executor with its group-sum
  * kernel compiled for 1 or 2 waves per SIMD, its flows formed from chunks of 8, 16
  * or 32 group sums, and event chunks of as many whole rounds of group-sum waves as
@@ -314,7 +315,8 @@ int me_kernel_times(me_handle h, double* total_ms, int64_t* launches);
  * receives the ME_TUNE_FIELDS integers (persistent, waves_per_simd, hel_per_item,
  * target_waves, executor, split waves per SIMD, flow chunk, split rounds, colour
  * grid, Berends-Giele launch shape; 0 in the last five = default).  The
- * Berends-Giele executor is a candidate in its three launch shapes and, for four
+ * Berends-Giele executor is a candidate in its three launch shapes (six gluons in
+ * FP64: one) and, for four
  * and five gluons, with helicity recycling (variants 3, 4 and 5). */
 #define ME_TUNE_FIELDS 10
 int me_autotune(me_handle h, const double* momenta, int64_t nevt, double alpha_s, double* out_me2,

@@ -1808,13 +1808,14 @@ int me_autotune(me_handle h, const double* momenta, int64_t nevt, double alpha_s
   const bool fp64 = h->params.colorsum_mode == ME_CS_FP64;
   std::vector<TuneCand> cands;
   if (h->desc->launch) {
-    if (fp64) {
+    if (fp64 && !h->pair) {
       const int lane[8][4] = {{0, 1, 0, 1024}, {0, 1, 0, 4096}, {0, 1, 0, 16384}, {1, 1, 0, 0},
                               {1, 1, 8, 0},    {1, 2, 8, 0},    {1, 1, 1, 0},     {1, 2, 1, 0}};
       for (const auto& l : lane) cands.push_back(TuneCand{{l[0], l[1], l[2], l[3], ME_EXEC_LANE, 0, 0, 0, 0, 0}});
     } else {
-      // the matrix-core modes stage one helicity per chunk: the launch fields do not matter
-      cands.push_back(TuneCand{{0, 1, 0, 4096, ME_EXEC_LANE, 0, 0, 0, 0, 0}});
+      // the matrix-core modes stage one helicity per chunk, and few flows are one launch in
+      // FP64: the launch fields do not matter
+      cands.push_back(TuneCand{{0, 1, 0, h->pair ? 0 : 4096, ME_EXEC_LANE, 0, 0, 0, 0, 0}});
     }
   }
   if (fp64) {
@@ -1822,7 +1823,9 @@ int me_autotune(me_handle h, const double* momenta, int64_t nevt, double alpha_s
   } else if (!h->desc->launch) {
     cands.push_back(TuneCand{{0, 1, 0, 4096, ME_EXEC_TEAM, 0, 0, 0, 0, 0}});
   }
-  for (int v : {0, 1, 2}) cands.push_back(TuneCand{{0, 1, 0, 4096, ME_EXEC_BG, 0, 0, 0, 0, v}});
+  // six gluons in FP64 have one kernel whatever the shape
+  const int shapes = fp64 && !h->bg->recycle && h->bg->fused_slot_doubles() > 0 ? 1 : 3;
+  for (int v = 0; v < shapes; ++v) cands.push_back(TuneCand{{0, 1, 0, 4096, ME_EXEC_BG, 0, 0, 0, 0, v}});
   if (h->bg->recycle)
     for (int v : {3, 4, 5}) cands.push_back(TuneCand{{0, 1, 0, 4096, ME_EXEC_BG, 0, 0, 0, 0, v}});
   if (h->desc->split) {

@@ -107,3 +107,20 @@ def test_autotune_cache_and_parameter(binding, tmp_path, monkeypatch):
     assert d.me_autotune(mom, 8192, AS, out) == fp64_best
     assert np.array_equal(got, d.compute(mom, AS).cpu().numpy())
     assert len(cache.read_text().splitlines()) == 2
+
+
+@pytest.mark.parametrize('name,npar,nevt', [('gg_ttx', 4, 64), ('gg_ttxg', 5, 1000), ('gg_ttxgggg', 8, 16)])
+def test_autotune_reports_no_field_without_effect(binding, name, npar, nevt):
+    """Where every launch shape is the same kernel, it is timed once and reported with the
+    default fields, every time."""
+    _say(f'case autotune repeated {name} {nevt} events')
+    mom = torch.from_numpy(rambo.generate(npar, nevt, 41)).cuda()
+    out = torch.empty(nevt, dtype=torch.float64, device='cuda')
+    for _ in range(4):
+        best = binding.MatrixElement(name).me_autotune(mom, nevt, AS, out)
+        if best['executor'] == binding.ME_EXEC_LANE:
+            assert (best['persistent'], best['waves_per_simd'], best['hel_per_item'], best['target_waves']) == \
+                (0, 1, 0, 4096)
+        if best['executor'] == binding.ME_EXEC_BG and npar == 8:
+            assert best['bg_variant'] == 0
+        _say(f'  chosen {best}')
