@@ -341,11 +341,7 @@ def main():
         traffic = MEASURED_TRAFFIC.get(key)
     executor = (tuned or {}).get('executor', 0)
     bg_variant = (tuned or {}).get('bg_variant', 0)
-    bgk = {0: 'bg_kernel', 1: 'bg_kernel', 2: 'bg_kernel', 3: 'bgh_kernel'}.get(bg_variant, 'bgm_fused_kernel')
-    if process == 'gg_ttxgggg':   # six gluons: one FP64 kernel whatever the launch shape
-        bgk = 'bgm_fused_kernel'
-    kname = {1: f'team_kernel<{process}_team>', 2: f'sums_kernel<{process}>',
-             3: f'{bgk}<{NPAR[process] - 2}>'}.get(executor, f'me_kernel<{process}>')
+    kname, counted_by = flops.diagram_kernel_name(process, executor, bg_variant)
     ncol = {'gg_ttx': 2, 'gg_ttxg': 6, 'gg_ttxgg': 24, 'gg_ttxggg': 120, 'gg_ttxgggg': 720}[process]
     cname = (f'colour_f64_tri_kernel<{ncol}>' if ncol > 128 else f'colour_f64_kernel<{ncol}>') \
         if executor in (2, 3) else 'colour_mfma_kernel'
@@ -376,7 +372,7 @@ def main():
                      'traffic': traffic[0] if traffic else None,
                      'traffic_source': traffic[1] if traffic else None,
                      'kernel': kname, 'flops_per_event_helicity': f_unit,
-                     'flops_source': 'operations of the generated code, counted (tests/test_generator.py)',
+                     'flops_source': f'operations of its code, counted ({counted_by})',
                      'kernel_ms_per_launch': kms / launches[binding.ME_KT_DIAGRAM],
                      'launches': launches[binding.ME_KT_DIAGRAM],
                      'binding_resource': binding_resource(traffic, kms / launches[binding.ME_KT_DIAGRAM],

@@ -219,7 +219,9 @@ def colour_sectors_flops(n):
 def diagram_kernel(name, executor, bg_variant=0):
     """FP64 flops per (event, helicity) of the kernel that evaluates the diagrams:
     everything for the one-lane and team executors (flows and colour form are fused
-    into it; the team program runs the same routines), the group sums alone for the
+    into it; the team program runs the same routines; the one-launch kernels of the
+    processes with few flows evaluate one helicity of each mirror pair, and all good
+    helicities come in pairs: half of it), the group sums alone for the
     split executor (executor 2), whose flows and colour form run in kernels of their
     own, the recursion alone for the Berends-Giele executor (executor 3), whose
     colour form is a kernel of its own; with helicity recycling (launch variant 3)
@@ -240,7 +242,29 @@ def diagram_kernel(name, executor, bg_variant=0):
         if bg_variant == 3:
             return (bgh_event(npar - 2)['total'] + 6 * QUARK_BRANCH_MEAN) / 2 ** npar
         return bg_row(npar - 2)['total'] + QUARK_BRANCH_MEAN
-    return per_event_helicity(name) + QUARK_BRANCH_MEAN
+    full = per_event_helicity(name) + QUARK_BRANCH_MEAN
+    return full / 2 if one_launch(name, executor) else full
+
+
+def one_launch(name, executor):
+    """Whether the executor's FP64 path is the one-launch kernel (csrc/me_pair.h)."""
+    from .build import PAIR_MAX_NPAR
+    from .gen import codegen
+    return executor == 0 and codegen.PROCESS_NPAR[name] <= PAIR_MAX_NPAR
+
+
+def diagram_kernel_name(name, executor, bg_variant=0):
+    """(the FP64 kernel whose flops diagram_kernel gives, the test that counts them)."""
+    from .gen import codegen
+    n = codegen.PROCESS_NPAR[name] - 2
+    code = 'tests/test_generator.py'
+    if executor == 3 and (bg_variant in (4, 5) or n == 6):   # six gluons: whatever the launch shape
+        return f'bgm_fused_kernel<{n}>', 'tests/test_bgm.py'
+    if executor == 3:
+        return f'{"bgh_kernel" if bg_variant == 3 else "bg_kernel"}<{n}>', code
+    if one_launch(name, executor):
+        return f'pair_kernel<{name}>', code
+    return {1: f'team_kernel<{name}_team>', 2: f'sums_kernel<{name}>'}.get(executor, f'me_kernel<{name}>'), code
 
 
 def split_bytes(name):

@@ -100,3 +100,21 @@ def test_draw_never_takes_an_entry_of_no_weight():
         assert bgm_build.draw(w, -1.0)[0] == 0
     assert gaps > 50
     assert bgm_build.draw(np.zeros(7), 0.0)[0] == 0
+
+
+def test_flops_and_names_of_the_diagram_kernels():
+    """The kernel each executor's FP64 path launches, the test that counts its operations,
+    and half of the per-helicity code where one helicity of a mirror pair is evaluated."""
+    name = flops.diagram_kernel_name
+    for p in ('gg_ttx', 'gg_ttxg'):
+        assert name(p, 0) == (f'pair_kernel<{p}>', 'tests/test_generator.py')
+        assert flops.diagram_kernel(p, 0) == (flops.per_event_helicity(p) + flops.QUARK_BRANCH_MEAN) / 2
+        assert flops.diagram_kernel(p, 1) == flops.per_event_helicity(p) + flops.QUARK_BRANCH_MEAN
+    assert name('gg_ttxgg', 0) == ('me_kernel<gg_ttxgg>', 'tests/test_generator.py')
+    assert flops.diagram_kernel('gg_ttxgg', 0) == flops.per_event_helicity('gg_ttxgg') + flops.QUARK_BRANCH_MEAN
+    assert name('gg_ttxggg', 3, 3) == ('bgh_kernel<5>', 'tests/test_generator.py')
+    assert name('gg_ttxggg', 3, 4) == ('bgm_fused_kernel<5>', 'tests/test_bgm.py')
+    assert name('gg_ttxgggg', 3, 1) == ('bgm_fused_kernel<6>', 'tests/test_bgm.py')
+    assert name('gg_ttxggg', 3, 1) == ('bg_kernel<5>', 'tests/test_generator.py')
+    assert name('gg_ttxgg', 2) == ('sums_kernel<gg_ttxgg>', 'tests/test_generator.py')
+    assert name('gg_ttxg', 1) == ('team_kernel<gg_ttxg_team>', 'tests/test_generator.py')
