@@ -343,8 +343,7 @@ def main():
     bg_variant = (tuned or {}).get('bg_variant', 0)
     kname, counted_by = flops.diagram_kernel_name(process, executor, bg_variant)
     ncol = {'gg_ttx': 2, 'gg_ttxg': 6, 'gg_ttxgg': 24, 'gg_ttxggg': 120, 'gg_ttxgggg': 720}[process]
-    cname = (f'colour_f64_tri_kernel<{ncol}>' if ncol > 128 else f'colour_f64_kernel<{ncol}>') \
-        if executor in (2, 3) else 'colour_mfma_kernel'
+    cname = f'colour_f64_kernel<{ncol}>' if executor in (2, 3) else 'colour_mfma_kernel'
     # the dominant kernel is the diagram kernel; its algorithmic flops per (event, helicity)
     f_unit = flops.diagram_kernel(process, executor, bg_variant)
     tot_ms, launches = ktimes

@@ -32,34 +32,30 @@ PAIR_HEADERS = ['me_pair.h', 'me_pair_desc.h']
 # code no longer fits the registers
 PAIR_MAX_NPAR = 5
 SDE_HEADERS = ['me_sde.h', 'me_sde_desc.h']
-BG_HEADERS = ['me_device.h', 'me_bg.h', 'me_bgh.h', 'me_bgm.h', 'me_bgm_shape.h', 'me_bg_desc.h', 'colour_mfma.h',
-              'me_colour_big.h']
+BG_HEADERS = ['me_device.h', 'me_bg.h', 'me_bgh.h', 'me_bgm.h', 'me_bgm_shape.h', 'me_bg_desc.h', 'colour_mfma.h']
 
 
 def bg_unit(name, n):
-    """Source of the Berends-Giele unit of a process: the recursion kernel for n gluons
-    and the FP64 colour form of its n! flows (the full matrix held in LDS up to 128
-    flows, the block-triangular form streamed through LDS beyond)."""
+    """Source of the Berends-Giele unit of a process: the recursion kernels for n gluons
+    and, for the launch shapes that do not fuse it, the FP64 colour form of the n! flows
+    (the full matrix held in LDS; six gluons have no FP64 launch without it)."""
     import math
     ncol = math.factorial(n)
-    if ncol <= 128:
-        # the full matrix fits in LDS: the split executor's colour kernel
-        colour = ('  constexpr int RPB = 4 * 8 * COLOUR_F64_TILES;\n'
+    colour, ptr = '', 'nullptr'
+    if n < 6:
+        ptr = f'&colour64_{name}'
+        colour = (f'static hipError_t colour64_{name}(const double* jt, int64_t nrow, const double* cf64, '
+                  'double* out, hipStream_t s) {\n'
+                  '  constexpr int RPB = 4 * 8 * COLOUR_F64_TILES;\n'
                   '  const int64_t tiles = (nrow + RPB - 1) / RPB;\n'
                   f'  hipLaunchKernelGGL(colour_f64_kernel<{ncol}>, dim3((unsigned)std::min<int64_t>(tiles, '
-                  'COLOUR_F64_GRID)), dim3(256), 0, s, jt, nrow, cf64, out);\n')
-    else:
-        colour = ('  const int64_t tiles = (nrow + 32 * BIG_NT - 1) / (32 * BIG_NT);\n'
-                  f'  hipLaunchKernelGGL(colour_f64_tri_kernel<{ncol}>, dim3((unsigned)std::min<int64_t>(tiles, '
-                  'BIG_GRID)), dim3(256), 0, s, jt, nrow, cf64, out);\n')
-    tri = 0 if ncol <= 128 else 1
+                  'COLOUR_F64_GRID)), dim3(256), 0, s, jt, nrow, cf64, out);\n'
+                  '  return hipGetLastError();\n}\n')
     return (f'// Berends-Giele executor of process {name} (generated).\n'
-            '#include <algorithm>\n#include "me_bgm.h"\n#include "colour_mfma.h"\n#include "me_colour_big.h"\n'
-            'namespace me {\n'
-            f'static hipError_t colour64_{name}(const double* jt, int64_t nrow, const double* cf64, double* out, '
-            'hipStream_t s) {\n' + colour + '  return hipGetLastError();\n}\n'
+            '#include <algorithm>\n#include "me_bgm.h"\n#include "colour_mfma.h"\n'
+            f'namespace me {{\n{colour}'
             f'const BgDesc* bg_{name}() {{\n  static const BgDesc d = {{"{name}", {n}, {ncol}, &launch_bg<{n}>, '
-            f'&colour64_{name}, {tri}, {int(n in (4, 5))}, &bgm_fused_per_cu<{n}>, '
+            f'{ptr}, {int(n in (4, 5))}, &bgm_fused_per_cu<{n}>, '
             f'&bgm_fused_slot_doubles<{n}>, &bgm_block_events<{n}>}};\n'
             '  return &d;\n}\n}\n')
 ARCH = 'gfx950'

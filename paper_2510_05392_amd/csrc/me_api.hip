@@ -205,8 +205,7 @@ struct me_ctx {
   size_t jamps_cap = 0;       // doubles
   double* d_sums = nullptr;   // colour-group sums, then colour flows, of the split executor
   size_t sums_cap = 0;        // doubles
-  double* d_cf64 = nullptr;   // colour matrix for the split executor's FP64 matrix-core colour form
-  double* d_cf64_tri = nullptr;  // its block-triangular form for the Berends-Giele executor's
+  double* d_cf64 = nullptr;   // colour matrix for the FP64 matrix-core colour kernel
   int device = 0;             // device current at me_init
   double* d_static = nullptr; // this device's static scratch array (me_compute_noalloc)
   double* d_soa = nullptr;    // structure-of-arrays copy of the momenta [npar][4][nevt]
@@ -401,8 +400,6 @@ int ensure_bg_tables(me_ctx* c) {
   return ME_OK;
 }
 
-// Events per chunk of the Berends-Giele executor: the dual amplitudes of a chunk
-// (2 NCOL doubles per row, nhel rows per event) fill at most ME_SPLIT_SCRATCH_BYTES.
 // The Berends-Giele executor runs the two-sided recursion with the colour form and the
 // helicity sum fused: four and five gluons in launch variants 4 and 5 (FP64, or split
 // FP16 / BF16 on the matrix cores); six gluons in FP64 whatever the launch shape (4096
@@ -423,6 +420,9 @@ int64_t bg_fused_blocks(const me_ctx* h) {
   return std::max<int64_t>(1, b);
 }
 
+// Events per chunk of its launches that do not fuse the colour form: the dual amplitudes
+// of a chunk (2 NCOL doubles per row, nhel rows per event) fill at most
+// ME_SPLIT_SCRATCH_BYTES.
 int64_t bg_chunk(const me_ctx* h, int64_t nevt) {
   const size_t per_event = sizeof(double) * 2 * (size_t)h->desc->ncol * h->good.size();
   int64_t chunk = (int64_t)(ME_SPLIT_SCRATCH_BYTES / per_event);
@@ -561,33 +561,25 @@ int build_tables(me_ctx* c, int mode) {
   return ME_OK;
 }
 
-// Integer colour matrix in FP64 for the split executor's matrix-core colour form:
-// [16 MB][4 KS] zero padded, MB = ceil(NCOL / 16), KS = ceil(NCOL / 4).
+// Integer colour matrix in FP64 for the colour kernel of the split and Berends-Giele
+// executors: [16 MB][4 KS] zero padded, MB = ceil(NCOL / 16), KS = ceil(NCOL / 4).
 int build_cf64(me_ctx* c) {
-  if (!c->desc->split && !c->bg) return ME_OK;
+  if (!c->desc->split && !(c->bg && c->bg->colour64)) return ME_OK;
   const int n = c->desc->ncol;
   const int kp = ((n + 3) / 4) * 4, mp = ((n + 15) / 16) * 16;
-  // full matrix (split executor) and block-triangular form (Berends-Giele executor:
-  // the diagonal 16 x 16 blocks as they are, twice the blocks above, zero below)
-  std::vector<double> t((size_t)mp * kp, 0.0), tri((size_t)mp * kp, 0.0);
+  std::vector<double> t((size_t)mp * kp, 0.0);
   for (int i = 0; i < n; ++i)
     for (int k = 0; k < n; ++k) {
       const int v = c->desc->cf_int[i * n + k];
-      // the colour kernels hold the matrix in FP32
+      // the colour kernel holds the matrix in FP32
       if (v >= (1 << 24) || v <= -(1 << 24)) return fail(ME_EINVAL, "colour matrix entry not exact in FP32");
       t[(size_t)i * kp + k] = (double)v;
-      const int bi = i / 16, bk = k / 16;
-      tri[(size_t)i * kp + k] = bk > bi ? 2.0 * v : (bk == bi ? (double)v : 0.0);
     }
   hipError_t e = hipMalloc(&c->d_cf64, t.size() * sizeof(double));
   if (e == hipSuccess) e = hipMemcpy(c->d_cf64, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMalloc(&c->d_cf64_tri, tri.size() * sizeof(double));
-  if (e == hipSuccess)
-    e = hipMemcpy(c->d_cf64_tri, tri.data(), tri.size() * sizeof(double), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     if (c->d_cf64) (void)hipFree(c->d_cf64);
-    if (c->d_cf64_tri) (void)hipFree(c->d_cf64_tri);
-    c->d_cf64 = c->d_cf64_tri = nullptr;
+    c->d_cf64 = nullptr;
     return hip_fail(e, "FP64 colour-matrix table");
   }
   return ME_OK;
@@ -694,7 +686,6 @@ int me_init(const char* process, const me_params* p, me_handle* out) {
     (void)hipFree(c->d_hels);
     (void)hipFree(c->d_scratch_hels);
     if (c->d_cf64) (void)hipFree(c->d_cf64);
-    if (c->d_cf64_tri) (void)hipFree(c->d_cf64_tri);
     free_tables(c);
     delete c;
     return rc;
@@ -719,7 +710,6 @@ int me_init(const char* process, const me_params* p, me_handle* out) {
           (void)hipFree(c->d_hels);
           (void)hipFree(c->d_scratch_hels);
           if (c->d_cf64) (void)hipFree(c->d_cf64);
-          if (c->d_cf64_tri) (void)hipFree(c->d_cf64_tri);
           free_tables(c);
           delete c;
           return hip_fail(e, "hipGetSymbolAddress(scratch)");
@@ -737,7 +727,6 @@ int me_init(const char* process, const me_params* p, me_handle* out) {
     if (c->d_counter) (void)hipFree(c->d_counter);
     if (c->d_check) (void)hipFree(c->d_check);
     if (c->d_cf64) (void)hipFree(c->d_cf64);
-    if (c->d_cf64_tri) (void)hipFree(c->d_cf64_tri);
     free_tables(c);
     delete c;
     return fail(ME_ENOMEM, "work counter / capture stream");
@@ -763,7 +752,6 @@ int me_finalize(me_handle h) {
   if (h->d_jamps) (void)hipFree(h->d_jamps);
   if (h->d_sums) (void)hipFree(h->d_sums);
   if (h->d_cf64) (void)hipFree(h->d_cf64);
-  if (h->d_cf64_tri) (void)hipFree(h->d_cf64_tri);
   for (hipEvent_t e : h->ev_used) (void)hipEventSynchronize(e);
   release_timed(h);
   for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
@@ -1062,7 +1050,7 @@ int enqueue(me_ctx* h, const double* momenta, int64_t nevt, double alpha_s, doub
       kd.done();
       KernelMark kc(h, ME_KT_COLOUR, s);
       if (fp64) {
-        e = h->bg->colour64(h->d_sums, n * nhel, h->bg->colour_tri ? h->d_cf64_tri : h->d_cf64, h->d_partial, s);
+        e = h->bg->colour64(h->d_sums, n * nhel, h->d_cf64, h->d_partial, s);
       } else {
         me::ColourArgs ca{h->d_sums, n * nhel, h->params.colorsum_mode == ME_CS_FP16X2 ? 0 : 1, h->d_cf_hi,
                           h->d_cf_lo, 1.0 / h->desc->cf_den, h->d_partial, s, 1};

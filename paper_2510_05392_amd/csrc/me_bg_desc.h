@@ -66,8 +66,7 @@ struct BgDesc {
   int n;                 // gluons
   int ncol;              // orderings = colour flows
   BgLauncher launch;
-  Colour64Launcher colour64;
-  int colour_tri;        // 1: colour64 takes the block-triangular matrix, 0: the full one
+  Colour64Launcher colour64;   // FP64 colour form of the launches that do not fuse it, or nullptr
   int recycle;           // 1: launch variants 3, 4 and 5 (helicity recycling) are built
   int (*fused_per_cu)();                 // resident workgroups per CU of the fused kernel (variants 4, 5)
   int64_t (*fused_slot_doubles)();       // its scratch per workgroup
