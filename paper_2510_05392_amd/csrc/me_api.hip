@@ -287,15 +287,13 @@ int ensure_partial(me_ctx* c, size_t n) {
 }
 
 int upload_good(me_ctx* c, hipStream_t s) {
-  // the good helicities (capacity nhel), then the mirror pairs that hold one: the lower
-  // index of the pair, its number of good helicities in the upper half
+  // the good helicities (capacity nhel), then the mirror pairs that hold one
   const int all = c->desc->nhel;
-  std::vector<int> list(c->good), count(all, 0);
+  const std::vector<int> pairs = me::mirror_pairs(c->good, all);
+  std::vector<int> list(c->good);
   list.resize(2 * all, 0);
-  for (int h : c->good) ++count[std::min(h, all - 1 - h)];
-  c->npair = 0;
-  for (int h = 0; h < all; ++h)
-    if (count[h]) list[all + c->npair++] = h | count[h] << 16;
+  std::copy(pairs.begin(), pairs.end(), list.begin() + all);
+  c->npair = (int)pairs.size();
   hipError_t e = hipMemcpyAsync(c->d_hels, list.data(), list.size() * sizeof(int), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(helicities)");
   e = hipStreamSynchronize(s);

@@ -8,7 +8,7 @@ import numpy as np
 from .build import CSRC, HERE, OUT
 
 DEPS = [os.path.join(CSRC, h) for h in ('me_device.h', 'me_bg.h', 'me_bgh.h', 'me_bgm.h', 'me_bgm_shape.h',
-                                        'me_bgm_tables.h', 'me_bg_desc.h')]
+                                        'me_bgm_tables.h', 'me_bg_desc.h', 'me_pair_desc.h')]
 
 
 def _lib(name, opt):
@@ -47,6 +47,19 @@ def sectors(n, cf):
     p = lambda a: a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
     no = _lib('bgm_harness', '-O2').harness_bgm_sectors(n, p(cf), p(orb), p(sec))
     return orb[:no * g].reshape(no, g), sec[:g * no * no].reshape(g, no, no)
+
+
+def row(n, h):
+    """Row of helicity index h of n gluons."""
+    return _lib('bgm_harness', '-O2').harness_bgm_row(n, h)
+
+
+def mirror_pairs(good, nhel):
+    """[(lower helicity index, good helicities of the pair)] of a list of good helicities."""
+    good, pairs = np.ascontiguousarray(good, dtype=np.int32), np.zeros(nhel, dtype=np.int32)
+    p = lambda a: a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
+    k = _lib('bgm_harness', '-O2').harness_mirror_pairs(p(good), len(good), nhel, p(pairs))
+    return [(int(x) & 0xffff, int(x) >> 16) for x in pairs[:k]]
 
 
 def draw(w, t):

@@ -5,6 +5,7 @@
 
 #include "me_bgm.h"
 #include "me_bgm_tables.h"
+#include "me_pair_desc.h"
 
 template <int N>
 void bgm_eval(const double* mom, int nevt, double g, double mt, double* jamps) {
@@ -78,6 +79,18 @@ extern "C" int harness_bgm_words(int n) {
   return n == 4   ? (int)me::bgm_items<4>().size() - me::BgmShape<4>::TWORDS
          : n == 5 ? (int)me::bgm_items<5>().size() - me::BgmShape<5>::TWORDS
                   : (int)me::bgm_items<6>().size() - me::BgmShape<6>::TWORDS;
+}
+
+// row of helicity h of n gluons
+extern "C" int harness_bgm_row(int n, int h) {
+  return n == 4 ? me::bgm_row<4>(h) : n == 5 ? me::bgm_row<5>(h) : me::bgm_row<6>(h);
+}
+
+// mirror pairs of nh good helicities of all; returns their number
+extern "C" int harness_mirror_pairs(const int* good, int nh, int all, int* pairs) {
+  const std::vector<int> p = me::mirror_pairs(std::vector<int>(good, good + nh), all);
+  std::copy(p.begin(), p.end(), pairs);
+  return (int)p.size();
 }
 
 // orbits (norb x 2^nsym columns) and sectors of the colour form; returns norb

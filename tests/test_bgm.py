@@ -118,3 +118,19 @@ def test_flops_and_names_of_the_diagram_kernels():
     assert name('gg_ttxggg', 3, 1) == ('bg_kernel<5>', 'tests/test_generator.py')
     assert name('gg_ttxgg', 2) == ('sums_kernel<gg_ttxgg>', 'tests/test_generator.py')
     assert name('gg_ttxg', 1) == ('team_kernel<gg_ttxg_team>', 'tests/test_generator.py')
+
+
+@pytest.mark.parametrize('n', [4, 5, 6])
+def test_rows_of_helicities_whose_mirror_image_is_not_good(n):
+    """A helicity's row is the one of its own index or of its mirror image's, and of no
+    other's; pairs with one good helicity count once, whichever of the two it is."""
+    _, hel = bgm_build.jamps(n, rambo.generate(n + 2, 1, 8), 1.0, 173.0)
+    nhel = 2 ** (n + 2)
+    for h in range(nhel):
+        assert hel[bgm_build.row(n, h)] in (h, nhel - 1 - h)
+    rng = np.random.default_rng(n)
+    for good in ([0], [nhel - 1], [0, nhel - 1], sorted(rng.permutation(nhel)[:nhel // 3].tolist()), []):
+        want = {}
+        for h in good:
+            want[min(h, nhel - 1 - h)] = want.get(min(h, nhel - 1 - h), 0) + 1
+        assert bgm_build.mirror_pairs(good, nhel) == sorted(want.items())
