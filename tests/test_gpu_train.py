@@ -139,3 +139,40 @@ def test_captured_gradients_need_no_allocation(binding, width, shift):
         graph.replay()
         torch.cuda.synchronize()
         assert np.array_equal(sur.me_sur_get_grads(), ref.me_sur_get_grads())
+
+
+@pytest.mark.parametrize('width,depth,nfeat', [(32, 1, 15), (64, 3, 21), (256, 4, 15), (48, 2, 10)])
+def test_adam_steps_against_the_host(binding, width, depth, nfeat):
+    """Every parameter after each of three steps against Adam (beta 0.9 and 0.999, eps 1e-8)
+    on the host from the gradients read back: FP32 rounding of the step (1 - 0.999^k in FP32
+    is good to 2^-25 / 0.001 = 3e-5, half of that under the root, the rest is smaller: 1e-4
+    of lr together) and of the sum.  The network then acts as one that is given these
+    parameters: equal predictions and gradients."""
+    _say(f'case adam {nfeat}-{width}x{depth}')
+    rng = np.random.default_rng(width)
+    nb, lr = 300, 1e-3
+    sur, ref = (binding.Surrogate(nfeat, width, depth, seed=s) for s in (3, 4))
+    x = np.zeros((nb, sur.kpad), np.float32)
+    x[:, :nfeat] = rng.normal(size=(nb, nfeat))
+    feat = torch.from_numpy(x).bfloat16().view(torch.int16).reshape(-1).cuda()
+    target = torch.from_numpy(rng.normal(size=nb).astype(np.float32)).cuda()
+    b1, b2 = float(np.float32(0.9)), float(np.float32(0.999))
+    m, v = np.zeros(sur.nparams), np.zeros(sur.nparams)
+    for step in range(1, 4):
+        before = sur.me_sur_get_params().astype(np.float64)
+        sur.me_sur_train_step(feat, target, nb, lr)
+        torch.cuda.synchronize()
+        g, after = sur.me_sur_get_grads().astype(np.float64), sur.me_sur_get_params()
+        m, v = b1 * m + (1 - b1) * g, b2 * v + (1 - b2) * g * g
+        move = lr * (m / (1 - b1 ** step)) / (np.sqrt(v / (1 - b2 ** step)) + 1e-8)
+        assert np.abs(move).max() > 0.9 * lr and (np.abs(move) > 0.1 * lr).mean() > 0.9
+        assert np.all(np.abs(after - (before - move)) <= 1e-4 * lr + 2.0 ** -23 * np.abs(before))
+    ref.me_sur_set_params(sur.me_sur_get_params())
+    got = []
+    for s in (sur, ref):
+        y = torch.empty(nb, dtype=torch.float32, device='cuda')
+        s.me_sur_predict(feat, nb, y)
+        s.me_sur_grads(feat, target, nb)
+        torch.cuda.synchronize()
+        got.append((y.cpu().numpy(), s.me_sur_get_grads()))
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
