@@ -363,7 +363,9 @@ __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu
 // consecutive BF16, lane l = 32 h + r holding W[32 mb + f(r)][16 kk + 8 h + t], t < 8,
 // f(r) the row order of mlp_infer_kernel (an accumulator's consecutive elements are
 // consecutive outputs).  One operand is 1 KB of consecutive memory.
-__host__ __device__ inline int mlp_row(int r) { return 16 * (r >> 4) + 8 * ((r >> 2) & 1) + 4 * ((r >> 3) & 1) + (r & 3); }
+__host__ __device__ inline int mlp_row(int r) {
+  return 16 * (r >> 4) + 8 * ((r >> 2) & 1) + 4 * ((r >> 3) & 1) + (r & 3);
+}
 // position of element [o][k] of a matrix with kk operands per row block
 __host__ __device__ inline int64_t mlp_packed(int o, int k, int kks) {
   const int q = o & 31;   // the lane row r with mlp_row(r) = q: the order is its own inverse
@@ -377,11 +379,11 @@ struct MlpTrain {
   const __bf16* wlast;    // the output layer's row
   const float* b[17];
   float* z[17];           // [nb][outp]
-  __bf16* h[17];          // inputs of each layer [nb][kin]
+  __bf16* h[17];          // inputs of each layer [nb][kin], for me_sur_activations
   __bf16* ht[17];         // the same, [kin][nbs]
   __bf16* dzt[17];        // output gradients [out][nbs]
   float* part;            // [workgroup][D W + 2]: column sums of dZ, then the squared error
-  int layers, nfeat, kin0, outl;   // outl: row length of the output layer's z
+  int layers, kin0, outl;   // outl: row length of the output layer's z
 };
 
 // Forward pass, loss and the backward pass through every dZ, 32 rows a workgroup.  Each
@@ -400,9 +402,11 @@ struct MlpTrainShape {
   static constexpr int WAVES = MB > 4 ? 8 : 4;
 };
 template <int MB>
-__global__ void __launch_bounds__(64 * MlpTrainShape<MB>::WAVES) mlp_train_kernel(const __bf16* __restrict__ feat, const float* __restrict__ target,
-                                                        int64_t nb, int64_t nbs, MlpTrain net) {
-  constexpr int WV = MlpTrainShape<MB>::WAVES, W = 32 * MB, KS = 2 * MB, NB = (MB + WV - 1) / WV, AS = W + 8, FS = W + 4;
+__global__ void __launch_bounds__(64 * MlpTrainShape<MB>::WAVES)
+mlp_train_kernel(const __bf16* __restrict__ feat, const float* __restrict__ target, int64_t nb, int64_t nbs,
+                 MlpTrain net) {
+  constexpr int WV = MlpTrainShape<MB>::WAVES, W = 32 * MB, KS = 2 * MB, NB = (MB + WV - 1) / WV;
+  constexpr int AS = W + 8, FS = W + 4;
   __shared__ __attribute__((aligned(16))) __bf16 act[2][32 * AS];
   __shared__ __attribute__((aligned(16))) float dzs[32 * FS];
   __shared__ float dlast[32];
@@ -486,8 +490,10 @@ __global__ void __launch_bounds__(64 * MlpTrainShape<MB>::WAVES) mlp_train_kerne
       const bf16x8 b = on ? *reinterpret_cast<const bf16x8*>(feat + e * net.kin0 + 16 * kk + 8 * h) : zero8;
 #pragma unroll
       for (int n = 0; n < NB; ++n)
-        if (w + WV * n < MB)
-          acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q0[(int64_t)((w + WV * n) * ks0 + kk) * 64], b, acc[n], 0, 0, 0);
+        if (w + WV * n < MB) {
+          const bf16x8 a0 = q0[(int64_t)((w + WV * n) * ks0 + kk) * 64];
+          acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b, acc[n], 0, 0, 0);
+        }
       if (kk % WV == w) {
         if (on) *reinterpret_cast<bf16x8*>(net.h[0] + e * net.kin0 + 16 * kk + 8 * h) = b;
         __bf16* ht = net.ht[0] + (int64_t)(16 * kk + 8 * h) * nbs + e;
@@ -502,7 +508,7 @@ __global__ void __launch_bounds__(64 * MlpTrainShape<MB>::WAVES) mlp_train_kerne
   for (int ly = 1; ly < D; ++ly) {
     products(act[(ly - 1) & 1]);
     if (ly + 1 < D) weights(net.wf[ly + 1]);
-    else if (D > 1) weights(net.wb[D - 1]);
+    else weights(net.wb[D - 1]);
     activate(ly, act[ly & 1]);
     __syncthreads();
   }
@@ -593,8 +599,8 @@ __global__ void __launch_bounds__(64 * MlpTrainShape<MB>::WAVES) mlp_train_kerne
 // Weight and bias gradients of every layer from the transposed activations and output
 // gradients: block = one 32 x 32 tile of a layer's dW = dZ^T H (both operands have the
 // rows of the batch consecutive), its eight waves on interleaved K steps (there are only
-// some 200 tiles: latency of the loads is what it takes), their sums added in order; the last blocks add the workgroups' column sums (one layer each) and
-// squared errors.
+// some 200 tiles: latency of the loads is what it takes), their sums added in order; the
+// last blocks add the workgroups' column sums (one layer each) and squared errors.
 constexpr int kGradWaves = 8;
 struct MlpGrad {
   const __bf16* dzt[17];
@@ -1319,7 +1325,8 @@ int quantiles(const double* v, int arrays, int64_t n, double q, unsigned long lo
     hipLaunchKernelGGL(select_pass_kernel, dim3(nblk, arrays), dim3(256), 0, st, v, n, (unsigned long long)lo, pass,
                        words);
   // one sum and one minimum for all workgroups: no more of them than keep memory busy
-  hipLaunchKernelGGL(select_last_kernel, dim3(std::min(nblk, 64u), arrays), dim3(256), 0, st, v, n, (unsigned long long)lo, words);
+  hipLaunchKernelGGL(select_last_kernel, dim3(std::min(nblk, 64u), arrays), dim3(256), 0, st, v, n,
+                     (unsigned long long)lo, words);
   hipError_t e = hipGetLastError();
   SelectState state[2];
   if (e == hipSuccess)
@@ -1546,7 +1553,6 @@ int train_grads(me_sur_ctx* c, const uint16_t* feat, const float* target, int64_
   a.wlast = c->w16[L - 1];
   a.part = c->tpart;
   a.layers = L;
-  a.nfeat = c->nfeat;
   a.kin0 = c->kin0;
   a.outl = c->outp[L - 1];
   g.part = c->tpart;
