@@ -149,7 +149,8 @@ int me_compute(me_handle h, const double* momenta, int64_t nevt, double alpha_s,
  * allocation: its scratch (momenta as structure of arrays, 32 npar nevt bytes for
  * the one-lane kernel, and per-chunk partial sums, 8 nchunk nevt bytes, nchunk =
  * the helicity chunks that fill about target_waves wavefronts) lives in a static
- * device array of ME_NOALLOC_SCRATCH_BYTES.  Sizes needing more return ME_EINVAL
+ * device array of ME_NOALLOC_SCRATCH_BYTES (gg_ttx and gg_ttxg: one launch that does
+ * without, within the same limit).  Sizes needing more return ME_EINVAL
  * (gg_ttxggg: up to 299 593 events at one chunk).  The helicity filter must have
  * run (me_filter_helicities, or all_helicities = 1), else ME_EINVAL; the handle's
  * device must be current.  Results equal me_compute's with the lane executor and
@@ -333,9 +334,8 @@ int me_set_split(me_handle h, int wpe, int fchunk, int rounds, int colour_grid);
 /* Kernel of the Berends-Giele executor (paper, Discussion: the recursion for many
  * gluons): 0 = one (event, helicity) row per item with the default rows and
  * threads per workgroup, 1 = half of both, 2 = twice both (six gluons in FP64: the
- * kernel of 4 whichever is set, launches of no more events than the batch has); 3 =
- * helicity
- * recycling (four and five gluons: one workgroup per event(s), every current and
+ * kernel of 4 whichever is set, launches of no more events than the batch has);
+ * 3 = helicity recycling (four and five gluons: one workgroup per event(s), every current and
  * row spinor formed once per helicity assignment of its own particles, the full
  * orderings walked in rotation cycles); 4 = the recursion from both ends of the
  * quark line, one helicity of each mirror pair, canonical orderings of the long
@@ -344,8 +344,10 @@ int me_set_split(me_handle h, int wpe, int fchunk, int rounds, int colour_grid);
  * workgroup, no colour or reduction kernel, launches of as many event blocks as
  * ME_BG_FUSED_SCRATCH_BYTES of dual-amplitude slots hold; 5 = the same as one
  * persistent launch over the whole batch (scratch: one slot per resident workgroup,
- * 63 MB for g g -> t tbar g g g).  See
- * me_autotune.  ME_EINVAL for other values, and for 3, 4 and 5 on other processes.
+ * 63 MB for g g -> t tbar g g g; with five gluons 31 % slower than 4 on an MI355X).
+ * In 4 and 5 the split FP16 / BF16 colour forms cost more time than FP64, as a row and
+ * its mirror image round differently and each is formed: 30.2 and 31.8 ms against 27.6
+ * for 262144 g g -> t tbar g g g.  See me_autotune.  ME_EINVAL for other values, and for 3, 4 and 5 on other processes.
  * Results do not depend on it beyond rounding. */
 int me_set_bg(me_handle h, int variant);
 

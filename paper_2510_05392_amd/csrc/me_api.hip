@@ -231,7 +231,8 @@ struct me_ctx {
   int split_fchunk = 0;       // flows kernel: group sums per LDS chunk (8, 16, 32)
   int split_rounds = 0;       // events per chunk as whole rounds of group-sum waves (0: as many as fit)
   int colour_grid = 0;        // workgroups of the FP64 colour kernel
-  int bg_variant = 0;         // Berends-Giele kernel: launch shape 0, 1, 2; 3 = helicity recycling; 4, 5 = two-sided recursion, colour form fused
+  int bg_variant = 0;         // Berends-Giele kernel: launch shape 0, 1, 2; 3 = helicity recycling;
+                              // 4, 5 = two-sided recursion, colour form fused
   int bg_grid = 0;            // workgroups (scratch slots) per launch of the fused kernel
   int bg_resident = 0;        // its resident workgroups on the device
   bool tuned = false;         // me_autotune has run (or found its configuration in the cache)
@@ -1324,6 +1325,8 @@ int me_compute_noalloc(me_handle h, const double* momenta, int64_t nevt, double 
   nchunk = (nhel + hpc - 1) / hpc;
   const size_t soa_doubles = lane ? (size_t)nevt * h->desc->npar * 4 : 0;
   const size_t need = (soa_doubles + (size_t)nchunk * nevt) * sizeof(double);
+  // the limit is the call's contract for every process, also where one launch does
+  // without the scratch
   if (need > ME_NOALLOC_SCRATCH_BYTES)
     return fail(ME_EINVAL, "me_compute_noalloc: " + std::to_string(nevt) + " events need " + std::to_string(need) +
                                " bytes of scratch, more than ME_NOALLOC_SCRATCH_BYTES = " +

@@ -29,13 +29,15 @@
 // FP64 operations per event with all helicities (flops.bgm_event; counted by running
 // this code on a counting double): 3.47e6 for g g -> t t~ g g g against 19.1e6 of the
 // one-sided kernel of me_bgh.h, 0.27e6 against 1.24e6 for g g -> t t~ g g, 59.5e6 for
-// g g -> t t~ g g g g.  Bound by the issue of FP64 vector instructions: 42e3 a wave and
-// event on each of a compute unit's SIMDs, 18 ms of the 27.7 for 262144 five-gluon
-// events; the rest is latency of LDS and of the work-item records between barriers.  On
-// an MI355X, FP64 colour, against the one-sided kernel: 262144 g g -> t t~ g g g 27.7 ms
+// g g -> t t~ g g g g.  Bound by the issue of FP64 vector instructions: 40.4e3 vector
+// instructions an event, four cycles each on one of a compute unit's four SIMDs, are 68 %
+// of the 59.3e3 cycles that an event takes a compute unit (five gluons); the rest is
+// latency of LDS and of the work-item records between barriers.  On an MI355X, FP64
+// colour, against the one-sided kernel on the same card: 262144 g g -> t t~ g g g 27.7 ms
 // (149.7), 524288 g g -> t t~ g g 5.5 ms (18.8), 1000 g g -> t t~ g g g 0.12 ms (0.63);
 // split FP16 colour, 100003 g g -> t t~ g g g 11.5 ms (51.0); six gluons against the
-// one-row kernel of me_bg.h, 4096 events 11.1 ms (284).
+// one-row kernel of me_bg.h, 4096 events 11.1 ms (284).  Cards differ: another took 30.3,
+// 6.0, 0.13, 12.6 and 11.5 ms (152, 20.4, 0.63, 55.5 and 285).
 //
 // Frame of an event in LDS: slots of four complex numbers, component-major (component
 // c of slot s is the 16-byte element c NS + s), so that the 16-byte reads of lanes on
@@ -821,21 +823,33 @@ __device__ __forceinline__ int bgm_pick(const double* v, int first, int n, doubl
 
 #ifdef __HIPCC__
 // Workgroup of the fused kernels: EV events of WPE waves each, W waves per SIMD.
-// A five-gluon event (a frame of 67 KB) takes four waves, two workgroups to a compute
-// unit.  Six waves would divide its 384 currents of length 5 and 1152 prefix items
+// A five-gluon event (a frame of 79 KB) takes four waves, two workgroups to a compute
+// unit (160 KB).  Six waves would divide its 384 currents of length 5 and 1152 prefix items
 // evenly, but three waves a SIMD leave room for 168 registers each, and workgroups of
 // six waves were seen to run one at a time on a compute unit (65 ms for 262144 events
 // where four waves took 40, before later changes).  A four-gluon event (18 KB) is one
-// wave's work; four share a workgroup so that the set-up, which differs from lane to lane, is shared by kind.  A
-// six-gluon event (124 KB) has a compute unit to itself: eight waves, two a SIMD.
+// wave's work; four share a workgroup so that the set-up, which differs from lane to lane,
+// is shared by kind.  A six-gluon event (124 KB) has a compute unit to itself: eight waves, two a SIMD.
 template <int N> struct BgmLaunchShape;
 // LTAB: the work-item tables are copied to LDS first (four gluons: 7 KB, which leave two
 // workgroups to a compute unit; a record is then an LDS read, not one through the vector
 // cache in front of every item of the short phases: 524288 g g -> t t~ g g 5.51 ms
-// instead of 5.72).
-template <> struct BgmLaunchShape<4> { static constexpr int EV = 4, WPE = 1, W = 2; static constexpr bool LTAB = true; };
-template <> struct BgmLaunchShape<5> { static constexpr int EV = 1, WPE = 4, W = 2; static constexpr bool LTAB = false; };
-template <> struct BgmLaunchShape<6> { static constexpr int EV = 1, WPE = 8, W = 2; static constexpr bool LTAB = false; };
+// instead of 5.72 on one card).
+template <>
+struct BgmLaunchShape<4> {
+  static constexpr int EV = 4, WPE = 1, W = 2;
+  static constexpr bool LTAB = true;
+};
+template <>
+struct BgmLaunchShape<5> {
+  static constexpr int EV = 1, WPE = 4, W = 2;
+  static constexpr bool LTAB = false;
+};
+template <>
+struct BgmLaunchShape<6> {
+  static constexpr int EV = 1, WPE = 8, W = 2;
+  static constexpr bool LTAB = false;
+};
 
 // The items of a level to the threads, whole waves: the items of the next kind start
 // on a wave of their own.
@@ -1063,9 +1077,9 @@ __device__ __forceinline__ void bgm_butterfly(double* x) {
 
 // Five gluons: the forms of the 64 rows, by every wave of the workgroup.  Four lanes of
 // a wave (l % 16 equal) hold shares of a row's form; each hands its own to take(row,
-// share), all lanes at the same time.  A wave takes 16 rows: their real and then their imaginary parts are the columns of
-// v_mfma_f64_16x16x4f64, a sector's matrix its A operand (lane l: row l % 16, K index
-// l / 16), the orbits the K index.  A lane's four orbits o = 4 q + l / 16 are those of
+// share), all lanes at the same time.  A wave takes 16 rows: their real and then their
+// imaginary parts are the columns of v_mfma_f64_16x16x4f64, a sector's matrix its A
+// operand (lane l: row l % 16, K index l / 16), the orbits the K index.  A lane's four orbits o = 4 q + l / 16 are those of
 // its accumulator rows, so the dots use the operands in hand.  64 products per 16 rows
 // against 288 of the block-triangular form, and no matrix staged in LDS.
 template <int WAVES, typename Take>
@@ -1456,7 +1470,8 @@ bgm_fused_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt
     } else {
       double v = 0.0;
       if constexpr (N == 5)
-        bgm_colour5<WAVES>(slot, orb, sec, threadIdx.x, [&](int row, double f) { v += weight[row] ? (double)weight[row] * f : 0.0; });
+        bgm_colour5<WAVES>(slot, orb, sec, threadIdx.x,
+                           [&](int row, double f) { v += weight[row] ? (double)weight[row] * f : 0.0; });
       else
         v = bgm_colour6<WAVES>(bgm_lds, slot, orb, sec, weight);
       v = bgm_wave_sum(v);
@@ -1670,7 +1685,8 @@ hipError_t launch_bgm_select(const BgArgs& a) {
   if (!a.bgm || !a.orb || !a.sec || !a.out || !a.r_hel || !a.r_col || !a.sel_col || a.nhel < 1 ||
       a.nhel > (4 << N) || a.grid < 1 || (!a.counter && blocks > a.grid))
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(bgm_select_kernel<N>, dim3((unsigned)(blocks < a.grid ? blocks : a.grid)), dim3(bgm_threads<N>()), lds, a.stream, a.mom, a.n,
+  const unsigned grid = (unsigned)(blocks < a.grid ? blocks : a.grid);
+  hipLaunchKernelGGL(bgm_select_kernel<N>, dim3(grid), dim3(bgm_threads<N>()), lds, a.stream, a.mom, a.n,
                      a.g, a.mt, a.hels, a.nhel, a.bgm, a.orb, a.sec, a.jt, a.r_hel, a.r_col, a.out, a.sel_hel,
                      a.sel_col, a.out_scale, a.counter);
   return hipGetLastError();

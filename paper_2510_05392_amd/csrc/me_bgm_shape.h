@@ -12,7 +12,9 @@ struct BgmShape {
   static constexpr int fact(int n) { return perm(n, n); }
   static constexpr int comb(int n, int k) { return perm(n, k) / fact(k); }
   // variants of the sequences of length L: those with gluon 0, then those without
-  static constexpr int V(int L) { return L * perm(N - 1, L - 1) * (1 << (L - 1)) + (L < N ? perm(N - 1, L) * (1 << L) : 0); }
+  static constexpr int V(int L) {
+    return L * perm(N - 1, L - 1) * (1 << (L - 1)) + (L < N ? perm(N - 1, L) * (1 << L) : 0);
+  }
   // stored variants: J(c b a) = J(a b c), so of two mirrored sequences of length 3 one
   static constexpr int SV(int L) { return L == 3 ? V(3) / 2 : V(L); }
   // variants of the canonical sequences (lowest gluon first) of length L

@@ -66,8 +66,8 @@ hipError_t launch_pair(const PairArgs& a) {
   if (a.npair < 0 || a.npair > PairShape<P>::PAIRS) return hipErrorInvalidValue;
   for (int64_t off = 0; off < a.n; off += most) {
     const int64_t n = a.n - off < most ? a.n - off : most;
-    hipLaunchKernelGGL(pair_kernel<P>, dim3((unsigned)((n + kPairEvents - 1) / kPairEvents)), dim3((unsigned)THREADS), 0,
-                       a.stream, a.mom + off * (P::NPAR * 4), n, a.g, a.mt, a.pairs, a.npair,
+    const dim3 grid((unsigned)((n + kPairEvents - 1) / kPairEvents));
+    hipLaunchKernelGGL(pair_kernel<P>, grid, dim3((unsigned)THREADS), 0, a.stream, a.mom + off * (P::NPAR * 4), n, a.g, a.mt, a.pairs, a.npair,
                        a.alphas ? a.alphas + off : nullptr, a.out + off, a.scale);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
