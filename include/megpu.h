@@ -210,9 +210,10 @@ int me_num_channels(me_handle h, int32_t* nchan);
  *   out_me2[i] = as me_compute (FP64).
  * All outputs are device arrays of nevt entries.  Costs one me_compute plus
  * one helicity's dual amplitudes per event; with four and five gluons both draws come
- * out of the two-sided recursion's launch (me_set_bg 4) whatever the executor, with one
- * slot of scratch per resident workgroup (63 MB with five gluons, 25 MB with four;
- * fewer events, fewer slots). */
+ * out of the two-sided recursion's launch (me_set_bg 4) whatever the executor.  Its
+ * scratch: a slot of dual amplitudes for each event (123 KB with five gluons, 12 KB with
+ * four) up to four rounds of the resident workgroups (2048 events, 252 MB; 8192, 100 MB),
+ * one a resident workgroup for more events (63 MB; 25 MB). */
 int me_select(me_handle h, const double* momenta, int64_t nevt, double alpha_s, const double* r_hel,
               const double* r_col, double* out_me2, int32_t* sel_hel, int32_t* sel_col, void* stream);
 

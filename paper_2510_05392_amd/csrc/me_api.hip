@@ -236,7 +236,7 @@ struct me_ctx {
   int bg_grid = 0;            // workgroups (scratch slots) per launch of the fused kernel
   int bg_resident = 0;        // its resident workgroups on the device
   bool tuned = false;         // me_autotune has run (or found its configuration in the cache)
-  int* d_counter = nullptr;   // persistent work counter
+  int* d_counter = nullptr;   // persistent work counter, and that of the selection (0 between launches)
   int simds = 1024;           // compute units x 4
   // captured launch sequence of the last (momenta, out, nevt, alpha_s)
   hipStream_t capture_stream = nullptr;
@@ -718,7 +718,9 @@ int me_init(const char* process, const me_params* p, me_handle* out) {
       c->d_static = g_scratch_ptr[c->device];
     }
   }
-  if (hipMalloc(&c->d_counter, sizeof(int)) != hipSuccess ||
+  const int zeros[2] = {0, 0};
+  if (hipMalloc(&c->d_counter, sizeof(zeros)) != hipSuccess ||
+      hipMemcpy(c->d_counter, zeros, sizeof(zeros), hipMemcpyHostToDevice) != hipSuccess ||
       hipMalloc(&c->d_check, 2 * sizeof(unsigned long long)) != hipSuccess ||
       hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking) != hipSuccess) {
     (void)hipFree(c->d_hels);
@@ -1542,12 +1544,13 @@ static int select_two_sided(me_ctx* h, const double* momenta, int64_t nevt, doub
                             hipStream_t s) {
   int rc = ensure_bg_tables(h);
   if (rc) return rc;
-  // one slot per resident workgroup, whatever the batch
-  const int per_cu = h->bg->fused_per_cu();
-  if (per_cu < 1) return fail(ME_EHIP, "selection kernel: no resident workgroup fits");
+  // a slot a block up to four rounds of the resident workgroups, where it is the faster,
+  // else one a resident workgroup, which then takes blocks until there are none
+  if (h->bg_resident == 0) h->bg_resident = h->bg->fused_per_cu() * std::max(1, h->simds / 4);
+  if (h->bg_resident < 1) return fail(ME_EHIP, "selection kernel: no resident workgroup fits");
   const int ev = h->bg->fused_block_events();
   const int64_t blocks = (nevt + ev - 1) / ev;
-  const int64_t slots = std::min<int64_t>((int64_t)per_cu * std::max(1, h->simds / 4), blocks);
+  const int64_t slots = blocks <= 4 * (int64_t)h->bg_resident ? blocks : h->bg_resident;
   rc = ensure_sums(h, (size_t)slots * (size_t)h->bg->fused_slot_doubles());
   if (rc) return rc;
   me::BgArgs a{momenta, nevt, coupling(alpha_s), h->params.mt, h->d_hels, (int)h->good.size(), h->d_bg_sub,
@@ -1562,10 +1565,7 @@ static int select_two_sided(me_ctx* h, const double* momenta, int64_t nevt, doub
   a.out = out_me2;
   a.out_scale = 1.0 / ((double)h->desc->iden * (double)h->desc->cf_den);
   a.grid = (int)slots;
-  if (blocks > slots) {
-    hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, s, h->d_counter);
-    a.counter = reinterpret_cast<unsigned*>(h->d_counter);
-  }
+  a.counter = reinterpret_cast<unsigned*>(h->d_counter + 1);
   const hipError_t e = h->bg->launch(a);
   return e == hipSuccess ? ME_OK : hip_fail(e, "selection kernel launch");
 }

@@ -50,7 +50,7 @@ struct BgArgs {
   const double* r_col = nullptr;
   int* sel_hel = nullptr;
   int* sel_col = nullptr;
-  unsigned* counter = nullptr;   // cleared; not needed where one block a workgroup is all
+  unsigned* counter = nullptr;   // cleared once, and again by every launch that uses it
   double* out = nullptr;         // per-event |M|^2 [n] (nullptr: variant 4 runs as 3)
   double out_scale = 1.0;        // 1 / (IDEN x colour denominator)
   int grid = 0;                  // workgroups (= scratch slots)

@@ -1520,13 +1520,17 @@ __device__ __forceinline__ int bgm_draw(int l, int n, double r, Weight weight, d
 // that of both helicities of its mirror pair) and a flow with the |J_c|^2 of its row,
 // read back from the slot.  The row's amplitudes are there already: the one-lane route
 // formed every flow of every helicity from its diagrams and then those of the drawn one
-// once more.  16384 g g -> t t~ g g g on an MI355X: 1.77 ms, 106.7 by that route.  A
-// workgroup has one slot for all the blocks that it takes: a slot a block would be 2 GB of
-// scratch for these events, one a resident workgroup is 63 MB.  The first block is its
-// own, the others come from the counter (null: there are no others), as compute units do
-// not keep the same pace: block b + gridDim.x after b took 6 % more for 16384 events, 13 %
-// for 100003.
-template <int N>
+// once more.  16384 g g -> t t~ g g g on an MI355X: 1.77 ms, 106.7 by that route.
+// PERSIST: a workgroup has one slot for all the blocks that it takes (a slot a block would
+// be 2 GB of scratch for these events, one a resident workgroup is 63 MB).  The first is
+// its own, the others come from the counter, as compute units do not keep the same pace:
+// block b + gridDim.x after b took 6 % more for 16384 events, 13 % for 100003.  Every
+// block asks once, and the last to ask leaves the counter cleared for the next launch.
+// Up to four rounds of the resident workgroups every block has a slot and a workgroup of
+// its own: 600 and 1024 events 97 and 130 us (119 and 136 with PERSIST; four gluons, 2600
+// events, 43 and 55); from there on PERSIST is as fast (2600 events 311 us, 321 without)
+// and then faster (262144 four-gluon events 2.66 ms, 2.89).
+template <int N, bool PERSIST>
 __global__ void __launch_bounds__(64 * BgmLaunchShape<N>::EV * BgmLaunchShape<N>::WPE)
     __attribute__((amdgpu_waves_per_eu(BgmLaunchShape<N>::W)))
 bgm_select_kernel(const double* __restrict__ mom, int64_t n, double g0, double mt, const int* __restrict__ hels,
@@ -1544,13 +1548,19 @@ bgm_select_kernel(const double* __restrict__ mom, int64_t n, double g0, double m
   const uint32_t* items = bgm_tables<N>(bgm_lds, tabs);
   int64_t e0 = (int64_t)blockIdx.x * EV;
   while (e0 < n) {
-    // the block after this one, asked for now
     unsigned next = 0;
-    if (counter && threadIdx.x == 0) next = gridDim.x + atomicAdd(counter, 1u);
-    // an opaque zero: records and operands are read in each round, not held across rounds
     int o = 0, tid = threadIdx.x;
-    asm volatile("" : "+s"(o), "+v"(tid));
-    __builtin_assume(tid >= 0 && tid < 64 * WAVES);
+    if constexpr (PERSIST) {
+      // the block after this one, asked for now
+      if (threadIdx.x == 0) {
+        const unsigned k = atomicAdd(counter, 1u);
+        if (k == (unsigned)((n + EV - 1) / EV) - 1u) atomicExch(counter, 0u);
+        next = gridDim.x + k;
+      }
+      // an opaque zero: records and operands are read in each round, not held across rounds
+      asm volatile("" : "+s"(o), "+v"(tid));
+      __builtin_assume(tid >= 0 && tid < 64 * WAVES);
+    }
     const int nev = (int)(n - e0 < EV ? n - e0 : EV);
     bgm_events<N>(bgm_lds, items + o, mom + e0 * (N + 2) * 4, nullptr, nev, g0, mt, slot + o, tid, BghNoNote());
     __syncthreads();   // every amplitude of the block is stored
@@ -1587,7 +1597,7 @@ bgm_select_kernel(const double* __restrict__ mom, int64_t n, double g0, double m
         sel_col[e0 + w] = c;
       }
     }
-    if (!counter) return;
+    if constexpr (!PERSIST) return;
     if (threadIdx.x == 0) ticket = next;
     __syncthreads();   // the frames, the forms and the slot are the next block's
     e0 = (int64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)ticket) * EV;
@@ -1674,19 +1684,21 @@ hipError_t launch_bgm_fused_fmt(const BgArgs& a) {
   return hipGetLastError();
 }
 
-template <int N>
+// One block a workgroup where the launch's blocks are no more than a.grid slots, else
+// a.grid persistent workgroups.
+template <int N, bool PERSIST>
 hipError_t launch_bgm_select(const BgArgs& a) {
   constexpr int EV = BgmLaunchShape<N>::EV;
   constexpr size_t lds = bgm_lds_bytes<N>();
-  static const hipError_t attr = hipFuncSetAttribute((const void*)bgm_select_kernel<N>,
+  static const hipError_t attr = hipFuncSetAttribute((const void*)bgm_select_kernel<N, PERSIST>,
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (attr != hipSuccess) return attr;
   const int64_t blocks = (a.n + EV - 1) / EV;
   if (!a.bgm || !a.orb || !a.sec || !a.out || !a.r_hel || !a.r_col || !a.sel_col || a.nhel < 1 ||
-      a.nhel > (4 << N) || a.grid < 1 || (!a.counter && blocks > a.grid))
+      a.nhel > (4 << N) || a.grid < 1 || blocks > 0x7fffffff || (PERSIST ? !a.counter : blocks > a.grid))
     return hipErrorInvalidValue;
-  const unsigned grid = (unsigned)(blocks < a.grid ? blocks : a.grid);
-  hipLaunchKernelGGL(bgm_select_kernel<N>, dim3(grid), dim3(bgm_threads<N>()), lds, a.stream, a.mom, a.n,
+  const unsigned grid = (unsigned)(PERSIST ? a.grid : blocks);
+  hipLaunchKernelGGL((bgm_select_kernel<N, PERSIST>), dim3(grid), dim3(bgm_threads<N>()), lds, a.stream, a.mom, a.n,
                      a.g, a.mt, a.hels, a.nhel, a.bgm, a.orb, a.sec, a.jt, a.r_hel, a.r_col, a.out, a.sel_hel,
                      a.sel_col, a.out_scale, a.counter);
   return hipGetLastError();
@@ -1705,7 +1717,9 @@ hipError_t launch_bgm_fused_p(const BgArgs& a) {
 template <int N>
 hipError_t launch_bg(const BgArgs& a) {
   if constexpr (N == 4 || N == 5) {
-    if (a.sel_hel) return launch_bgm_select<N>(a);
+    if (a.sel_hel)
+      return (a.n + BgmLaunchShape<N>::EV - 1) / BgmLaunchShape<N>::EV > a.grid ? launch_bgm_select<N, true>(a)
+                                                                               : launch_bgm_select<N, false>(a);
     if ((a.variant == 4 || a.variant == 5) && a.out)
       return a.variant == 5 ? launch_bgm_fused_p<N, true>(a) : launch_bgm_fused_p<N, false>(a);
     if (a.variant >= 3) return launch_bgh<N>(a);

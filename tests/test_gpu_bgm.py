@@ -122,32 +122,38 @@ def test_selection_against_the_one_lane_sums(binding, name, npar, nevt):
         check(flows[k, e], rc[e], sc[e])
 
 
-@pytest.mark.parametrize('name,npar,nevt', [('gg_ttxgg', 6, 4 * 2 * 256 + 5), ('gg_ttxggg', 7, 2 * 2 * 256 + 3)])
-def test_selection_beyond_the_resident_workgroups(binding, name, npar, nevt):
-    """A workgroup that takes several blocks of events: every event's sum and draws are the
-    same bits as in a batch of the last seven events alone (an event's sums run in one
-    order wherever it stands)."""
+@pytest.mark.parametrize('name,npar,nevt', [('gg_ttxgg', 6, 4 * 4 * 512), ('gg_ttxgg', 6, 4 * 4 * 512 + 5),
+                                            ('gg_ttxggg', 7, 4 * 512), ('gg_ttxggg', 7, 4 * 512 + 3)])
+def test_selection_in_rounds_of_workgroups(binding, name, npar, nevt):
+    """Four rounds of 512 resident workgroups, and the first size beyond, where a workgroup
+    takes block after block: every event's sum and draws are the same bits as in batches of
+    the first and the last seven events alone (an event's sums run in one order wherever it
+    stands), in each of three calls."""
     _say(f'case selection in rounds {name} nevt={nevt}')
     mom = torch.from_numpy(rambo.generate(npar, nevt, 96)).cuda()
     rng = np.random.default_rng(nevt)
     rh, rc = (torch.from_numpy(rng.random(nevt)).cuda() for _ in range(2))
     m = binding.MatrixElement(name)
     m.me_filter_helicities(mom, nevt, AS)
-    res = []
-    for first in (0, nevt - 7):
-        n = nevt - first
-        out = torch.empty(n, dtype=torch.float64, device='cuda')
+
+    def select(first, n):
+        out = torch.zeros(n, dtype=torch.float64, device='cuda')
         sh, sc = (torch.full((n,), -1, dtype=torch.int32, device='cuda') for _ in range(2))
-        m.me_select(mom[first:], n, AS, rh[first:], rc[first:], out, sh, sc)
-        res.append([x.cpu().numpy()[-7:] for x in (out, sh, sc)])
+        m.me_select(mom[first:first + n], n, AS, rh[first:first + n], rc[first:first + n], out, sh, sc)
         assert int(sh.min()) >= 0 and int(sc.min()) >= 0 and bool(torch.all(out > 0))
-    assert all(np.array_equal(a, b) for a, b in zip(*res))
+        return [x.cpu().numpy() for x in (out, sh, sc)]
+
+    few = [select(0, 7), select(nevt - 7, 7)]
+    for _ in range(3):
+        all_ = select(0, nevt)
+        for want, part in zip(few, (slice(0, 7), slice(nevt - 7, nevt))):
+            assert all(np.array_equal(a[part], b) for a, b in zip(all_, want))
 
 
 def test_selection_scratch_is_bounded(binding):
-    """Scratch of one slot (123 KB with five gluons) per resident workgroup, 63 MB, and not
-    per event (2 GB for 16384 events)."""
-    _say('case selection scratch gg_ttxggg nevt=16384')
+    """Scratch of a slot (123 KB with five gluons) for each event of at most 2048, 252 MB,
+    or of one per resident workgroup, 63 MB, and not 2 GB for 16384 events."""
+    _say('case selection scratch gg_ttxggg')
     nevt = 16384
     mom = torch.from_numpy(rambo.generate(7, nevt, 97)).cuda()
     r = torch.rand(nevt, dtype=torch.float64, device='cuda')
@@ -157,6 +163,7 @@ def test_selection_scratch_is_bounded(binding):
     m.me_filter_helicities(mom, nevt, AS)
     torch.cuda.synchronize()
     before = torch.cuda.mem_get_info()[0]
-    m.me_select(mom, nevt, AS, r, r, out, sh, sc)
-    torch.cuda.synchronize()
-    assert before - torch.cuda.mem_get_info()[0] < 256 << 20
+    for n, most in ((nevt, 96 << 20), (2048, 288 << 20)):
+        m.me_select(mom, n, AS, r, r, out, sh, sc)
+        torch.cuda.synchronize()
+        assert before - torch.cuda.mem_get_info()[0] < most
