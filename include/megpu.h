@@ -212,8 +212,8 @@ int me_num_channels(me_handle h, int32_t* nchan);
  * one helicity's dual amplitudes per event; with four and five gluons both draws come
  * out of the two-sided recursion's launch (me_set_bg 4) whatever the executor.  Its
  * scratch: a slot of dual amplitudes for each event (123 KB with five gluons, 12 KB with
- * four) up to four rounds of the resident workgroups (2048 events, 252 MB; 8192, 100 MB),
- * one a resident workgroup for more events (63 MB; 25 MB). */
+ * four), at most those of four rounds of the resident workgroups (2048 events, 252 MB;
+ * 8192, 100 MB). */
 int me_select(me_handle h, const double* momenta, int64_t nevt, double alpha_s, const double* r_hel,
               const double* r_col, double* out_me2, int32_t* sel_hel, int32_t* sel_col, void* stream);
 

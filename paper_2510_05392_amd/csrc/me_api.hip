@@ -1544,14 +1544,14 @@ static int select_two_sided(me_ctx* h, const double* momenta, int64_t nevt, doub
                             hipStream_t s) {
   int rc = ensure_bg_tables(h);
   if (rc) return rc;
-  // a slot a block up to four rounds of the resident workgroups, where it is the faster,
-  // else one a resident workgroup, which then takes blocks until there are none
+  // a slot a block up to four rounds of the resident workgroups, where that is the faster;
+  // beyond, resident workgroups that take blocks until there are none (with no less
+  // scratch: a smaller batch after a larger one finds what it needs)
   if (h->bg_resident == 0) h->bg_resident = h->bg->fused_per_cu() * std::max(1, h->simds / 4);
   if (h->bg_resident < 1) return fail(ME_EHIP, "selection kernel: no resident workgroup fits");
   const int ev = h->bg->fused_block_events();
-  const int64_t blocks = (nevt + ev - 1) / ev;
-  const int64_t slots = blocks <= 4 * (int64_t)h->bg_resident ? blocks : h->bg_resident;
-  rc = ensure_sums(h, (size_t)slots * (size_t)h->bg->fused_slot_doubles());
+  const int64_t blocks = (nevt + ev - 1) / ev, most = 4 * (int64_t)h->bg_resident;
+  rc = ensure_sums(h, (size_t)std::min(blocks, most) * (size_t)h->bg->fused_slot_doubles());
   if (rc) return rc;
   me::BgArgs a{momenta, nevt, coupling(alpha_s), h->params.mt, h->d_hels, (int)h->good.size(), h->d_bg_sub,
                h->d_bg_mask, h->d_bg_last, nullptr, h->d_sums, s};
@@ -1564,7 +1564,7 @@ static int select_two_sided(me_ctx* h, const double* momenta, int64_t nevt, doub
   a.sel_col = (int*)sel_col;
   a.out = out_me2;
   a.out_scale = 1.0 / ((double)h->desc->iden * (double)h->desc->cf_den);
-  a.grid = (int)slots;
+  a.grid = (int)(blocks <= most ? blocks : h->bg_resident);
   a.counter = reinterpret_cast<unsigned*>(h->d_counter + 1);
   const hipError_t e = h->bg->launch(a);
   return e == hipSuccess ? ME_OK : hip_fail(e, "selection kernel launch");

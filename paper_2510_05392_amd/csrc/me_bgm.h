@@ -1522,10 +1522,10 @@ __device__ __forceinline__ int bgm_draw(int l, int n, double r, Weight weight, d
 // formed every flow of every helicity from its diagrams and then those of the drawn one
 // once more.  16384 g g -> t t~ g g g on an MI355X: 1.77 ms, 106.7 by that route.
 // PERSIST: a workgroup has one slot for all the blocks that it takes (a slot a block would
-// be 2 GB of scratch for these events, one a resident workgroup is 63 MB).  The first is
-// its own, the others come from the counter, as compute units do not keep the same pace:
-// block b + gridDim.x after b took 6 % more for 16384 events, 13 % for 100003.  Every
-// block asks once, and the last to ask leaves the counter cleared for the next launch.
+// be 2 GB of scratch for these events).  The first is its own, the others come from the
+// counter, as compute units do not keep the same pace: block b + gridDim.x after b took 6 %
+// more for 16384 events, 13 % for 100003.  Every block asks once, and the last to ask
+// leaves the counter cleared for the next launch.
 // Up to four rounds of the resident workgroups every block has a slot and a workgroup of
 // its own: 600 and 1024 events 97 and 130 us (119 and 136 with PERSIST; four gluons, 2600
 // events, 43 and 55); from there on PERSIST is as fast (2600 events 311 us, 321 without)
